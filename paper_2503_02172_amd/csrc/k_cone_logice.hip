@@ -326,46 +326,56 @@ void launch_logic_combine(int tnorm, const GroupArgs& g, const float* states, in
 
 // ---------------------------------------------------------------------------
 // ConE query packing for the VALU scorer: [row_block][k][field][TQ] with the
-// four fields cos(theta/2), sin(theta/2), cos(psi/2), sin(psi/2) of each
-// (complemented where the scored row is negated) query cone. One workgroup
-// per block of TQ rows; padding rows are zero.
+// five fields of each (complemented where the scored row is negated) query
+// cone that the scorer's max form reads (k_score.hip): tan(theta/2),
+// cos(psi/2) / r, sin(psi/2) / |cos(theta/2)|, sin(psi/2) / r and
+// r |cos(theta/2)|, r = center_reg. |cos(theta/2)| is at least 1e-18 and r at
+// least 2^-30, so every field and the scorer's products of them stay finite;
+// what the floors change is below the rounding of the sums. One workgroup per
+// block of TQ rows; padding rows are zero.
 // ---------------------------------------------------------------------------
 
 template <int TQ>
 __global__ __launch_bounds__(256) void k_pack_cone(const int32_t* src_row, const int32_t* neg, int n_rows,
-                                                   const float* states, int d, float* qpack)
+                                                   const float* states, int d, float r, float* qpack)
 {
     const int qb = blockIdx.x;
-    float* out = qpack + (int64_t)qb * d * 4 * TQ;
+    float* out = qpack + (int64_t)qb * d * 5 * TQ;
     for (int o = threadIdx.x; o < d * TQ; o += blockDim.x) {
         const int i = o % TQ, k = o / TQ;
         const int j = qb * TQ + i;
-        float ca = 0.f, sa = 0.f, cb = 0.f, sb = 0.f;
+        float f[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
         if (j < n_rows) {
             const float* st = states + (int64_t)src_row[j] * 2 * d;
             float th = st[k], ps = st[d + k];
             if (neg && neg[j]) cone_negate(th, ps);
+            float ca, sa, cb, sb;
             sincosf(0.5f * th, &sa, &ca);
             sincosf(0.5f * ps, &sb, &cb);
+            if (fabsf(ca) < 1e-18f) ca = 1e-18f;
+            f[0] = sa / ca;
+            f[1] = cb / r;
+            f[2] = sb / fabsf(ca);
+            f[3] = sb / r;
+            f[4] = r * fabsf(ca);
         }
-        float* dst = out + (int64_t)k * 4 * TQ + i;
-        dst[0] = ca;
-        dst[TQ] = sa;
-        dst[2 * TQ] = cb;
-        dst[3 * TQ] = sb;
+        float* dst = out + (int64_t)k * 5 * TQ + i;
+#pragma unroll
+        for (int t = 0; t < 5; ++t) dst[t * TQ] = f[t];
     }
 }
 
 void launch_pack_cone(const int32_t* src_row, const int32_t* neg, int n_rows, int n_rows_pad, const float* states,
-                      int d, float* qpack, hipStream_t s)
+                      int d, float center_reg, float* qpack, hipStream_t s)
 {
     if (n_rows_pad <= 0) return;
     const int tq = score_tq(KGQ_CONE, n_rows);
     const dim3 grid(n_rows_pad / tq);
+    const float r = std::max(center_reg, 0x1p-30f);
     if (score_small(n_rows))
-        hipLaunchKernelGGL(k_pack_cone<kTqConeSmall>, grid, dim3(256), 0, s, src_row, neg, n_rows, states, d, qpack);
+        hipLaunchKernelGGL(k_pack_cone<kTqConeSmall>, grid, dim3(256), 0, s, src_row, neg, n_rows, states, d, r, qpack);
     else
-        hipLaunchKernelGGL(k_pack_cone<kTqCone>, grid, dim3(256), 0, s, src_row, neg, n_rows, states, d, qpack);
+        hipLaunchKernelGGL(k_pack_cone<kTqCone>, grid, dim3(256), 0, s, src_row, neg, n_rows, states, d, r, qpack);
 }
 
 }  // namespace kgq

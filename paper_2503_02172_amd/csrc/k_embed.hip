@@ -618,7 +618,7 @@ __global__ __launch_bounds__(256) void k_pack_rows(const int32_t* src_row, const
 }
 
 void launch_pack(int model, const int32_t* src_row, const int32_t* neg, int n_rows, int n_rows_pad,
-                 const float* states, int W, int d, float* qpack, double* cq, hipStream_t s)
+                 const float* states, int W, int d, float center_reg, float* qpack, double* cq, hipStream_t s)
 {
     if (n_rows_pad <= 0) return;
     if (model == KGQ_BETAE) {
@@ -627,7 +627,7 @@ void launch_pack(int model, const int32_t* src_row, const int32_t* neg, int n_ro
         return;
     }
     if (model == KGQ_CONE) {
-        launch_pack_cone(src_row, neg, n_rows, n_rows_pad, states, d, qpack, s);
+        launch_pack_cone(src_row, neg, n_rows, n_rows_pad, states, d, center_reg, qpack, s);
         return;
     }
     const int tq = score_tq(model, n_rows);

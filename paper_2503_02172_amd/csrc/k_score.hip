@@ -27,16 +27,23 @@
 //           regrouping of dist_out + center_reg * dist_in
 //           (t <= o: center_reg * t; t > o: (t - o) + center_reg * o)
 //   ConE    with the entity's half-angle sine / cosine (Se, Ce) from the
-//           table and the query's (Ca, Sa) of theta/2 and (Cb, Sb) of psi/2:
-//           s = Se Ca - Ce Sa = sin((theta_e - theta)/2),
-//           c = Ce Ca + Se Sa = cos((theta_e - theta)/2),
-//           t = |s| Cb - |c| Sb;  acc1 += max(t, 0);  acc2 += min(|s|, Sb) (10,
-//           plus Cb and Sb moved to vector registers once per row and step)
-//           score = gamma - modulus (acc1 + center_reg acc2). This is the
-//           sector distance exactly: min(|sin(a + b)|, |sin(a - b)|) =
-//           ||sin a| cos b - |cos a| sin b| for b = psi/2 in [0, pi/2], and
-//           the bracket is negative exactly when |sin a| < sin b, i.e. inside
-//           the sector, where the outside distance is 0.
+//           table and the query's five values per dimension (k_pack_cone),
+//           T = tan(theta/2), p = cos b / r, q = sin b / cos(theta/2),
+//           n = sin b / r, w = r cos(theta/2), b = psi/2, r = center_reg:
+//           u = Se - Ce T, v = Ce + Se T,
+//           acc += w max(|u|, p |u| - n |v| + q)                          (6,
+//           plus T and q moved to vector registers once per row and step)
+//           score = gamma - modulus acc. This is the sector distance exactly.
+//           With x the folded half-angle between the axes (sin x = cos(theta/2)
+//           |u|, cos x = cos(theta/2) |v|), the outside distance is
+//           sin(x - b) for x > b, else 0, and the inside distance
+//           min(sin x, sin b); for 0 <= r <= 1 their weighted sum is
+//           max(r sin x, r sin b + sin(x - b)), since sin x <= sin b +
+//           sin(x - b) outside and sin b <= sin x + sin(b - x) inside.
+//           One accumulator and 6 instructions, where the two distances
+//           kept apart (the angle difference from products of sines and
+//           cosines) took two and 10: the 4,480-row sweep over 14,505
+//           entities at d = 400 went from 4.80 to 3.47 ms.
 // Union (disjunctive normal form, Eq. 1 of the paper): a query whose answer
 // has 2 conjunctive terms has two adjacent rows (a pair), one with 3 or 4
 // terms a group of four rows; its score is the max over the rows' scores.
@@ -117,9 +124,9 @@ __global__ __launch_bounds__(256) void k_score(ScoreArgs a, int nqg, int qchunk,
     const int qb = qg * 4 + wave;
     if (qb * TQ >= a.n_rows) return;
 
-    constexpr int F = (MODEL == 0) ? 1 : (MODEL == 1 ? 2 : 4);   // query fields per row
+    constexpr int F = (MODEL == 0) ? 1 : (MODEL == 1 ? 2 : 5);   // query fields per row
     constexpr int EF = (MODEL == 3) ? 2 : 1;                       // entity fields per dimension
-    constexpr bool TWO = MODEL != 0;                               // two accumulators per triple
+    constexpr bool TWO = MODEL == 1;                               // two accumulators per triple
     constexpr int AF = TWO ? 2 : 1;                                // accumulator fields (split-d partials)
     // Small batches split the dimensions over blockIdx.y: slice z covers
     // [z * kslice, z * kslice + d) (kslice and d multiples of 4) and writes
@@ -170,24 +177,23 @@ __global__ __launch_bounds__(256) void k_score(ScoreArgs a, int nqg, int qchunk,
                 for (int j = 0; j < 4; ++j) acc[i][j] += fabsf(e4[j] - c);
             } else if (MODEL == 3) {
                 const float ce4[4] = {eu.v[EF - 1].x, eu.v[EF - 1].y, eu.v[EF - 1].z, eu.v[EF - 1].w};
-                const float sa = qv[TQ + i];
-                // the aperture's cosine and sine as vector operands: the VALU
-                // takes a scalar operand on at most every other issue cycle,
-                // and with them in SGPRs 7 of the triple's 10 instructions
-                // would read one (2 moves per row and step, per 4 triples:
-                // the scorer at the 14,505-entity ConE workload went from
-                // 4.75 to 4.00 ms)
-                float cb, sb;
-                asm("v_mov_b32 %0, %1" : "=v"(cb) : "s"(qv[2 * TQ + i]));
-                asm("v_mov_b32 %0, %1" : "=v"(sb) : "s"(qv[3 * TQ + i]));
+                // tan and sin b / cos as vector operands: the VALU takes a
+                // scalar operand on at most every other issue cycle, and a
+                // fused multiply-add one in all (2 moves per row and step,
+                // per 4 triples)
+                float t, q;
+                asm volatile("v_mov_b32 %0, %1" : "=v"(t) : "s"(c));
+                asm volatile("v_mov_b32 %0, %1" : "=v"(q) : "s"(qv[2 * TQ + i]));
+                float p;
+                asm volatile("v_mov_b32 %0, %1" : "=v"(p) : "s"(qv[TQ + i]));
+                const float n = qv[3 * TQ + i], w = qv[4 * TQ + i];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const float sn = fmaf(-ce4[j], sa, e4[j] * c);    // sin((theta_e - theta) / 2)
-                    const float cs = fmaf(e4[j], sa, ce4[j] * c);     // cos((theta_e - theta) / 2)
-                    const float as = fabsf(sn);
-                    const float t = fmaf(-fabsf(cs), sb, as * cb);
-                    acc[i][j] += __builtin_fmaxf(t, 0.f);
-                    acc2[i][j] += __builtin_fminf(as, sb);
+                    const float u = fmaf(-ce4[j], t, e4[j]);     // sin((theta_e - theta) / 2) / cos(theta / 2)
+                    const float v = fmaf(e4[j], t, ce4[j]);      // cos((theta_e - theta) / 2) / cos(theta / 2)
+                    const float au = fabsf(u);
+                    const float x = fmaf(-n, fabsf(v), fmaf(p, au, q));
+                    acc[i][j] = fmaf(w, __builtin_fmaxf(au, x), acc[i][j]);
                 }
             } else {
                 const float o = qv[TQ + i];
@@ -203,6 +209,13 @@ __global__ __launch_bounds__(256) void k_score(ScoreArgs a, int nqg, int qchunk,
     using H0 = std::integral_constant<int, 0>;
     using H1 = std::integral_constant<int, TQ / 2>;
     using H2 = std::integral_constant<int, TQ>;
+    // ConE's one accumulator holds a larger sum than the outside distance's
+    // did; in two halves (the first waits in LDS) its rounding is half as
+    // large, and below that of the two accumulators it replaces.
+    constexpr bool HALVES = MODEL == 3;
+    __shared__ float4 half_sum[HALVES ? TQ : 1][HALVES ? 256 : 1];
+    const int k_half = d / 8 * 4;
+
     EVec ua, ub;
     float qa[QN], qb2[QN];
     load_e(0, ua);
@@ -226,6 +239,28 @@ __global__ __launch_bounds__(256) void k_score(ScoreArgs a, int nqg, int qchunk,
         for (int t = 0; t < QN; ++t) qa[t] = qc[k2 * QN + t];
         __builtin_amdgcn_sched_barrier(0);
         compute(ub, qb2, H1{}, H2{});
+        if constexpr (HALVES) {
+            if (k + 2 == k_half) {
+#pragma unroll
+                for (int i = 0; i < TQ; ++i) {
+                    half_sum[i][threadIdx.x] = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
+                }
+            }
+        }
+    }
+    if constexpr (HALVES) {
+        if (k_half > 0) {
+#pragma unroll
+            for (int i = 0; i < TQ; ++i) {
+                const float4 h = half_sum[i][threadIdx.x];
+                acc[i][0] += h.x;
+                acc[i][1] += h.y;
+                acc[i][2] += h.z;
+                acc[i][3] += h.w;
+            }
+        }
     }
 
     // Epilogue: finish the scores, merge union pairs, store.
@@ -267,8 +302,7 @@ __global__ __launch_bounds__(256) void k_score(ScoreArgs a, int nqg, int qchunk,
         for (int u = 0; u < 4; ++u)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                if (MODEL == 0) sc[u][j] = a.gamma - a.dist_scale * acc[i + u][j];
-                else if (MODEL == 3) sc[u][j] = a.gamma - a.dist_scale * fmaf(a.center_reg, acc2[i + u][j], acc[i + u][j]);
+                if (MODEL != 1) sc[u][j] = a.gamma - a.dist_scale * acc[i + u][j];
                 else sc[u][j] = a.gamma - acc[i + u][j] + (1.0f - a.center_reg) * acc2[i + u][j];
             }
         if (row < a.n_quad) {
@@ -301,7 +335,7 @@ __global__ __launch_bounds__(256) void k_score(ScoreArgs a, int nqg, int qchunk,
 template <int MODEL>
 __global__ __launch_bounds__(256) void k_score_sum(ScoreArgs a, int splits, int64_t rows_pad, int n_out)
 {
-    constexpr int F = (MODEL == 0) ? 1 : 2;     // accumulator fields of the partials (as AF in k_score)
+    constexpr int F = (MODEL == 1) ? 2 : 1;     // accumulator fields of the partials (as AF in k_score)
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= (int64_t)n_out * a.N) return;
     const int o = (int)(t / a.N);
@@ -325,11 +359,10 @@ __global__ __launch_bounds__(256) void k_score_sum(ScoreArgs a, int splits, int6
         for (int z = 0; z < splits; ++z) {
             const float* pz = a.part + (int64_t)z * F * rows_pad * n_pad;
             s1 += pz[(int64_t)(r0 + u) * n_pad + e];
-            if (MODEL != 0) s2 += pz[(rows_pad + r0 + u) * n_pad + e];
+            if (MODEL == 1) s2 += pz[(rows_pad + r0 + u) * n_pad + e];
         }
-        const float v = MODEL == 0   ? a.gamma - a.dist_scale * s1
-                        : MODEL == 3 ? a.gamma - a.dist_scale * fmaf(a.center_reg, s2, s1)
-                                     : a.gamma - s1 + (1.0f - a.center_reg) * s2;
+        const float v =
+            MODEL != 1 ? a.gamma - a.dist_scale * s1 : a.gamma - s1 + (1.0f - a.center_reg) * s2;
         best = u == 0 ? v : fmaxf(best, v);
     }
     a.scores[(int64_t)a.out_dest[o] * a.ld + e] = best;
@@ -346,7 +379,7 @@ bool launch_score(const ScoreArgs& a, hipStream_t s)
     const int nqg = (nqb + 3) / 4;
     const int total = (int)(a.n_blocks * nqg);
     const int per_xcd = (total + 7) / 8;
-    const int QF = form == KGQ_GQE ? 1 : (form == KGQ_Q2B ? 2 : 4);   // query fields
+    const int QF = form == KGQ_GQE ? 1 : (form == KGQ_Q2B ? 2 : 5);   // query fields
     // query chunk: as many query groups as ~2 MiB of packed queries (about
     // half an XCD's L2); the entity table is streamed once per chunk, and the
     // XCDs split the global order evenly whatever the chunk size
@@ -356,7 +389,7 @@ bool launch_score(const ScoreArgs& a, hipStream_t s)
     // latency chain on a few compute units, so the dimensions are split over
     // up to 16 slices (each at least 16 dimensions) whose partials fit the
     // lane's workspace; a second kernel sums them.
-    const int F = form == KGQ_GQE ? 1 : 2;         // accumulator fields
+    const int F = form == KGQ_Q2B ? 2 : 1;         // accumulator fields
     const int64_t rows_pad = (int64_t)nqg * 4 * tq, n_pad = a.n_blocks * kEntBlock;
     int splits = 1;
     if (a.part && total < 128 && a.d >= 32) {
@@ -387,12 +420,10 @@ bool launch_score(const ScoreArgs& a, hipStream_t s)
         const int n_out = (a.n_quad >> 2) + (a.n_pair >> 1) + (a.n_rows - a.n_quad - a.n_pair);
         const int64_t tot = (int64_t)n_out * a.N;
         const dim3 g2((unsigned)((tot + 255) / 256));
-        if (form == KGQ_GQE)
-            hipLaunchKernelGGL((k_score_sum<0>), g2, dim3(256), 0, s, b, z, rows_pad, n_out);
-        else if (form == KGQ_Q2B)
+        if (form == KGQ_Q2B)
             hipLaunchKernelGGL((k_score_sum<1>), g2, dim3(256), 0, s, b, z, rows_pad, n_out);
         else
-            hipLaunchKernelGGL((k_score_sum<3>), g2, dim3(256), 0, s, b, z, rows_pad, n_out);
+            hipLaunchKernelGGL((k_score_sum<0>), g2, dim3(256), 0, s, b, z, rows_pad, n_out);
     }
     return b.chunk_key != nullptr;
 }

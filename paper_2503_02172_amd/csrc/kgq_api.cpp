@@ -324,11 +324,11 @@ void free_all(kgq_handle* h)
 }
 
 // Floats of one scored row in the packed query buffer: GQE d; Query2Box
-// (center, offset), BetaE (alpha, beta) and LogicE (l, u) 2d; ConE 4d (the
-// half-angle cosine and sine of axis and aperture).
+// (center, offset), BetaE (alpha, beta) and LogicE (l, u) 2d; ConE 5d (the
+// fields of k_pack_cone).
 int64_t qpack_row_floats(int model, int d)
 {
-    return (int64_t)d * (model == KGQ_GQE ? 1 : model == KGQ_CONE ? 4 : 2);
+    return (int64_t)d * (model == KGQ_GQE ? 1 : model == KGQ_CONE ? 5 : 2);
 }
 
 kgq_status allocate_all(kgq_handle* h)
@@ -766,7 +766,7 @@ kgq_status run_plan(kgq_handle* h, Lane& L, const Plan& p, const int32_t* P, con
     {
         StageTimer t(h, 3, s);
         launch_pack(c.model, P + p.off_score_src, mlp ? P + p.off_score_neg : nullptr, p.n_score_rows, n_rows_pad,
-                    L.states, W, d_score, L.qpack, L.cq, s);
+                    L.states, W, d_score, c.center_reg, L.qpack, L.cq, s);
     }
     float* dst = out_scores ? out_scores : L.scores;
     bool keyed = false;   // the scorer wrote chunk keys for top-k

@@ -206,7 +206,7 @@ void launch_betae_proj_prep(const int32_t* src_row, const int32_t* anchor_ref, c
 // Pack scored rows into the scorer's layout; BetaE also C_q = sum lnB(a, b)
 // and the reciprocal of rows with neg[j] != 0 (neg may be NULL).
 void launch_pack(int model, const int32_t* src_row, const int32_t* neg, int n_rows, int n_rows_pad,
-                 const float* states, int W, int d, float* qpack, double* cq, hipStream_t s);
+                 const float* states, int W, int d, float center_reg, float* qpack, double* cq, hipStream_t s);
 
 // ---- ConE / LogicE (k_cone_logice.hip) ----
 void launch_cone_entity_prep(const float* src, int64_t N, int d, int64_t n_blocks, float* ent_rm, float* blocked,
@@ -229,7 +229,7 @@ void launch_cone_combine_arg(const GroupArgs& g, const float* states, const floa
 void launch_logic_combine(int tnorm, const GroupArgs& g, const float* states, int d, float* out_states,
                           hipStream_t s);
 void launch_pack_cone(const int32_t* src_row, const int32_t* neg, int n_rows, int n_rows_pad, const float* states,
-                      int d, float* qpack, hipStream_t s);
+                      int d, float center_reg, float* qpack, hipStream_t s);
 
 // Order-preserving key of a score: unsigned comparison of keys orders the
 // scores as floats, -0 and +0 equal (NaNs sort by their bits, above +inf or
