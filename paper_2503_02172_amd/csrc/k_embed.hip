@@ -17,6 +17,7 @@
 // them: an out-of-range id raises a flag bit and is replaced by 0, so no
 // access ever leaves a table.
 #include <algorithm>
+#include <cmath>
 
 #include "kgq_internal.hpp"
 
@@ -37,32 +38,152 @@ __device__ __forceinline__ float load_param(const void* src, int bf16, int64_t i
 // Load-time kernels
 // ---------------------------------------------------------------------------
 
-// One thread per entity slot of the padded table; writes the blocked
-// dimension-major layout (coalesced across threads) and a row-major copy.
-__global__ void k_relayout_points(const void* src, int bf16, int64_t N, int d, int64_t n_pad,
-                                  float* rowmajor, float* blocked)
+// 64 entities x 64 coordinates per workgroup, transposed through LDS: rows are
+// read (and copied row-major in float32) along the coordinates, the blocked
+// dimension-major layout is written along the entities.
+__global__ __launch_bounds__(256) void k_relayout_points(const void* src, int bf16, int64_t N, int d,
+                                                         float* rowmajor, float* blocked)
 {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n_pad) return;
-    const int64_t blk = e / kEntBlock;
-    const int lo = (int)(e % kEntBlock);
-    float* dst = blocked + blk * (int64_t)d * kEntBlock + lo;
-    for (int k = 0; k < d; ++k) {
-        float v = 0.f;
-        if (e < N) {
-            v = load_param(src, bf16, e * d + k);
-            rowmajor[e * d + k] = v;
+    __shared__ float tile[64][65];
+    const int t = threadIdx.x;
+    const int64_t e0 = (int64_t)blockIdx.x * 64;
+    const int k0 = blockIdx.y * 64, c = k0 + (t & 15) * 4;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = (t >> 4) + 16 * i;
+        const int64_t at = (e0 + r) * d + c;
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (e0 + r < N && c < d) {      // (d is a multiple of 4)
+            if (bf16) {
+                const ushort4 h = *reinterpret_cast<const ushort4*>(reinterpret_cast<const uint16_t*>(src) + at);
+                v = make_float4(bf16_to_f32(h.x), bf16_to_f32(h.y), bf16_to_f32(h.z), bf16_to_f32(h.w));
+            } else {
+                v = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(src) + at);
+            }
+            *reinterpret_cast<float4*>(rowmajor + at) = v;
         }
-        dst[(int64_t)k * kEntBlock] = v;
+        float (*col)[65] = tile + (t & 15) * 4;
+        col[0][r] = v.x;
+        col[1][r] = v.y;
+        col[2][r] = v.z;
+        col[3][r] = v.w;
     }
+    __syncthreads();
+    float* dst = blocked + (e0 / kEntBlock) * (int64_t)d * kEntBlock + e0 % kEntBlock + (t & 63);
+    for (int k = t >> 6; k < 64 && k0 + k < d; k += 4) dst[(int64_t)(k0 + k) * kEntBlock] = tile[k][t & 63];
 }
 
 void launch_relayout_points(const void* src, int src_bf16, int64_t N, int d, int64_t n_blocks,
                             float* rowmajor, float* blocked, hipStream_t s)
 {
-    const int64_t n_pad = n_blocks * kEntBlock;
-    hipLaunchKernelGGL(k_relayout_points, dim3((unsigned)((n_pad + 255) / 256)), dim3(256), 0, s,
-                       src, src_bf16, N, d, n_pad, rowmajor, blocked);
+    hipLaunchKernelGGL(k_relayout_points, dim3((unsigned)(n_blocks * (kEntBlock / 64)), (d + 63) / 64), dim3(256), 0, s,
+                       src, src_bf16, N, d, rowmajor, blocked);
+}
+
+// Sum of one value per thread over a workgroup of 256, the same in each.
+__device__ __forceinline__ double block_sum(double v)
+{
+    __shared__ double sh[4];
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+
+__global__ __launch_bounds__(256) void k_table_range(const float4* __restrict__ x, int64_t n4, double* __restrict__ part)
+{
+    __shared__ float sh_lo[4], sh_hi[4];
+    float lo = __builtin_inff(), hi = -__builtin_inff();
+    double sum = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)kStatBlocks * 256) {
+        const float4 v = x[i];
+        lo = fminf(fminf(fminf(lo, v.x), fminf(v.y, v.z)), v.w);
+        hi = fmaxf(fmaxf(fmaxf(hi, v.x), fmaxf(v.y, v.z)), v.w);
+        sum += ((double)v.x + (double)v.y) + ((double)v.z + (double)v.w);
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        lo = fminf(lo, __shfl_xor(lo, off, 64));
+        hi = fmaxf(hi, __shfl_xor(hi, off, 64));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        sh_lo[threadIdx.x >> 6] = lo;
+        sh_hi[threadIdx.x >> 6] = hi;
+    }
+    sum = block_sum(sum);
+    if (threadIdx.x == 0) {
+        double* o = part + 4 * blockIdx.x;
+        o[0] = fminf(fminf(sh_lo[0], sh_lo[1]), fminf(sh_lo[2], sh_lo[3]));
+        o[1] = fmaxf(fmaxf(sh_hi[0], sh_hi[1]), fmaxf(sh_hi[2], sh_hi[3]));
+        o[2] = sum;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_table_deviation(const float4* __restrict__ x, int64_t n4,
+                                                         double* __restrict__ part)
+{
+    double mean = 0.0;
+    for (int b = threadIdx.x; b < kStatBlocks; b += 256) mean += part[4 * b + 2];
+    mean = block_sum(mean) / (4.0 * (double)n4);
+    double dev = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)kStatBlocks * 256) {
+        const float4 v = x[i];
+        dev += (fabs((double)v.x - mean) + fabs((double)v.y - mean)) + (fabs((double)v.z - mean) + fabs((double)v.w - mean));
+    }
+    dev = block_sum(dev);
+    if (threadIdx.x == 0) part[4 * blockIdx.x + 3] = dev;
+}
+
+void launch_table_stats(const float* x, int64_t n, double* part, hipStream_t s)
+{
+    const float4* x4 = reinterpret_cast<const float4*>(x);
+    hipLaunchKernelGGL(k_table_range, dim3(kStatBlocks), dim3(256), 0, s, x4, n / 4, part);
+    hipLaunchKernelGGL(k_table_deviation, dim3(kStatBlocks), dim3(256), 0, s, x4, n / 4, part);
+}
+
+// The quantisation error of a distance, each of its 2 x width values off by
+// at most half a quantum and 0.29 of one at the root mean square, is 0.41
+// sqrt(width) quanta; that of a float sum of width terms of mean size t grows
+// to 0.25 sqrt(width) 2^-24 (width t). The table takes the fixed-point form
+// while the first is at most a quarter of the second with t = mad, the mean
+// absolute deviation (an entity and a query state differ by that or more):
+// tables of uniform values from a width of 53 on, of normal ones (range 9
+// deviations) from 150, and tables whose outliers stretch the range beyond
+// about 30 mad at width 400 not at all. Measured error against 64 bits on
+// uniform tables: 1.1e-6 in floats, 5.4e-7 here (63,361 x 400); 1.9e-7 and
+// 1.1e-7 (LogicE, 14,505 x 800).
+L1Fixed choose_l1_fixed(double lo, double hi, double sum, double mad, int width)
+{
+    L1Fixed f;
+    const double range = hi - lo;
+    if (!(sum - sum == 0.0) || !(range > 0.0) || !(range < 1e30) || !(range > 1e-30)) return f;   // NaN, inf, no range
+    const double u_max = std::min(8388607.0, std::floor(4294967295.0 / width));
+    const float q = std::nextafter((float)(range / u_max), 1e38f);     // range / q <= u_max
+    if (0.41 * (double)q > 0.25 * 0.25 * 0x1p-24 * width * mad) return f;
+    f.on = true;
+    f.lo = (float)lo;
+    f.hi = (float)hi;
+    f.quantum = q;
+    return f;
+}
+
+__global__ __launch_bounds__(256) void k_l1_quantise(float4* __restrict__ blk, int64_t n4, L1Fixed f, double inv_quantum)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n4) return;
+    const float4 v = blk[i];
+    double ex = 0.0;
+    blk[i] = make_float4(__uint_as_float(l1_fixed_bits(v.x, f, inv_quantum, ex)),
+                         __uint_as_float(l1_fixed_bits(v.y, f, inv_quantum, ex)),
+                         __uint_as_float(l1_fixed_bits(v.z, f, inv_quantum, ex)),
+                         __uint_as_float(l1_fixed_bits(v.w, f, inv_quantum, ex)));
+}
+
+void launch_l1_quantise(float* blk, int64_t n, const L1Fixed& f, hipStream_t s)
+{
+    const int64_t n4 = n / 4;
+    hipLaunchKernelGGL(k_l1_quantise, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s,
+                       reinterpret_cast<float4*>(blk), n4, f, 1.0 / (double)f.quantum);
 }
 
 // Digamma for x > 0 in double precision: shift the argument up with
@@ -574,6 +695,91 @@ __global__ __launch_bounds__(256) void k_pack(const int32_t* src_row, const int3
             out[(int64_t)k0 * F * TQ + o] = tile[i * RS + f * KC + kk];
         }
         __syncthreads();
+    }
+}
+
+// The same layout in fixed point (L1Fixed; one field), for the L1 scorer's
+// integer form, and each row's base. A wavefront takes whole rows (every
+// fourth of the block's), so that a row's clamped amount is one wave sum in a
+// fixed order.
+template <int TQ, bool NEGL>
+__global__ __launch_bounds__(256) void k_pack_l1(const int32_t* src_row, const int32_t* neg, int n_rows,
+                                                 const float* states, int W, int d, L1Fixed f, double inv_quantum,
+                                                 float gamma, float dist_scale, uint32_t* qpack, double* base)
+{
+    constexpr int KC = 8192 / TQ / 4 * 4;     // coordinates per chunk (a 32 KiB tile)
+    constexpr int RS = KC + 1;
+    constexpr int RW = TQ / 4;                // rows per wavefront
+    constexpr int PER = (KC + 255) / 256;     // float4 loads per lane, row and chunk
+    __shared__ uint32_t tile[TQ * RS];
+    const int qb = blockIdx.x;
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int half = d / 2;
+    int src[RW];
+    bool ng[RW];
+    double ex[RW];
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+        const int j = qb * TQ + wave + 4 * r;
+        src[r] = j < n_rows ? src_row[j] : -1;
+        ng[r] = NEGL && j < n_rows && neg && neg[j];
+        ex[r] = 0.0;
+    }
+    uint32_t* out = qpack + (int64_t)qb * d * TQ;
+    for (int k0 = 0; k0 < d; k0 += KC) {
+        const int kc = min(KC, d - k0);
+        // every load of the chunk first (clamped into the row: no branch)
+        float4 v[RW][PER];
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+#pragma unroll
+            for (int p = 0; p < PER; ++p) {
+                int col = k0 + min(4 * (lane + 64 * p), kc - 4);
+                if (NEGL && ng[r]) col = col >= half ? col - half : col + half;
+                v[r][p] = *reinterpret_cast<const float4*>(states + (int64_t)max(src[r], 0) * W + col);
+            }
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+#pragma unroll
+            for (int p = 0; p < PER; ++p) {
+                const int k = 4 * (lane + 64 * p);
+                if (k >= kc) continue;
+                float x[4] = {v[r][p].x, v[r][p].y, v[r][p].z, v[r][p].w};
+                uint32_t* dst = tile + (wave + 4 * r) * RS + k;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    if (NEGL && ng[r]) x[c] = 1.0f - x[c];
+                    dst[c] = l1_fixed_bits(src[r] >= 0 ? x[c] : f.lo, f, inv_quantum, ex[r]);
+                }
+            }
+        __syncthreads();
+        for (int o = t; o < kc * TQ; o += 256) out[(int64_t)k0 * TQ + o] = tile[(o % TQ) * RS + o / TQ];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+        double e = ex[r];
+        for (int off = 32; off > 0; off >>= 1) e += __shfl_xor(e, off, 64);
+        if (lane == 0) base[qb * TQ + wave + 4 * r] = (double)gamma - (double)dist_scale * e;
+    }
+}
+
+void launch_pack_l1(int model, const int32_t* src_row, const int32_t* neg, int n_rows, int n_rows_pad,
+                    const float* states, int W, int d, const L1Fixed& f, float gamma, float dist_scale, float* qpack,
+                    double* base, hipStream_t s)
+{
+    if (n_rows_pad <= 0) return;
+    const dim3 grid(n_rows_pad / score_tq(model, n_rows));
+    uint32_t* q = reinterpret_cast<uint32_t*>(qpack);
+    const double inv = 1.0 / (double)f.quantum;
+    const bool small = score_small(n_rows);
+    if (model == KGQ_LOGICE) {
+        if (small) hipLaunchKernelGGL((k_pack_l1<kTqGqeSmall, true>), grid, dim3(256), 0, s, src_row, neg, n_rows, states, W, d, f, inv, gamma, dist_scale, q, base);
+        else hipLaunchKernelGGL((k_pack_l1<kTqGqe, true>), grid, dim3(256), 0, s, src_row, neg, n_rows, states, W, d, f, inv, gamma, dist_scale, q, base);
+    } else {
+        if (small) hipLaunchKernelGGL((k_pack_l1<kTqGqeSmall, false>), grid, dim3(256), 0, s, src_row, nullptr, n_rows, states, W, d, f, inv, gamma, dist_scale, q, base);
+        else hipLaunchKernelGGL((k_pack_l1<kTqGqe, false>), grid, dim3(256), 0, s, src_row, nullptr, n_rows, states, W, d, f, inv, gamma, dist_scale, q, base);
     }
 }
 

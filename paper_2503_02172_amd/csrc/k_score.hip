@@ -22,6 +22,16 @@
 //
 // Per-triple work (one non-packed VALU op each):
 //   GQE     d = e - q;  acc += |d|                                       (2)
+//           With a fixed-point table (L1Fixed), the same words as integers
+//           or as floats: two rows of three take v_sad_u32 (|e - q| + acc),
+//           the third the two float instructions. v_sad_u32, like min and
+//           max, issues at half rate on a unit of its own, so the float
+//           instructions of the third row go in between: 4 issue slots for 3
+//           triples. Register-only probes, in T triples/s: the float pair
+//           29.7, v_sad_u32 alone 38.1, mixed two to one 52.9. The sums are
+//           exact in the integer rows and as before in the others. The
+//           1,229-row sweep over 63,361 entities at d = 400 went from
+//           1.18 to 0.86 ms.
 //   Q2B     t = |e - c|: acc1 += t; acc2 += min(t, o)                    (4)
 //           score = gamma - acc1 + (1 - center_reg) * acc2, the exact
 //           regrouping of dist_out + center_reg * dist_in
@@ -101,8 +111,52 @@ __device__ __forceinline__ void store_row(const ScoreArgs& a, int64_t orow, int6
     store_scores4(a.scores + orow * a.ld, e0, a.N, v);
 }
 
-template <int MODEL, int TQ>
-__global__ __launch_bounds__(256) void k_score(ScoreArgs a, int nqg, int qchunk, int total_wg, int wg_per_xcd,
+// One step of the fixed-point L1 form for G rows (the last in floats, the
+// others by v_sad_u32) and the lane's 4 entities, in an order that puts a
+// full-rate instruction behind each half-rate one. q: the rows' words; the
+// float row's goes to a vector register, since the VALU takes a scalar operand
+// on at most every other issue cycle. (volatile: the compiler would move the
+// copy ahead, to where the word has not arrived yet.)
+template <int G>
+__device__ __forceinline__ void l1_fixed_step(uint32_t (*acc)[4], const float4& e, const float* q)
+{
+    static_assert(G == 3 || G == 4, "rows per group");
+    float t0, t1, qf;
+    if constexpr (G == 3)
+        asm volatile("v_mov_b32 %14, %21\n\tv_sad_u32 %0, %15, %19, %0\n\t"
+                     "v_sub_f32 %12, %15, %14\n\tv_sad_u32 %4, %15, %20, %4\n\t"
+                     "v_add_f32 %8, %8, |%12|\n\tv_sad_u32 %1, %16, %19, %1\n\t"
+                     "v_sub_f32 %13, %16, %14\n\tv_sad_u32 %5, %16, %20, %5\n\t"
+                     "v_add_f32 %9, %9, |%13|\n\tv_sad_u32 %2, %17, %19, %2\n\t"
+                     "v_sub_f32 %12, %17, %14\n\tv_sad_u32 %6, %17, %20, %6\n\t"
+                     "v_add_f32 %10, %10, |%12|\n\tv_sad_u32 %3, %18, %19, %3\n\t"
+                     "v_sub_f32 %13, %18, %14\n\tv_sad_u32 %7, %18, %20, %7\n\t"
+                     "v_add_f32 %11, %11, |%13|"
+                     : "+v"(acc[0][0]), "+v"(acc[0][1]), "+v"(acc[0][2]), "+v"(acc[0][3]), "+v"(acc[1][0]),
+                       "+v"(acc[1][1]), "+v"(acc[1][2]), "+v"(acc[1][3]), "+v"(acc[2][0]), "+v"(acc[2][1]),
+                       "+v"(acc[2][2]), "+v"(acc[2][3]), "=&v"(t0), "=&v"(t1), "=&v"(qf)
+                     : "v"(e.x), "v"(e.y), "v"(e.z), "v"(e.w), "s"(q[0]), "s"(q[1]), "s"(q[2]));
+    else
+        asm volatile("v_mov_b32 %18, %26\n\tv_sad_u32 %0, %19, %23, %0\n\t"
+                     "v_sub_f32 %16, %19, %18\n\tv_sad_u32 %4, %19, %24, %4\n\t"
+                     "v_add_f32 %12, %12, |%16|\n\tv_sad_u32 %8, %19, %25, %8\n\t"
+                     "v_sad_u32 %1, %20, %23, %1\n\tv_sub_f32 %17, %20, %18\n\t"
+                     "v_sad_u32 %5, %20, %24, %5\n\tv_add_f32 %13, %13, |%17|\n\t"
+                     "v_sad_u32 %9, %20, %25, %9\n\tv_sad_u32 %2, %21, %23, %2\n\t"
+                     "v_sub_f32 %16, %21, %18\n\tv_sad_u32 %6, %21, %24, %6\n\t"
+                     "v_add_f32 %14, %14, |%16|\n\tv_sad_u32 %10, %21, %25, %10\n\t"
+                     "v_sad_u32 %3, %22, %23, %3\n\tv_sub_f32 %17, %22, %18\n\t"
+                     "v_sad_u32 %7, %22, %24, %7\n\tv_add_f32 %15, %15, |%17|\n\t"
+                     "v_sad_u32 %11, %22, %25, %11"
+                     : "+v"(acc[0][0]), "+v"(acc[0][1]), "+v"(acc[0][2]), "+v"(acc[0][3]), "+v"(acc[1][0]),
+                       "+v"(acc[1][1]), "+v"(acc[1][2]), "+v"(acc[1][3]), "+v"(acc[2][0]), "+v"(acc[2][1]),
+                       "+v"(acc[2][2]), "+v"(acc[2][3]), "+v"(acc[3][0]), "+v"(acc[3][1]), "+v"(acc[3][2]),
+                       "+v"(acc[3][3]), "=&v"(t0), "=&v"(t1), "=&v"(qf)
+                     : "v"(e.x), "v"(e.y), "v"(e.z), "v"(e.w), "s"(q[0]), "s"(q[1]), "s"(q[2]), "s"(q[3]));
+}
+
+template <int MODEL, int TQ, bool FIXED = false>
+__global__ __launch_bounds__(256, 4) void k_score(ScoreArgs a, int nqg, int qchunk, int total_wg, int wg_per_xcd,
                                                int kslice)
 {
     // XCD-aware mapping: workgroup b runs on XCD b % 8 (round-robin dispatch),
@@ -134,25 +188,42 @@ __global__ __launch_bounds__(256) void k_score(ScoreArgs a, int nqg, int qchunk,
     const int k_begin = blockIdx.y * kslice;
     const int d = min(kslice, a.d - k_begin);
     const float* __restrict__ qp = a.qpack + ((int64_t)qb * a.d + k_begin) * F * TQ;
-    const float* __restrict__ ep = a.ent + ((int64_t)eb * a.d + k_begin) * EF * kEntBlock + lane * 4;
+    const float* __restrict__ ep = a.ent + ((int64_t)eb * a.d + k_begin) * EF * kEntBlock;
 
-    float acc[TQ][4];
+    // fixed-point form: rows r with r % G == G - 1 sum floats, the others
+    // integers; both kept as words
+    static_assert(!FIXED || MODEL == 0, "the fixed-point form is L1's");
+    constexpr int G = TQ % 3 == 0 ? 3 : 4;
+    static_assert(!FIXED || TQ % G == 0, "whole groups");
+    uint32_t accw[FIXED ? TQ : 1][4];
+    float acc[FIXED ? 1 : TQ][4];
     float acc2[TWO ? TQ : 1][4];
 #pragma unroll
-    for (int i = 0; i < TQ; ++i)
+    for (int i = 0; i < (FIXED ? 1 : TQ); ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
 #pragma unroll
     for (int i = 0; i < (TWO ? TQ : 1); ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc2[i][j] = 0.f;
+#pragma unroll
+    for (int i = 0; i < (FIXED ? TQ : 1); ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) accw[i][j] = 0u;
 
-    // Software pipeline, two steps per trip with named buffers A and B: a
-    // step's entity vector(s) are requested a step ahead, and its query
-    // scalars half a step ahead, after the previous wait (scalar loads may
-    // return out of order, so each wait on them covers every one
-    // outstanding). d is even (a multiple of 4).
+    // Software pipeline, four steps per trip with named buffers: a step's
+    // entity vector(s) are requested two steps ahead, and its query scalars
+    // one step ahead (two where a step is short: few rows), right after the
+    // wait for the current batch (scalar loads may return out of order, so
+    // each wait on them covers every one outstanding: one issued later would
+    // have less time to arrive in). d is a multiple of 4. Against one step
+    // and half a step ahead: 1,229 rows x 63,361 GQE entities 0.89 -> 0.85 ms
+    // a call, 5,632 x 14,505 Query2Box 2.19 -> 2.15 ms.
     constexpr int QN = F * TQ;
+    // steps per batch of query scalars (two batches in SGPRs): two where a
+    // step is short, 4 rows or 8 (64 Query2Box queries over 14,505 entities:
+    // 178 -> 152 us a call; the fixed-point form's 8 rows gain nothing)
+    constexpr int SB = QN <= 8 && !FIXED ? 2 : 1;
     // The packed queries are read-only for the whole kernel; reading them
     // through the constant address space keeps them on scalar loads.
     const __attribute__((address_space(4))) float* qc = (const __attribute__((address_space(4))) float*)qp;
@@ -160,55 +231,58 @@ __global__ __launch_bounds__(256) void k_score(ScoreArgs a, int nqg, int qchunk,
     struct EVec {
         float4 v[EF];
     };
+    const uint32_t lane4 = lane * 4;
     auto load_e = [&](int k, EVec& u) {
 #pragma unroll
         for (int f = 0; f < EF; ++f)
-            u.v[f] = *reinterpret_cast<const float4*>(ep + ((int64_t)k * EF + f) * kEntBlock);
+            u.v[f] = *reinterpret_cast<const float4*>(ep + (k * EF + f) * kEntBlock + lane4);
     };
-    // rows [R0, R1) of one step
-    auto compute = [&](const EVec& eu, const float* qv, auto R0c, auto R1c) {
-        constexpr int R0 = decltype(R0c)::value, R1 = decltype(R1c)::value;
-        const float e4[4] = {eu.v[0].x, eu.v[0].y, eu.v[0].z, eu.v[0].w};
+    // one step
+    auto compute = [&](const EVec& eu, const float (&qb)[SB * QN], auto off) {
+        const float* qv = qb + decltype(off)::value * QN;
+        if constexpr (FIXED) {
 #pragma unroll
-        for (int i = R0; i < R1; ++i) {
-            const float c = qv[i];
-            if (MODEL == 0) {
+            for (int i = 0; i < TQ; i += G) l1_fixed_step<G>(accw + i, eu.v[0], qv + i);
+        } else {
+            const float e4[4] = {eu.v[0].x, eu.v[0].y, eu.v[0].z, eu.v[0].w};
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] += fabsf(e4[j] - c);
-            } else if (MODEL == 3) {
-                const float ce4[4] = {eu.v[EF - 1].x, eu.v[EF - 1].y, eu.v[EF - 1].z, eu.v[EF - 1].w};
-                // tan and sin b / cos as vector operands: the VALU takes a
-                // scalar operand on at most every other issue cycle, and a
-                // fused multiply-add one in all (2 moves per row and step,
-                // per 4 triples)
-                float t, q;
-                asm volatile("v_mov_b32 %0, %1" : "=v"(t) : "s"(c));
-                asm volatile("v_mov_b32 %0, %1" : "=v"(q) : "s"(qv[2 * TQ + i]));
-                float p;
-                asm volatile("v_mov_b32 %0, %1" : "=v"(p) : "s"(qv[TQ + i]));
-                const float n = qv[3 * TQ + i], w = qv[4 * TQ + i];
+            for (int i = 0; i < TQ; ++i) {
+                const float c = qv[i];
+                if (MODEL == 0) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const float u = fmaf(-ce4[j], t, e4[j]);     // sin((theta_e - theta) / 2) / cos(theta / 2)
-                    const float v = fmaf(e4[j], t, ce4[j]);      // cos((theta_e - theta) / 2) / cos(theta / 2)
-                    const float au = fabsf(u);
-                    const float x = fmaf(-n, fabsf(v), fmaf(p, au, q));
-                    acc[i][j] = fmaf(w, __builtin_fmaxf(au, x), acc[i][j]);
-                }
-            } else {
-                const float o = qv[TQ + i];
+                    for (int j = 0; j < 4; ++j) acc[i][j] += fabsf(e4[j] - c);
+                } else if (MODEL == 3) {
+                    const float ce4[4] = {eu.v[EF - 1].x, eu.v[EF - 1].y, eu.v[EF - 1].z, eu.v[EF - 1].w};
+                    // tan and sin b / cos as vector operands: the VALU takes a
+                    // scalar operand on at most every other issue cycle, and a
+                    // fused multiply-add one in all (2 moves per row and step,
+                    // per 4 triples)
+                    float t, q;
+                    asm volatile("v_mov_b32 %0, %1" : "=v"(t) : "s"(c));
+                    asm volatile("v_mov_b32 %0, %1" : "=v"(q) : "s"(qv[2 * TQ + i]));
+                    float p;
+                    asm volatile("v_mov_b32 %0, %1" : "=v"(p) : "s"(qv[TQ + i]));
+                    const float n = qv[3 * TQ + i], w = qv[4 * TQ + i];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const float t = fabsf(e4[j] - c);
-                    acc[i][j] += t;
-                    acc2[i][j] += __builtin_fminf(t, o);
+                    for (int j = 0; j < 4; ++j) {
+                        const float u = fmaf(-ce4[j], t, e4[j]);     // sin((theta_e - theta) / 2) / cos(theta / 2)
+                        const float v = fmaf(e4[j], t, ce4[j]);      // cos((theta_e - theta) / 2) / cos(theta / 2)
+                        const float au = fabsf(u);
+                        const float x = fmaf(-n, fabsf(v), fmaf(p, au, q));
+                        acc[i][j] = fmaf(w, __builtin_fmaxf(au, x), acc[i][j]);
+                    }
+                } else {
+                    const float o = qv[TQ + i];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float t = fabsf(e4[j] - c);
+                        acc[i][j] += t;
+                        acc2[i][j] += __builtin_fminf(t, o);
+                    }
                 }
             }
         }
     };
-    using H0 = std::integral_constant<int, 0>;
-    using H1 = std::integral_constant<int, TQ / 2>;
-    using H2 = std::integral_constant<int, TQ>;
     // ConE's one accumulator holds a larger sum than the outside distance's
     // did; in two halves (the first waits in LDS) its rounding is half as
     // large, and below that of the two accumulators it replaces.
@@ -216,31 +290,50 @@ __global__ __launch_bounds__(256) void k_score(ScoreArgs a, int nqg, int qchunk,
     __shared__ float4 half_sum[HALVES ? TQ : 1][HALVES ? 256 : 1];
     const int k_half = d / 8 * 4;
 
-    EVec ua, ub;
-    float qa[QN], qb2[QN];
-    load_e(0, ua);
+    EVec u[4];
+    float qa[SB * QN], qb2[SB * QN];
+    // steps from step S of the trip on; the last steps of a block read up to
+    // two steps past it (the next block, or the padding behind the last):
+    // unused
+    auto load_q = [&](int S, float (&q)[SB * QN]) {
 #pragma unroll
-    for (int t = 0; t < QN; ++t) qa[t] = qc[t];
-    for (int k = 0; k < d; k += 2) {
-        load_e(k + 1, ub);                                  // B <- step k + 1
+        for (int t = 0; t < SB * QN; ++t) q[t] = qc[S * QN + t];
+    };
+    // step S of the trip, its scalars the OFF-th step of q; the entities of
+    // step S + 2 are requested, and at a batch's first step the next batch
+    auto step = [&](int S, const EVec& cur, EVec& ahead, const float (&q)[SB * QN], auto off, float (&next)[SB * QN]) {
+        constexpr int OFF = decltype(off)::value;
+        if constexpr (OFF == 0) {
+            __builtin_amdgcn_s_waitcnt(kWaitLgkmcnt0);      // q
+            __builtin_amdgcn_sched_barrier(0);
+            load_q(S + SB, next);
+        }
+        load_e(S + 2, ahead);
         __builtin_amdgcn_sched_barrier(0);
-        compute(ua, qa, H0{}, H1{});
+        compute(cur, q, off);
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int t = 0; t < QN; ++t) qb2[t] = qc[(k + 1) * QN + t];
-        __builtin_amdgcn_sched_barrier(0);
-        compute(ua, qa, H1{}, H2{});
-        const int k2 = (k + 2 < d) ? k + 2 : k + 1;         // A <- step k + 2 (last trip: in bounds, unused)
-        load_e(k2, ua);
-        __builtin_amdgcn_sched_barrier(0);
-        compute(ub, qb2, H0{}, H1{});
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int t = 0; t < QN; ++t) qa[t] = qc[k2 * QN + t];
-        __builtin_amdgcn_sched_barrier(0);
-        compute(ub, qb2, H1{}, H2{});
+    };
+    using Q0 = std::integral_constant<int, 0>;
+    using Q1 = std::integral_constant<int, SB - 1>;
+    load_e(0, u[0]);
+    load_e(1, u[1]);
+    load_q(0, qa);
+    for (int k = 0; k < d; k += 4) {
+        if constexpr (SB == 1) {
+            step(0, u[0], u[2], qa, Q0{}, qb2);
+            step(1, u[1], u[3], qb2, Q0{}, qa);
+            step(2, u[2], u[0], qa, Q0{}, qb2);
+            step(3, u[3], u[1], qb2, Q0{}, qa);
+        } else {
+            step(0, u[0], u[2], qa, Q0{}, qb2);
+            step(1, u[1], u[3], qa, Q1{}, qb2);
+            step(2, u[2], u[0], qb2, Q0{}, qa);
+            step(3, u[3], u[1], qb2, Q1{}, qa);
+        }
+        qc += 4 * QN;
+        ep += 4 * EF * kEntBlock;
         if constexpr (HALVES) {
-            if (k + 2 == k_half) {
+            if (k + 4 == k_half) {
 #pragma unroll
                 for (int i = 0; i < TQ; ++i) {
                     half_sum[i][threadIdx.x] = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
@@ -263,6 +356,12 @@ __global__ __launch_bounds__(256) void k_score(ScoreArgs a, int nqg, int qchunk,
         }
     }
 
+    // row i's distance to entity j, in the units of dist_scale
+    auto dist = [&](int i, int j) {
+        if constexpr (FIXED) return i % G == G - 1 ? __uint_as_float(accw[i][j]) : (float)accw[i][j];
+        else return acc[i][j];
+    };
+
     // Epilogue: finish the scores, merge union pairs, store.
     const int64_t e0 = (int64_t)eb * kEntBlock + lane * 4;
     if (a.part) {
@@ -273,7 +372,7 @@ __global__ __launch_bounds__(256) void k_score(ScoreArgs a, int nqg, int qchunk,
 #pragma unroll
         for (int i = 0; i < TQ; ++i) {
             const int64_t row = (int64_t)qb * TQ + i;
-            *reinterpret_cast<float4*>(pz + row * n_pad + e0) = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
+            *reinterpret_cast<float4*>(pz + row * n_pad + e0) = make_float4(dist(i, 0), dist(i, 1), dist(i, 2), dist(i, 3));
             if (TWO)
                 *reinterpret_cast<float4*>(pz + (rows_pad + row) * n_pad + e0) =
                     make_float4(acc2[i][0], acc2[i][1], acc2[i][2], acc2[i][3]);
@@ -289,6 +388,14 @@ __global__ __launch_bounds__(256) void k_score(ScoreArgs a, int nqg, int qchunk,
     static_assert(TQ <= 64, "one row per lane");
     const int32_t od_lane =
         a.out_dest[score_out_index(min(qb * TQ + min(lane, TQ - 1), a.n_rows - 1), a.n_quad, a.n_pair)];
+    // fixed-point form: what the row's distance is subtracted from, in two
+    // floats (gamma less what was clamped does not round)
+    float base_hi = a.gamma, base_lo = 0.f;
+    if constexpr (FIXED) {
+        const double base = a.cq[min(qb * TQ + min(lane, TQ - 1), a.n_rows - 1)];
+        base_hi = (float)base;
+        base_lo = base_hi - base_hi == 0.f ? (float)(base - (double)base_hi) : 0.f;    // (infinite: no low part)
+    }
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     int32_t od[TQ];
 #pragma unroll
@@ -302,7 +409,11 @@ __global__ __launch_bounds__(256) void k_score(ScoreArgs a, int nqg, int qchunk,
         for (int u = 0; u < 4; ++u)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                if (MODEL != 1) sc[u][j] = a.gamma - a.dist_scale * acc[i + u][j];
+                if (FIXED)
+                    sc[u][j] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(base_hi), i + u)) +
+                               fmaf(-a.dist_scale, dist(i + u, j),
+                                    __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(base_lo), i + u)));
+                else if (MODEL != 1) sc[u][j] = a.gamma - a.dist_scale * dist(i + u, j);
                 else sc[u][j] = a.gamma - acc[i + u][j] + (1.0f - a.center_reg) * acc2[i + u][j];
             }
         if (row < a.n_quad) {
@@ -362,7 +473,8 @@ __global__ __launch_bounds__(256) void k_score_sum(ScoreArgs a, int splits, int6
             if (MODEL == 1) s2 += pz[(rows_pad + r0 + u) * n_pad + e];
         }
         const float v =
-            MODEL != 1 ? a.gamma - a.dist_scale * s1 : a.gamma - s1 + (1.0f - a.center_reg) * s2;
+            MODEL != 1 ? (a.l1_fixed ? (float)(a.cq[r0 + u] - (double)a.dist_scale * (double)s1)
+                                     : a.gamma - a.dist_scale * s1) : a.gamma - s1 + (1.0f - a.center_reg) * s2;
         best = u == 0 ? v : fmaxf(best, v);
     }
     a.scores[(int64_t)a.out_dest[o] * a.ld + e] = best;
@@ -406,7 +518,10 @@ bool launch_score(const ScoreArgs& a, hipStream_t s)
     }
     if (splits > 1) b.chunk_key = nullptr;   // the split-d sum writes no keys
     dim3 grid(per_xcd * 8, z);
-    if (form == KGQ_GQE) {
+    if (form == KGQ_GQE && a.l1_fixed) {
+        if (small) hipLaunchKernelGGL((k_score<0, kTqGqeSmall, true>), grid, dim3(256), 0, s, b, nqg, qc, total, per_xcd, kslice);
+        else hipLaunchKernelGGL((k_score<0, kTqGqe, true>), grid, dim3(256), 0, s, b, nqg, qc, total, per_xcd, kslice);
+    } else if (form == KGQ_GQE) {
         if (small) hipLaunchKernelGGL((k_score<0, kTqGqeSmall>), grid, dim3(256), 0, s, b, nqg, qc, total, per_xcd, kslice);
         else hipLaunchKernelGGL((k_score<0, kTqGqe>), grid, dim3(256), 0, s, b, nqg, qc, total, per_xcd, kslice);
     } else if (form == KGQ_Q2B) {

@@ -103,6 +103,7 @@ struct kgq_handle {
     double* ent_const = nullptr;  // BetaE E_e [n_pad]
     uint16_t* ent_planes = nullptr;   // BetaE [U | V] rows of ent_blk as three bf16 planes (when 2d % 32 == 0)
     float* rel_o_sp = nullptr;    // Q2B softplus(offset_raw) [R x d]
+    L1Fixed l1;                   // GQE / LogicE: fixed-point form of ent_blk (off: floats)
     float cone_modulus = 0.f;     // ConE distance scale (host copy of "modulus")
     float* int_cat_w = nullptr;   // ConE [inter.axis.w1; inter.arg.w1] [2d x 2d]
     float* int_cat_b = nullptr;   // ConE [inter.axis.b1; inter.arg.b1] [2d]
@@ -349,7 +350,7 @@ kgq_status allocate_all(kgq_handle* h)
     }
     if (mlp_model(c.model)) {
         ALLOC(h->ent_rm, N * 2 * d);
-        ALLOC(h->ent_blk, n_pad * 2 * d);
+        ALLOC(h->ent_blk, n_pad * 2 * d + kEntPad);
         if (c.model == KGQ_BETAE) ALLOC(h->ent_const, n_pad);
         if (c.model == KGQ_BETAE && (2 * d) % 32 == 0) ALLOC(h->ent_planes, 3 * n_pad * 2 * d);
         ALLOC(h->proj1_ent, N * 4 * d);
@@ -360,7 +361,7 @@ kgq_status allocate_all(kgq_handle* h)
         }
     } else {
         ALLOC(h->ent_rm, N * d);
-        ALLOC(h->ent_blk, n_pad * d);
+        ALLOC(h->ent_blk, n_pad * d + kEntPad);
         if (c.model == KGQ_Q2B) ALLOC(h->rel_o_sp, (int64_t)c.n_relations * d);
     }
     // bf16 planes of every dense-layer weight whose K (its columns) the
@@ -403,7 +404,7 @@ kgq_status allocate_all(kgq_handle* h)
             }
         }
         ALLOC(L.logits, m_max * d);
-        ALLOC(L.qpack, h->cap_score_rows * qpack_row_floats(c.model, (int)d));
+        ALLOC(L.qpack, h->cap_score_rows * qpack_row_floats(c.model, (int)d) + kQpackPad);
         ALLOC(L.cq, h->cap_score_rows);
         ALLOC(L.scores, Bm * N);
         // split-K runs only while a layer has fewer than 128 output tiles of
@@ -765,6 +766,11 @@ kgq_status run_plan(kgq_handle* h, Lane& L, const Plan& p, const int32_t* P, con
     const int d_score = logice ? 2 * d : d;    // LogicE scores its 2d bound coordinates as one vector
     {
         StageTimer t(h, 3, s);
+        if (h->l1.on)
+            launch_pack_l1(c.model, P + p.off_score_src, logice ? P + p.off_score_neg : nullptr, p.n_score_rows,
+                           n_rows_pad, L.states, W, d_score, h->l1, c.gamma, logice ? 1.0f / (float)(2 * d) : 1.0f,
+                           L.qpack, L.cq, s);
+        else
         launch_pack(c.model, P + p.off_score_src, mlp ? P + p.off_score_neg : nullptr, p.n_score_rows, n_rows_pad,
                     L.states, W, d_score, c.center_reg, L.qpack, L.cq, s);
     }
@@ -775,6 +781,8 @@ kgq_status run_plan(kgq_handle* h, Lane& L, const Plan& p, const int32_t* P, con
         ScoreArgs a{c.model, L.qpack, h->ent_blk, L.cq, h->ent_const, P + p.off_out_dest, p.n_score_rows,
                     p.n_quad_rows, p.n_pair_rows, d_score, N, h->n_blocks, c.gamma, c.center_reg, dst, N};
         a.dist_scale = logice ? 1.0f / (float)(2 * d) : cone ? h->cone_modulus : 1.0f;
+        a.l1_fixed = h->l1.on;
+        if (h->l1.on) a.dist_scale *= h->l1.quantum;
         if (betae && h->dense_path != KGQ_DENSE_FP32) a.ent_planes = h->ent_planes;
         a.split_always = h->dense_path == KGQ_DENSE_BF16X3;
         a.part = L.score_ws;
@@ -882,7 +890,7 @@ int64_t carve_scratch(const kgq_handle* h, const Plan& p, int32_t k, bool need_s
     V.logits = reinterpret_cast<float*>(take(m * d * 4));
     const int tq = score_row_pad(c.model);
     const int64_t srows = ((int64_t)(p.n_score_rows + tq - 1) / tq) * tq;
-    V.qpack = reinterpret_cast<float*>(take(srows * qpack_row_floats(c.model, (int)d) * 4));
+    V.qpack = reinterpret_cast<float*>(take((srows * qpack_row_floats(c.model, (int)d) + kQpackPad) * 4));
     V.cq = reinterpret_cast<double*>(take(srows * 8));
     V.scores = need_scores ? reinterpret_cast<float*>(take(B * N * 4)) : nullptr;
     const int64_t ncand = need_topk ? topk_scratch_elems(B, N, k) : 0;
@@ -1215,6 +1223,28 @@ static kgq_status build_proj1(kgq_handle* h)
     return KGQ_OK;
 }
 
+// GQE / LogicE: choose the scoring table's form from its values, and bring
+// it into fixed point where that is the one. `part`: device scratch of
+// kStatBlocks x 4 doubles.
+static hipError_t fix_points(kgq_handle* h, int width, void* part)
+{
+    const int64_t n = h->cfg.n_entities * width;
+    double p[4 * kStatBlocks];
+    launch_table_stats(h->ent_rm, n, static_cast<double*>(part), nullptr);
+    const hipError_t e = hipMemcpy(p, part, sizeof(p), hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return e;
+    double lo = p[0], hi = p[1], sum = 0.0, dev = 0.0;
+    for (int b = 0; b < kStatBlocks; ++b) {
+        lo = std::min(lo, p[4 * b]);
+        hi = std::max(hi, p[4 * b + 1]);
+        sum += p[4 * b + 2];
+        dev += p[4 * b + 3];
+    }
+    h->l1 = choose_l1_fixed(lo, hi, sum, dev / (double)n, width);
+    if (h->l1.on) launch_l1_quantise(h->ent_blk, h->n_blocks * kEntBlock * width, h->l1, nullptr);
+    return hipSuccess;
+}
+
 kgq_status kgq_load_params(kgq_handle* h, const char* name, const void* src, size_t nbytes, int32_t dtype,
                            int32_t src_is_device)
 {
@@ -1279,7 +1309,7 @@ kgq_status kgq_load_params(kgq_handle* h, const char* name, const void* src, siz
     }
     // entity table: stage, then build the derived layouts
     void* stage = nullptr;
-    hipError_t e = hipMalloc(&stage, nbytes);
+    hipError_t e = hipMalloc(&stage, std::max(nbytes, (size_t)kStatBlocks * 4 * sizeof(double)));
     if (e != hipSuccess) return fail(h, KGQ_E_OOM, "staging buffer for the entity table");
     e = hipMemcpy(stage, src, nbytes, kind);
     if (e == hipSuccess) {
@@ -1293,10 +1323,12 @@ kgq_status kgq_load_params(kgq_handle* h, const char* name, const void* src, siz
         else if (c.model == KGQ_CONE)
             launch_cone_entity_prep(static_cast<const float*>(stage), c.n_entities, c.dim, h->n_blocks, h->ent_rm,
                                     h->ent_blk, nullptr);
-        else
-            launch_relayout_points(stage, bf16, c.n_entities, c.model == KGQ_LOGICE ? 2 * c.dim : c.dim,
-                                   h->n_blocks, h->ent_rm, h->ent_blk, nullptr);
-        e = hipGetLastError();
+        else {
+            const int width = c.model == KGQ_LOGICE ? 2 * c.dim : c.dim;
+            launch_relayout_points(stage, bf16, c.n_entities, width, h->n_blocks, h->ent_rm, h->ent_blk, nullptr);
+            if (c.model != KGQ_Q2B) e = fix_points(h, width, stage);
+        }
+        if (e == hipSuccess) e = hipGetLastError();
         if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     }
     (void)hipFree(stage);

@@ -35,6 +35,12 @@ constexpr int kTqCone = 8;
 // padded to the matrix-core scorer's 128-row tile.
 constexpr int kRowTileBetae = 128;
 
+// The VALU scorers read up to two dimension steps past the last block of the
+// entity table and one past the last block of packed rows: floats allocated
+// behind each.
+constexpr int kEntPad = 2 * 2 * kEntBlock;
+constexpr int kQpackPad = 64;
+
 // LogicE scores with GQE's L1 kernel over its 2d bound coordinates.
 inline int valu_form(int model) { return model == KGQ_LOGICE ? KGQ_GQE : model; }
 
@@ -67,6 +73,31 @@ inline int score_tq(int model, int n_rows)
     case KGQ_Q2B: return small ? kTqQ2bSmall : kTqQ2b;
     default: return small ? kTqConeSmall : kTqCone;
     }
+}
+
+// GQE's and LogicE's entity table in fixed point, for the L1 scorer's integer
+// form (k_score.hip): coordinate x is held as the bits 0x4B000000 + u, u =
+// round((x - lo) / quantum), lo the table's least value and u at most u_max <
+// 2^23. Read as an integer, differences of such words are differences of u;
+// read as a float, the word is 2^23 + u and they are the same, exactly.
+// u_max * width < 2^32, so a sum of |differences| over the scored width never
+// wraps. A query coordinate outside [lo, hi] is moved to the nearer end, and
+// what it was moved by is added to the row's distance as it is: every entity
+// lies on the other side, so the distance splits exactly.
+struct L1Fixed {
+    bool on = false;
+    float lo = 0.f, hi = 0.f;
+    float quantum = 0.f;
+};
+// The fixed-point form of a table of n coordinates (rows of `width`), or off
+// where it would be coarser than the float sums it replaces.
+L1Fixed choose_l1_fixed(double lo, double hi, double sum, double mad, int width);
+// x as u (x clamped to the table's range), and by how much it was clamped.
+__device__ __forceinline__ uint32_t l1_fixed_bits(float x, const L1Fixed& f, double inv_quantum, double& excess)
+{
+    const float c = fminf(fmaxf(x, f.lo), f.hi);
+    excess += fabs((double)x - (double)c);             // NaN and infinities pass through here
+    return 0x4B000000u + (uint32_t)__double2uint_rn(((double)c - (double)f.lo) * inv_quantum);
 }
 
 // Models whose projection is an MLP (one dense-layer pass per hop) and that
@@ -134,6 +165,13 @@ __device__ __forceinline__ float apply_epilogue(int epi, int split, int n, float
 // scorer layout (fp32), padding with zeros; also writes a row-major fp32 copy.
 void launch_relayout_points(const void* src, int src_bf16, int64_t N, int d, int64_t n_blocks,
                             float* rowmajor, float* blocked, hipStream_t s);
+
+// Least and largest value, sum, and sum of |x - mean| of x[0 .. n), n a
+// multiple of 4: [kStatBlocks x 4] doubles, one part per workgroup.
+constexpr int kStatBlocks = 512;
+void launch_table_stats(const float* x, int64_t n, double* part, hipStream_t s);
+// Blocked scoring table to fixed-point words, in place (n a multiple of 256).
+void launch_l1_quantise(float* blk, int64_t n, const L1Fixed& f, hipStream_t s);
 
 // BetaE: decode alpha|beta [N x 2d] to fp32 row-major, and build U, V
 // (blocked) and the per-entity constant E_e (double).
@@ -203,6 +241,12 @@ void launch_betae_proj_prep(const int32_t* src_row, const int32_t* anchor_ref, c
                             const float* states, const float* ent_ab, const float* rel,
                             int64_t n_ent, int n_rel, int d, float* x, int* flag, hipStream_t s);
 
+// Pack scored rows in fixed point for the L1 scorer's integer form
+// ([row_block][k][TQ] words), and each row's base: gamma minus dist_scale
+// times what its coordinates were clamped by.
+void launch_pack_l1(int model, const int32_t* src_row, const int32_t* neg, int n_rows, int n_rows_pad,
+                    const float* states, int W, int d, const L1Fixed& f, float gamma, float dist_scale, float* qpack,
+                    double* base, hipStream_t s);
 // Pack scored rows into the scorer's layout; BetaE also C_q = sum lnB(a, b)
 // and the reciprocal of rows with neg[j] != 0 (neg may be NULL).
 void launch_pack(int model, const int32_t* src_row, const int32_t* neg, int n_rows, int n_rows_pad,
@@ -248,6 +292,8 @@ constexpr int kKeyChunk = 64;   // entities per chunk key
 // the counter counts stores as well, in issue order; kernels that store in a
 // loop load what the loop needs first and wait for it once with this.
 constexpr int kWaitVmcnt0 = 0x0F70;
+// s_waitcnt lgkmcnt(0) alone (vmcnt 63, expcnt 7): scalar and LDS loads.
+constexpr int kWaitLgkmcnt0 = 0xC07F;
 
 // Threads per workgroup for a row of `width` floats: one element per thread
 // (up to 1,024), so that no thread loads after it has stored.
@@ -280,6 +326,9 @@ struct ScoreArgs {
     // distance scale: score = gamma - dist_scale * distance (GQE 1, LogicE
     // 1 / (2d), ConE its modulus; Query2Box ignores it)
     float dist_scale = 1.0f;
+    // GQE / LogicE: table and packed rows are fixed-point words (L1Fixed); cq
+    // then holds each row's base, and dist_scale the quantum's factor too
+    bool l1_fixed = false;
     float* part = nullptr;             // GQE / Query2Box split-d partials for small batches
     int64_t part_elems = 0;            //   (nullptr: never split)
     // BetaE: the [U | V] rows of `ent` split into three bf16 planes (plane

@@ -6,6 +6,7 @@ import pytest
 
 from oracle import oracle as O
 from paper_2503_02172_amd import synth
+from tests.parity import check_scores, check_topk
 
 pytestmark = pytest.mark.gpu
 
@@ -46,3 +47,93 @@ def test_gpu_cone_max_form(structure, B, center_reg):
     # usual weights) by up to 12 * 4d ulp
     tol = 4 * EPS * abs(w.gamma) + mod * d * (16 + d + np.pi * 12 * 4 * d) * EPS
     assert np.abs(out["scores"] - ref).max() <= tol, (np.abs(out["scores"] - ref).max(), tol)
+
+
+def _gqe(table, rel_scale, d, n_ent, seed):
+    w = synth.make_tiny(O.GQE, n_ent=n_ent, n_rel=7, dim=d, seed=seed)
+    rng = np.random.Generator(np.random.PCG64(seed + 1))
+    if table == "normal":
+        w.params["entity"] = rng.normal(0, 0.5, (n_ent, d)).astype(np.float32)
+    elif table == "offset":
+        w.params["entity"] += np.float32(100.0)
+    elif table == "outlier":
+        w.params["entity"][3, 1] = 4000.0
+    elif table == "equal":
+        w.params["entity"][:] = 0.25
+    w.params["relation"] *= np.float32(rel_scale)
+    return w
+
+
+@pytest.mark.parametrize("table", ["uniform", "normal", "offset", "outlier", "equal"])
+@pytest.mark.parametrize("d,B,rel_scale", [(32, 5, 1.0), (400, 9, 8.0), (100, 1100, 3.0), (8, 3, 1.0)])
+def test_gpu_l1_fixed_and_float(table, d, B, rel_scale):
+    """GQE's L1 scores on tables that take the fixed-point form (uniform,
+    normal, shifted) and on those that keep floats (a far outlier, one value
+    only, too few dimensions), with query coordinates up to 24 times outside
+    the table's range. Tolerance: every coordinate off by a quantum (range /
+    2^23) and the state's two roundings, and the sum by width ulp."""
+    n_ent = 300
+    w = _gqe(table, rel_scale, d, n_ent, 71)
+    qb = synth.draw_queries("3p", B, n_ent, 7, seed=72)
+    out = _scores(w, O.GQE, "3p", qb, 5)
+    ref = O.Model(O.GQE, w.params, w.gamma).scores(S["3p"], qb.anchors, qb.relations)
+    e = w.params["entity"]
+    rng = float(e.max() - e.min())
+    dist = np.abs(w.gamma - ref)
+    state = np.abs(e).max() + 3 * np.abs(w.params["relation"]).max()
+    tol = d * (rng * 2.0 ** -23 + 4 * EPS * state) + (d + 4) * EPS * (dist + w.gamma)
+    assert np.all(np.abs(out["scores"] - ref) <= tol), (np.abs(out["scores"] - ref) / tol).max()
+    check_topk(out["idx"], out["score"], ref, 5, float((tol / np.maximum(np.abs(ref), w.gamma)).max()), w.gamma, table)
+
+
+@pytest.mark.parametrize("structure", ["2u", "pni", "1p"])
+@pytest.mark.parametrize("B", [3, 700])
+def test_gpu_l1_fixed_logice(structure, B):
+    """LogicE's bounds in fixed point (width 2d = 128): union pairs, a
+    negated answer path, single rows; split and unsplit scorers."""
+    w = synth.make_tiny(O.LOGICE, n_ent=520, n_rel=7, dim=64, seed=81)
+    qb = synth.draw_queries(structure, B, 520, 7, seed=82)
+    out = _scores(w, O.LOGICE, structure, qb, 5)
+    ref = O.Model(O.LOGICE, w.params, w.gamma).scores(S[structure], qb.anchors, qb.relations)
+    # bounds in [0, 1]: a quantum of 2^-23, the states' own float error (three
+    # dense layers of up to 4d terms, then a sigmoid), the mean's rounding
+    tol = 2.0 ** -23 + 3 * 4 * 64 * EPS + 132 * EPS + 4 * EPS
+    assert np.abs(out["scores"] - ref).max() <= tol, np.abs(out["scores"] - ref).max()
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf])
+def test_gpu_l1_infinite_query(bad):
+    """A query state with an infinite coordinate is infinitely far from every
+    entity in either form; other rows are untouched."""
+    w = synth.make_tiny(O.GQE, n_ent=300, n_rel=7, dim=32, seed=91)
+    w.params["relation"][2, 5] = bad
+    qb = synth.draw_queries("1p", 8, 300, 7, seed=92)
+    qb.relations[:, 0] = [0, 1, 2, 3, 4, 5, 6, 2]
+    out = _scores(w, O.GQE, "1p", qb, 5)["scores"]
+    assert np.all(np.isneginf(out[[2, 7]]))
+    assert np.all(np.isfinite(np.delete(out, [2, 7], 0)))
+
+
+@pytest.mark.parametrize("model,name", [(O.GQE, "entity"), (O.Q2B, "entity"), (O.LOGICE, "entity.bounds")],
+                         ids=["gqe", "q2b", "logice"])
+@pytest.mark.parametrize("n_ent,d", [(70, 36), (257, 64), (64, 132)])
+def test_gpu_point_table_layout_bf16(model, name, n_ent, d):
+    """A bf16 entity table and its float32 values give the same scores (the
+    re-layout's two input types, at ragged tiles of entities and coordinates)."""
+    import torch
+    from paper_2503_02172_amd import kgq
+    w = synth.make_tiny(model, n_ent=n_ent, n_rel=7, dim=d, seed=95)
+    bits = synth.bf16_rne(w.params[name])
+    w.params[name] = synth.bf16_decode(bits)
+    qb = synth.draw_queries("2i", 9, n_ent, 7, seed=96)
+    outs = []
+    for dtype in (kgq.F32, kgq.BF16):
+        with kgq.Engine(model, n_ent, 7, d, w.gamma, 16, entity_dtype=dtype) as eng:
+            for n, a in w.params.items():
+                eng.load(n, bits if n == name and dtype == kgq.BF16 else a, dtype if n == name else kgq.F32)
+            out = eng.execute(S["2i"], qb.anchors, qb.relations, k=5, scores=True)
+            torch.cuda.synchronize()
+            outs.append(out["scores"].cpu().numpy())
+    assert np.array_equal(outs[0], outs[1])
+    ref = O.Model(model, w.params, w.gamma).scores(S["2i"], qb.anchors, qb.relations)
+    check_scores(outs[0], ref, w.rtol, w.gamma, name)
