@@ -268,16 +268,15 @@ kgq_status kgq_set_checked(kgq_handle* h, int32_t on);
  *     others (K < 32, layers of at most 64 rows, and kgq_dense layers below
  *     the bounds) on the FP32 matrix cores. Inputs
  *     must be finite and below 3.39e38 in magnitude on the bf16 path.
- *     BetaE scores on the bf16 path when 2d is a multiple of 32 and the call
- *     scores more than 64 rows (more than 128 when 128-row tiles would give
- *     fewer than 256 workgroups); smaller calls score on the FP32 matrix
- *     cores.
+ *     BetaE scores on the f16 matrix cores, each FP32 operand row scaled by a
+ *     power of two and split into two f16 parts, three of the four part
+ *     products kept, when the call has more than 256 tiles of 64 scored rows
+ *     x 64 entities; smaller calls score on the FP32 matrix cores.
  *   KGQ_DENSE_FP32: every layer and the BetaE scorer on the FP32 matrix cores.
- *   KGQ_DENSE_BF16X3: every layer with K >= 32, and the BetaE scorer when
- *     2d is a multiple of 32, on the bf16 path, whatever the size (for
- *     tests).
- * The bf16 parts of the weights and of BetaE's entity-side scoring rows are
- * made when they are loaded, whatever the path. Takes effect for calls
+ *   KGQ_DENSE_BF16X3: every layer with K >= 32 on the bf16 path, and the
+ *     BetaE scorer on the f16 matrix cores, whatever the size (for tests).
+ * The parts of the weights and of BetaE's entity-side scoring rows are made
+ * when they are loaded, whatever the path. Takes effect for calls
  * enqueued after it. Errors: INVALID_ARG. */
 typedef enum { KGQ_DENSE_AUTO = 0, KGQ_DENSE_FP32 = 1, KGQ_DENSE_BF16X3 = 2 } kgq_dense_path;
 kgq_status kgq_set_dense_path(kgq_handle* h, int32_t path);

@@ -20,6 +20,7 @@
 #include <cmath>
 
 #include "kgq_internal.hpp"
+#include "mfma_tile.hpp"
 
 namespace kgq {
 
@@ -788,34 +789,69 @@ void launch_pack_l1(int model, const int32_t* src_row, const int32_t* neg, int n
 // double precision (rows are regulariser outputs or their reciprocals, so
 // positive; lnbeta_pos keeps the kernel at 45 VGPRs where the library lgamma
 // fallback took 176). A negated answer row (neg[j] != 0) is packed as the
-// reciprocals of its shape parameters. One workgroup per row; padding rows
-// are zero with C_q = 0.
-__global__ __launch_bounds__(256) void k_pack_rows(const int32_t* src_row, const int32_t* neg, int n_rows,
-                                                   const float* states, int d, float* qrows, double* cq)
+// reciprocals of its shape parameters. One workgroup per row. SPLIT: the row
+// in the split form of the f16 matrix-core tile, with its scale.
+template <bool SPLIT>
+__global__ __launch_bounds__(256) void k_pack_rows(const int32_t* src_row, const int32_t* neg, const float* states,
+                                                   int d, float* qrows, double* cq, float* q_scale)
 {
     __shared__ double part[4];
+    __shared__ float big[4];
     const int j = blockIdx.x;
     const int t = threadIdx.x;
-    const int src = j < n_rows ? src_row[j] : -1;
-    const bool inv = src >= 0 && neg && neg[j];
-    const float* st = states + (int64_t)(src >= 0 ? src : 0) * 2 * d;
-    float* dst = qrows + (int64_t)j * 2 * d;
-    for (int k = 4 * t; k < 2 * d; k += 4 * 256) {
-        float4 v = *reinterpret_cast<const float4*>(st + k);
-        if (inv) v = make_float4(1.0f / v.x, 1.0f / v.y, 1.0f / v.z, 1.0f / v.w);
-        *reinterpret_cast<float4*>(dst + k) = src >= 0 ? v : make_float4(0.f, 0.f, 0.f, 0.f);
+    const bool inv = neg && neg[j];
+    const float* st = states + (int64_t)src_row[j] * 2 * d;
+    if constexpr (SPLIT) {
+        // the row's largest magnitude, then chunks of 8 (32 bytes each)
+        const int n8 = (int)(plane_ld(2 * d) / 8);
+        float* dst = qrows + (int64_t)j * n8 * 8;
+        auto load8 = [&](int c, float (&x)[8]) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int k = 8 * c + 4 * h;
+                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (k < 2 * d) {
+                    v = *reinterpret_cast<const float4*>(st + k);
+                    if (inv) v = make_float4(1.0f / v.x, 1.0f / v.y, 1.0f / v.z, 1.0f / v.w);
+                }
+                x[4 * h] = v.x;
+                x[4 * h + 1] = v.y;
+                x[4 * h + 2] = v.z;
+                x[4 * h + 3] = v.w;
+            }
+        };
+        float x[8], m = 0.f;
+        for (int c = t; c < n8; c += 256) {
+            load8(c, x);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) m = fmaxf(m, fabsf(x[u]));
+        }
+        for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+        if ((t & 63) == 0) big[t >> 6] = m;
+        __syncthreads();
+        const float sc = split_scale(fmaxf(fmaxf(big[0], big[1]), fmaxf(big[2], big[3])));
+        for (int c = t; c < n8; c += 256) {
+            if (n8 > 256) load8(c, x);
+            store_split8(dst + 8 * c, x, split_inverse(sc));
+        }
+        if (t == 0) q_scale[j] = sc;
+    } else {
+        float* dst = qrows + (int64_t)j * 2 * d;
+        for (int k = 4 * t; k < 2 * d; k += 4 * 256) {
+            float4 v = *reinterpret_cast<const float4*>(st + k);
+            if (inv) v = make_float4(1.0f / v.x, 1.0f / v.y, 1.0f / v.z, 1.0f / v.w);
+            *reinterpret_cast<float4*>(dst + k) = v;
+        }
     }
     double lnb = 0.0;
-    if (src >= 0) {
-        for (int k = t; k < d; k += 256) {
-            float af = st[k], bf = st[d + k];
-            if (inv) {
-                af = 1.0f / af;
-                bf = 1.0f / bf;
-            }
-            const double a = af, b = bf;
-            lnb += lnbeta_pos(a, b);
+    for (int k = t; k < d; k += 256) {
+        float af = st[k], bf = st[d + k];
+        if (inv) {
+            af = 1.0f / af;
+            bf = 1.0f / bf;
         }
+        const double a = af, b = bf;
+        lnb += lnbeta_pos(a, b);
     }
     for (int off = 32; off > 0; off >>= 1) lnb += __shfl_xor(lnb, off, 64);
     if ((t & 63) == 0) part[t >> 6] = lnb;
@@ -824,12 +860,15 @@ __global__ __launch_bounds__(256) void k_pack_rows(const int32_t* src_row, const
 }
 
 void launch_pack(int model, const int32_t* src_row, const int32_t* neg, int n_rows, int n_rows_pad,
-                 const float* states, int W, int d, float center_reg, float* qpack, double* cq, hipStream_t s)
+                 const float* states, int W, int d, float center_reg, float* qpack, double* cq, float* q_scale,
+                 hipStream_t s)
 {
     if (n_rows_pad <= 0) return;
     if (model == KGQ_BETAE) {
-        hipLaunchKernelGGL(k_pack_rows, dim3(n_rows_pad), dim3(256), 0, s, src_row, neg, n_rows, states, d, qpack,
-                           cq);
+        if (q_scale)
+            hipLaunchKernelGGL(k_pack_rows<true>, dim3(n_rows), dim3(256), 0, s, src_row, neg, states, d, qpack, cq, q_scale);
+        else
+            hipLaunchKernelGGL(k_pack_rows<false>, dim3(n_rows), dim3(256), 0, s, src_row, neg, states, d, qpack, cq, nullptr);
         return;
     }
     if (model == KGQ_CONE) {

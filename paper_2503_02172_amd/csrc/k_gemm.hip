@@ -166,6 +166,35 @@ void launch_split_planes(const float* w, uint16_t* p, int64_t rows, int64_t cols
     hipLaunchKernelGGL(k_split_planes, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, w, p, cols, ld, n);
 }
 
+// One wavefront per row: its largest magnitude, then its chunks of 8.
+__global__ __launch_bounds__(256) void k_split_rows(const float* __restrict__ w, int64_t rows, int cols, int64_t ld,
+                                                    float* __restrict__ dst, float* __restrict__ scale)
+{
+    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (row >= rows) return;
+    const int lane = threadIdx.x & 63;
+    const float* src = w + row * ld;
+    float m = 0.f;
+    for (int k = lane; k < cols; k += 64) m = fmaxf(m, fabsf(src[k]));
+    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+    const float sc = split_scale(m), inv = split_inverse(sc);
+    const int n8 = (int)(plane_ld(cols) / 8);
+    float* out = dst + row * (int64_t)n8 * 8;
+    for (int c = lane; c < n8; c += 64) {
+        float x[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) x[t] = c * 8 + t < cols ? src[c * 8 + t] : 0.f;
+        store_split8(out + c * 8, x, inv);
+    }
+    if (lane == 0) scale[row] = sc;
+}
+
+void launch_split_rows(const float* w, int64_t rows, int64_t cols, int64_t ld, float* dst, float* scale, hipStream_t s)
+{
+    if (rows <= 0) return;
+    hipLaunchKernelGGL(k_split_rows, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, w, rows, (int)cols, ld, dst, scale);
+}
+
 template <int BM, int BN, bool PRIO>
 __device__ __forceinline__ void gemm_bf16x3_tile(const GemmArgs& g, int tm, int tn, int per_xcd, float* sm)
 {

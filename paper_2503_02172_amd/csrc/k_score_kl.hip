@@ -12,26 +12,23 @@
 // on the matrix cores; the VALU form is bound by the half-rate FMA issue of
 // the vector units.
 //
-// Tiling (mfma_tile.hpp). When 2d is a multiple of 32 and the [U | V] rows
-// have been split into three bf16 planes at load, the contraction runs on
-// v_mfma_f32_16x16x32_bf16 with the query rows split in registers and six
-// part products kept: FP32 accuracy at 0.375 of the FP32 matrix-core time per
-// k range (MfmaTileBf16x3 with 128-row x 128-entity tiles, 4 x 1
-// wavefronts and raised issue priority while fragments are read and split,
-// an 80 KiB LDS ring; 1.7x faster than the FP32 loop at the 63,361-entity
-// workload, and 6% faster than 128 x 64 tiles).
-// Otherwise 64-row x 64-entity tiles, 2 x 2 MFMA tiles of 16 x 16 per
-// wavefront, on v_mfma_f32_16x16x4_f32 with full FP32 inputs: through the
-// direct-to-LDS ring of three stages when 2d is a multiple of 16 (measured
-// faster, epilogue included, than 128 x 64, 64 x 128 or 128 x 128 tiles and
-// than two or four stages), else the register-staged loop with 128 x 128
-// tiles. The epilogue adds
-// C_q + E_e in double precision, stages the output tile in LDS, takes the
-// max over union groups of four and pairs of rows and writes each output
-// row with 16-byte non-temporal stores. On the 128-entity bf16 tiles it also
-// writes, per output row and chunk of 64 entities, the largest key of the
-// chunk's scores, from which top-k skips the chunks that cannot hold an
-// answer.
+// Tiling (mfma_tile.hpp). The contraction runs on v_mfma_f32_16x16x32_f16 with
+// both operands split ahead into two f16 parts and scaled by row (the entity
+// rows at load, the query rows by the pack kernel) and three part products
+// kept (MfmaTileF16x2, tiles of 128 entities x 128 query rows, 64 KiB of LDS,
+// two workgroups per compute unit): k_score_kl_split. All its terms are
+// positive, and its error against 64 bits is that of the 32-bit sum. At the
+// 63,361-entity workload it took the scorer from 1.21 ms (three bf16 parts,
+// six products, the query rows split in the loop) to 0.69 ms.
+// Small calls, and KGQ_DENSE_FP32: 64-row x 64-entity tiles on
+// v_mfma_f32_16x16x4_f32 with full FP32 inputs, through the direct-to-LDS
+// ring of three stages when 2d is a multiple of 16, else the register-staged
+// loop. Its epilogue adds C_q + E_e in double precision, stages the output
+// tile in LDS, takes the max over union groups of four and pairs of rows and
+// writes each output row with 16-byte non-temporal stores.
+// The split kernel also writes, per output row and chunk of 64 entities, the
+// largest key of the chunk's scores, from which top-k skips the chunks that
+// cannot hold an answer.
 // Workgroups are ordered in chunks of row tiles (about 2 MiB of query rows),
 // each swept against every entity tile: the chunk's rows stay in L2 while
 // the entity table streams past.
@@ -46,12 +43,19 @@ namespace kgq {
 // loop 128 x 128, or 64 x 64 for small batches, where the larger tile leaves
 // the chip underfilled and each workgroup's K loop is a latency chain. Query
 // rows are padded to 128 (kRowTileBetae), a multiple of every tile's rows.
+// x of the lane that the DPP control names (quad permutations).
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float x)
+{
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xF, 0xF, false));
+}
+
 template <class KlTile>
 __global__ __launch_bounds__(256, 2) void k_score_kl(ScoreArgs a, int n_mt, int n_nt, int qchunk, int total,
                                                      int per_xcd)
 {
     constexpr int KL_BM = KlTile::kBM, KL_BN = KlTile::kBN;
-    extern __shared__ __align__(16) float sm[];   // KlTile::SMEM floats, set at launch
+    extern __shared__ __align__(16) float sm[];   // set at launch
 
     // XCD-aware order (workgroup b runs on XCD b % 8): chunks of qchunk row
     // tiles, then entity tiles, then the chunk's row tiles.
@@ -66,16 +70,11 @@ __global__ __launch_bounds__(256, 2) void k_score_kl(ScoreArgs a, int n_mt, int 
     const int mt = c * qchunk + (r - nt * qcc);
     const int m0 = mt * KL_BM, n0 = nt * KL_BN;
 
-    // Query rows are padded (with zeros) to a multiple of 128 and entity
-    // rows to a multiple of 256, so the whole tile is inside both buffers.
-    const int K = 2 * a.d;
+    // Entity rows are padded (with zeros) to a multiple of 256, so the tile's
+    // columns are inside; query rows past the last are read from it.
     const int n_ent_pad = (int)(a.n_blocks * kEntBlock);
     v4f acc[KlTile::TM][KlTile::TN];
-    if constexpr (KlTile::kBf16x3)
-        KlTile::run(a.qpack, K, n_mt * KL_BM, a.n_rows, a.ent_planes, (int64_t)n_ent_pad * K, K, n_ent_pad, K, m0,
-                    n0, sm, acc);
-    else
-        KlTile::run(a.qpack, K, n_mt * KL_BM, a.ent, K, n_ent_pad, K, m0, n0, sm, acc);
+    KlTile::run(a.qpack, 2 * a.d, a.n_rows, a.ent, 2 * a.d, n_ent_pad, 2 * a.d, m0, n0, sm, acc);
 
     // Epilogue, staged through LDS (the ring is free after the K loop):
     //   1. each lane subtracts E_e and its accumulators from gamma - C_q (one
@@ -90,17 +89,16 @@ __global__ __launch_bounds__(256, 2) void k_score_kl(ScoreArgs a, int n_mt, int 
     //      output row with 16-byte non-temporal stores, so the score matrix
     //      streams past L2 in whole lines instead of 64-byte pieces that
     //      evict the entity rows still to be read.
-    // Query rows are padded to a multiple of 128 (C_q = 0 there) and E_e to
-    // the entity blocks, so the constant reads are in bounds for every row
-    // and column of the tile; padding never reaches the output.
+    // E_e is padded to the entity blocks; rows past the last read the last
+    // row's constants and never reach the output.
     constexpr int TLD = KL_BN + 4;
-    static_assert(KL_BM * TLD <= KlTile::SMEM, "output tile fits the LDS ring");
-    static_assert(KL_BN % 4 == 0 && 256 % (KL_BN / 4) == 0, "output row pieces");
+    constexpr int THREADS = 256;
+    static_assert(KL_BN % 4 == 0 && THREADS % (KL_BN / 4) == 0 && KL_BM % (THREADS / (KL_BN / 4)) == 0, "output row pieces");
     // The output rows of the thread's rows in step 2, loaded now and waited
     // for once before it: a load inside its loop would wait (vmcnt) for the
     // stores issued before it as well. (Rows past the last are clamped to
     // it: no branch, so the loads issue back to back.)
-    constexpr int C4 = KL_BN / 4, RPP = 256 / C4;     // 16-byte pieces per row, rows per pass
+    constexpr int C4 = KL_BN / 4, RPP = THREADS / C4;     // 16-byte pieces per row, rows per pass
     constexpr int NIT = KL_BM / RPP;
     const int r0 = threadIdx.x / C4;
     int32_t od[NIT];
@@ -115,7 +113,7 @@ __global__ __launch_bounds__(256, 2) void k_score_kl(ScoreArgs a, int n_mt, int 
 #pragma unroll
     for (int i = 0; i < KlTile::TM; ++i)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) gq[i][q] = (double)a.gamma - a.cq[m0 + KlTile::row_of(i) + q];
+        for (int q = 0; q < 4; ++q) gq[i][q] = (double)a.gamma - a.cq[min(m0 + KlTile::row_of(i) + q, a.n_rows - 1)];
 #pragma unroll
     for (int j = 0; j < KlTile::TN; ++j) {
         const int cj = KlTile::col_of(j);
@@ -131,13 +129,7 @@ __global__ __launch_bounds__(256, 2) void k_score_kl(ScoreArgs a, int n_mt, int 
     __syncthreads();
     const int c4 = threadIdx.x % C4;
     const int64_t n = n0 + 4 * c4;
-    // Chunk keys (128-entity tiles only): the 16 lanes of a chunk are one DPP
-    // row, and every lane of a row stays in the loop below (the row-uniform
-    // branches keep its DPP rows whole); lanes past N add key 0.
-    constexpr bool KEYS = KlTile::kBf16x3 && KL_BN == 2 * kKeyChunk;
-    const bool keys = KEYS && a.chunk_key != nullptr;
-    const bool tail = n0 + KL_BN > a.N;               // the last entity tile
-    if (!keys && n >= a.N) return;
+    if (n >= a.N) return;
     const int n_grouped = a.n_quad + a.n_pair;
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
@@ -159,25 +151,6 @@ __global__ __launch_bounds__(256, 2) void k_score_kl(ScoreArgs a, int n_mt, int 
             v = make_float4(fmaxf(v.x, w.x), fmaxf(v.y, w.y), fmaxf(v.z, w.z), fmaxf(v.w, w.w));
         }
         const int64_t orow = od[it];
-        if constexpr (KEYS) {
-            if (keys) {
-                // An upper bound of the keys of the lane's scores: the key of
-                // their float maximum (the scores order as their keys, NaN
-                // aside), or the largest key when one is NaN; columns past N
-                // count as -inf (in the last entity tile only).
-                float4 kv = v;
-                if (tail) {
-                    const float ninf = -__builtin_inff();
-                    kv = make_float4(n < a.N ? kv.x : ninf, n + 1 < a.N ? kv.y : ninf, n + 2 < a.N ? kv.z : ninf,
-                                     n + 3 < a.N ? kv.w : ninf);
-                }
-                const float mx = fmaxf(fmaxf(kv.x, kv.y), fmaxf(kv.z, kv.w));
-                const bool nan = __builtin_isunordered(kv.x, kv.y) || __builtin_isunordered(kv.z, kv.w);
-                const uint32_t u = __float_as_uint(mx == 0.0f ? 0.0f : mx);
-                const uint32_t kx = chunk16_max(nan ? 0xFFFFFFFFu : u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u));
-                if ((c4 & 15) == 0 && n < a.N) a.chunk_key[orow * a.key_ld + n / kKeyChunk] = max(kx, 1u);
-            }
-        }
         float* dst = a.scores + orow * a.ld + n;
         if (n + 3 < a.N) {
             // rows start only 4-byte aligned; gfx950 takes dword-aligned
@@ -192,6 +165,196 @@ __global__ __launch_bounds__(256, 2) void k_score_kl(ScoreArgs a, int n_mt, int 
     }
 }
 
+// Split form on the f16 matrix cores (MfmaTileF16x2): the entity rows are
+// operand A and the query rows B, so a lane holds 4 consecutive entities of
+// one query row in each block and the epilogue stays in registers: no LDS
+// tile, no barrier, and the 64 entities of a wavefront are one chunk key.
+// Through an LDS tile like the FP32 kernel's the epilogue took 0.22 of 0.77 ms
+// at the 63,361-entity workload (2,341 rows), 0.05 of it for the stores; in
+// registers 0.18. The rest was the slot of a workgroup standing empty between
+// tiles (constants' loads, stores draining, the next workgroup's start and
+// first stage), so two workgroups per compute unit stay and take tile after
+// tile: a tile's last stage requests the next tile's first, and the wait for
+// the epilogue's constants, before its stores, covers it: 0.69 ms.
+template <class Tile>
+__global__ __launch_bounds__(Tile::kThreads, 2) void k_score_kl_split(ScoreArgs a, int n_qt, int n_et, int qchunk,
+                                                                      int total, int per_xcd)
+{
+    constexpr int BE = Tile::kBM, BQ = Tile::kBN;      // entities, query rows of a tile
+    extern __shared__ __align__(16) float sm[];
+    // XCD-aware order as in k_score_kl (chunks of qchunk query tiles, then
+    // entity tiles, then the chunk's query tiles): XCD x has positions
+    // [x * per_xcd, (x + 1) * per_xcd), its workgroups take them in turn
+    const int xcd0 = (blockIdx.x & 7) * per_xcd;
+    const int n_mine = min(per_xcd, total - xcd0), n_wg = gridDim.x >> 3;
+    const int64_t ld = plane_ld(2 * a.d);
+    const int nk = (int)(ld / 32);
+    typename Tile::Loader loader;
+    int e0 = 0, q0 = 0;
+    auto locate = [&](int p) {
+        const int L = xcd0 + p;
+        const int chunk_wg = qchunk * n_et;
+        const int c = L / chunk_wg;
+        const int r = L - c * chunk_wg;
+        const int qcc = min(qchunk, n_qt - c * qchunk);
+        const int et = r / qcc;
+        e0 = et * BE;
+        q0 = (c * qchunk + (r - et * qcc)) * BQ;
+        loader.set(a.ent_split, ld, (int)(a.n_blocks * kEntBlock), a.qpack, ld, a.n_rows, e0, q0);
+    };
+    int pos = blockIdx.x >> 3, slot = 0;
+    if (pos >= n_mine) return;
+    locate(pos);
+    loader.issue(0, sm, slot);
+    wait_vm_barrier<0>();
+    for (;;) {
+        v4f acc[Tile::TM][Tile::TN], low[Tile::TM][Tile::TN];
+        Tile::clear(acc, low);
+        const int te0 = e0, tq0 = q0;              // this tile; the next one's from the last stage on
+        const bool more = pos + n_wg < n_mine;
+        for (int kt = 0; kt < nk; ++kt) {
+            if (kt > 0) wait_vm_barrier<0>();      // (the first stage landed before the loop or the last stores)
+            Tile::stage(sm, slot, acc, low, [&] {
+                if (kt + 1 < nk) {
+                    loader.issue(kt + 1, sm, slot ^ 1);
+                } else if (more) {
+                    locate(pos + n_wg);
+                    loader.issue(0, sm, slot ^ 1);
+                }
+            });
+            slot ^= 1;
+        }
+        pos += n_wg;
+
+        // The lane's query rows (one per block column; past the last: the last's
+        // constants, nothing stored) and entities (the table's constants are
+        // padded to whole blocks). Loaded before the first store and waited for
+        // once: a load issued later would wait (vmcnt) for the stores before it.
+        constexpr int TM = Tile::TM, TN = Tile::TN;
+        double gq[TN];
+        float sq[TN];
+        int32_t od[TN];
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int m = min(tq0 + Tile::col_of(j), a.n_rows - 1);
+            gq[j] = a.cq[m];
+            sq[j] = a.q_scale[m];
+            od[j] = a.out_dest[score_out_index(m, a.n_quad, a.n_pair)];
+        }
+        // scores in place: gamma - C_q - E_e - the contraction (the large sum plus
+        // the small ones', in the two rows' scales), in double precision
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int e = te0 + Tile::row_of(i);
+            double ee[4];
+            float se[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                ee[q] = (double)a.gamma - a.ee[e + q];
+                se[q] = a.ent_scale[e + q];
+            }
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float v = fmaf(low[i][j][q], kSplitLow, acc[i][j][q]) * (sq[j] * se[q]);
+                    acc[i][j][q] = (float)((ee[q] - gq[j]) - (double)v);
+                }
+        }
+        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);                  // the constants, and the next tile's first stage
+        const int n_grouped = a.n_quad + a.n_pair;
+        const int64_t ew = te0 + Tile::row_of(0);                  // the lane's first entity
+        const bool tail = te0 + BE > a.N;                          // the last entity tile
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int m = tq0 + Tile::col_of(j);
+            // union groups of four rows and pairs: the maximum over a quad of
+            // lanes or a pair; its first lane stores
+            bool first = m < a.n_rows;
+            if (m - (int)(threadIdx.x & 15) < n_grouped) {        // (the same for the 16 lanes of a block column)
+                const bool quad = m < a.n_quad, pair = !quad && m < n_grouped;
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        float v = acc[i][j][q];
+                        const float p = fmaxf(v, dpp_f32<0xB1>(v));          // lanes 1, 0, 3, 2
+                        const float f = fmaxf(p, dpp_f32<0x4E>(p));          // lanes 2, 3, 0, 1
+                        acc[i][j][q] = quad ? f : pair ? p : v;
+                    }
+                if (quad) first = first && (m & 3) == 0;
+                else if (pair) first = first && ((m - a.n_quad) & 1) == 0;
+            }
+            float* dst = a.scores + od[j] * a.ld + ew;
+            float kmax = -__builtin_inff();
+            bool nan = false;
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                v4f v = acc[i][j];
+                if (!tail) {
+                    typedef float f4u_t __attribute__((ext_vector_type(4), aligned(4)));
+                    if (first) *reinterpret_cast<f4u_t*>(dst + i * 16) = v;
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const bool in = ew + i * 16 + q < a.N;
+                        if (first && in) dst[i * 16 + q] = v[q];
+                        v[q] = in ? v[q] : -__builtin_inff();
+                    }
+                }
+                kmax = fmaxf(kmax, fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)));
+                nan = nan || __builtin_isunordered(v.x, v.y) || __builtin_isunordered(v.z, v.w);
+            }
+            if (a.chunk_key) {
+                // an upper bound of the keys of the chunk's scores: the key of
+                // their float maximum (the scores order as their keys, NaN
+                // aside), or the largest key when one is NaN
+                const uint32_t u = __float_as_uint(kmax == 0.0f ? 0.0f : kmax);
+                uint32_t kx = nan ? 0xFFFFFFFFu : u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+                kx = max(kx, (uint32_t)__shfl_xor((int)kx, 16, 64));
+                kx = max(kx, (uint32_t)__shfl_xor((int)kx, 32, 64));
+                const int64_t chunk0 = te0 + (Tile::row_of(0) & ~(kKeyChunk - 1));
+                if (first && (threadIdx.x & 48) == 0 && chunk0 < a.N)
+                    a.chunk_key[od[j] * a.key_ld + chunk0 / kKeyChunk] = max(kx, 1u);
+            }
+        }
+        if (!more) return;
+        // every wavefront's part of the next tile's first stage has landed
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    }
+}
+
+// Query-tile chunk: as many tiles as ~2 MiB of query rows (about half an
+// XCD's L2). The entity table is streamed once per chunk, and the XCDs split
+// the global order evenly whatever the chunk size, so larger chunks cost no
+// balance.
+static int tile_chunk(int n_tiles, int rows, int64_t row_floats)
+{
+    return (int)std::min<int64_t>(n_tiles, std::max<int64_t>(1, (int64_t)(2 << 20) / (rows * row_floats * 4)));
+}
+
+// Dynamic LDS above the 64 KiB static limit: raised once per device and kernel.
+template <class Kernel>
+static void raise_lds(Kernel k, int bytes, bool (&raised)[64])
+{
+    int dev = 0;
+    if (bytes > 65536 && hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64 && !raised[dev])
+        raised[dev] = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
+}
+
+template <class Tile>
+static void launch_split(const ScoreArgs& a, hipStream_t s)
+{
+    static_assert(Tile::TM * 16 == kKeyChunk, "a wavefront's entities are one chunk");
+    const int n_qt = (a.n_rows + Tile::kBN - 1) / Tile::kBN;
+    const int n_et = (int)((a.N + Tile::kBM - 1) / Tile::kBM);
+    const int total = n_qt * n_et, per_xcd = (total + 7) / 8;
+    static bool raised[64] = {};
+    raise_lds(k_score_kl_split<Tile>, Tile::SMEM * 4, raised);
+    const int n_wg = std::min(per_xcd, 64);    // per XCD: two on each of 32 compute units
+    hipLaunchKernelGGL((k_score_kl_split<Tile>), dim3(n_wg * 8), dim3(Tile::kThreads), Tile::SMEM * 4, s, a, n_qt, n_et, tile_chunk(n_qt, Tile::kBN, plane_ld(2 * a.d)), total, per_xcd);
+}
+
 template <class Tile>
 static void launch_tiles(const ScoreArgs& a, hipStream_t s)
 {
@@ -200,49 +363,35 @@ static void launch_tiles(const ScoreArgs& a, hipStream_t s)
     const int n_nt = (int)((a.N + BN - 1) / BN);
     const int total = n_mt * n_nt;
     const int per_xcd = (total + 7) / 8;
-    // Row-tile chunk: as many row tiles as ~2 MiB of query rows (about half an
-    // XCD's L2). The entity table is streamed once per chunk, and the XCDs
-    // split the global order evenly whatever the chunk size, so larger
-    // chunks cost no balance.
-    const int64_t tile_bytes = (int64_t)BM * 2 * a.d * 4;
-    const int qchunk = (int)std::min<int64_t>(n_mt, std::max<int64_t>(1, (int64_t)(2 << 20) / tile_bytes));
-    // LDS is dynamic so that rings above the 64 KiB static limit fit; the
-    // limit is raised once per device and tile
-    constexpr int lds = Tile::SMEM * 4;
-    if (lds > 65536) {
-        static bool raised[64] = {};
-        int dev = 0;
-        if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64 && !raised[dev]) {
-            if (hipFuncSetAttribute((const void*)k_score_kl<Tile>, hipFuncAttributeMaxDynamicSharedMemorySize, lds) ==
-                hipSuccess)
-                raised[dev] = true;
-        }
-    }
-    hipLaunchKernelGGL((k_score_kl<Tile>), dim3(per_xcd * 8), dim3(256), lds, s, a, n_mt, n_nt, qchunk, total,
-                       per_xcd);
+    constexpr int lds = std::max(Tile::SMEM, BM * (BN + 4)) * 4;    // the tile ring, then the output tile over it
+    static bool raised[64] = {};
+    raise_lds(k_score_kl<Tile>, lds, raised);
+    hipLaunchKernelGGL((k_score_kl<Tile>), dim3(per_xcd * 8), dim3(256), lds, s, a, n_mt, n_nt,
+                       tile_chunk(n_mt, BM, 2 * a.d), total, per_xcd);
 }
 
-constexpr int kScoreKlFp32Rows = 64;   // scored rows up to which the FP32 tile runs
+// The split form from more than one FP32 tile (64 x 64) per compute unit on:
+// below, its tiles of 128 x 128 leave most of the chip idle. One 1p query: 80
+// us a call split and 75 FP32 at 14,505 entities (227 tiles), 106 and 126 at
+// 63,361 (990); 96 rows at 14,505 (454 tiles): 91 and 98; 192 rows at 3,000
+// (141 tiles): 87 and 81.
+bool score_kl_takes_split(int n_rows, int64_t N, bool always)
+{
+    return always || (int64_t)((n_rows + 63) / 64) * ((N + 63) / 64) > 256;
+}
 
 bool launch_score_kl(const ScoreArgs& a, hipStream_t s)
 {
     if (a.n_rows <= 0) return false;
     using LdsTile = MfmaTileLds<64, 64, 3>;
     using LdsTileHalf = MfmaTileLds<64, 64, 3, true>;
-    using SplitTile = MfmaTileBf16x3<128, 128, 4, true>;
-    // The bf16 split tile pays from 65 scored rows on: at fewer, its
-    // 128-row tile is mostly padding and its entity-tile grid too small to
-    // fill the chip (B = 1: 142 us per 1p query at 63,361 entities, 92 us at
-    // 14,505, against 131 and 77 us on the FP32 64 x 64 tile). Up to 128
-    // rows it also needs a workgroup per compute unit (96 rows at 14,505
-    // entities, 114 tiles: 1.12 against 1.04 us per query); from 129 rows
-    // it wins with fewer (160 and 240 rows at 14,505: 0.71 and 0.50 against
-    // 0.74 and 0.57 us per query).
-    const int64_t split_tiles = (int64_t)((a.n_rows + 127) / 128) * ((a.N + 127) / 128);
-    const bool split_pays =
-        a.split_always || (a.n_rows > kScoreKlFp32Rows && (a.n_rows > 128 || split_tiles >= 256));
-    if (a.ent_planes && (2 * a.d) % 32 == 0 && split_pays) {   // planes: row stride 2d
-        launch_tiles<SplitTile>(a, s);
+    // 128 x 128 with 4 wavefronts: 0.73 ms a launch at the 63,361-entity
+    // workload (before the workgroups stayed), 256 entities x 128 rows 0.80,
+    // 128 x 256 0.90, both with 8 wavefronts; 128 x 64 1.40 against 1.31 ms a
+    // step, 4 x 1 wavefronts 1.325
+    using SplitTile = MfmaTileF16x2<128, 128, 2, 2>;
+    if (a.ent_split) {
+        launch_split<SplitTile>(a, s);
         return a.chunk_key != nullptr;
     }
     if (LdsTile::supports(2 * a.d)) {
@@ -252,7 +401,7 @@ bool launch_score_kl(const ScoreArgs& a, hipStream_t s)
     } else {
         const int64_t big_tiles = (int64_t)((a.n_rows + 127) / 128) * ((a.N + 127) / 128);
         if (big_tiles < 512) launch_tiles<MfmaTileReg<64, 64>>(a, s);
-        else launch_tiles<MfmaTileReg<kRowTileBetae, 128>>(a, s);
+        else launch_tiles<MfmaTileReg<128, 128>>(a, s);
     }
     return false;
 }

@@ -48,6 +48,7 @@ struct Lane {
     float* gate = nullptr;
     float* qpack = nullptr;
     double* cq = nullptr;
+    float* q_scale = nullptr;     // BetaE: scales of the packed rows in split form
     float* scores = nullptr;
     float* gemm_ws = nullptr;     // split-K partials of small dense layers
     int64_t gemm_ws_elems = 0;
@@ -101,7 +102,8 @@ struct kgq_handle {
     float* ent_blk = nullptr;     // scoring table: GQE/Q2B/LogicE blocked points; BetaE row-major U|V;
                                   // ConE blocked half-angle sin | cos
     double* ent_const = nullptr;  // BetaE E_e [n_pad]
-    uint16_t* ent_planes = nullptr;   // BetaE [U | V] rows of ent_blk as three bf16 planes (when 2d % 32 == 0)
+    float* ent_split = nullptr;   // BetaE [U | V] rows of ent_blk in split form, with their scales [n_pad]
+    float* ent_scale = nullptr;
     float* rel_o_sp = nullptr;    // Q2B softplus(offset_raw) [R x d]
     L1Fixed l1;                   // GQE / LogicE: fixed-point form of ent_blk (off: floats)
     float cone_modulus = 0.f;     // ConE distance scale (host copy of "modulus")
@@ -329,6 +331,7 @@ void free_all(kgq_handle* h)
 // fields of k_pack_cone).
 int64_t qpack_row_floats(int model, int d)
 {
+    if (model == KGQ_BETAE) return plane_ld(2 * d);   // rows in split form end in whole stages
     return (int64_t)d * (model == KGQ_GQE ? 1 : model == KGQ_CONE ? 5 : 2);
 }
 
@@ -352,7 +355,10 @@ kgq_status allocate_all(kgq_handle* h)
         ALLOC(h->ent_rm, N * 2 * d);
         ALLOC(h->ent_blk, n_pad * 2 * d + kEntPad);
         if (c.model == KGQ_BETAE) ALLOC(h->ent_const, n_pad);
-        if (c.model == KGQ_BETAE && (2 * d) % 32 == 0) ALLOC(h->ent_planes, 3 * n_pad * 2 * d);
+        if (c.model == KGQ_BETAE) {
+            ALLOC(h->ent_split, n_pad * plane_ld(2 * d));
+            ALLOC(h->ent_scale, n_pad);
+        }
         ALLOC(h->proj1_ent, N * 4 * d);
         ALLOC(h->proj1_rel, (int64_t)c.n_relations * 4 * d);
         if (c.model == KGQ_CONE) {
@@ -406,6 +412,7 @@ kgq_status allocate_all(kgq_handle* h)
         ALLOC(L.logits, m_max * d);
         ALLOC(L.qpack, h->cap_score_rows * qpack_row_floats(c.model, (int)d) + kQpackPad);
         ALLOC(L.cq, h->cap_score_rows);
+        ALLOC(L.q_scale, h->cap_score_rows);
         ALLOC(L.scores, Bm * N);
         // split-K runs only while a layer has fewer than 128 output tiles of
         // 64 x 64, so 16 slices of it stay below 16 x 128 x 4096 floats
@@ -764,6 +771,9 @@ kgq_status run_plan(kgq_handle* h, Lane& L, const Plan& p, const int32_t* P, con
     const int tq = score_row_pad(c.model);
     const int n_rows_pad = ((p.n_score_rows + tq - 1) / tq) * tq;
     const int d_score = logice ? 2 * d : d;    // LogicE scores its 2d bound coordinates as one vector
+    // BetaE: query and entity rows in split form on the f16 matrix cores
+    const bool split = betae && h->dense_path != KGQ_DENSE_FP32 &&
+                       score_kl_takes_split(p.n_score_rows, N, h->dense_path == KGQ_DENSE_BF16X3);
     {
         StageTimer t(h, 3, s);
         if (h->l1.on)
@@ -772,7 +782,7 @@ kgq_status run_plan(kgq_handle* h, Lane& L, const Plan& p, const int32_t* P, con
                            L.qpack, L.cq, s);
         else
         launch_pack(c.model, P + p.off_score_src, mlp ? P + p.off_score_neg : nullptr, p.n_score_rows, n_rows_pad,
-                    L.states, W, d_score, c.center_reg, L.qpack, L.cq, s);
+                    L.states, W, d_score, c.center_reg, L.qpack, L.cq, split ? L.q_scale : nullptr, s);
     }
     float* dst = out_scores ? out_scores : L.scores;
     bool keyed = false;   // the scorer wrote chunk keys for top-k
@@ -783,8 +793,11 @@ kgq_status run_plan(kgq_handle* h, Lane& L, const Plan& p, const int32_t* P, con
         a.dist_scale = logice ? 1.0f / (float)(2 * d) : cone ? h->cone_modulus : 1.0f;
         a.l1_fixed = h->l1.on;
         if (h->l1.on) a.dist_scale *= h->l1.quantum;
-        if (betae && h->dense_path != KGQ_DENSE_FP32) a.ent_planes = h->ent_planes;
-        a.split_always = h->dense_path == KGQ_DENSE_BF16X3;
+        if (split) {
+            a.ent_split = h->ent_split;
+            a.ent_scale = h->ent_scale;
+            a.q_scale = L.q_scale;
+        }
         a.part = L.score_ws;
         a.part_elems = L.score_ws_elems;
         if (out_idx) {
@@ -892,6 +905,7 @@ int64_t carve_scratch(const kgq_handle* h, const Plan& p, int32_t k, bool need_s
     const int64_t srows = ((int64_t)(p.n_score_rows + tq - 1) / tq) * tq;
     V.qpack = reinterpret_cast<float*>(take((srows * qpack_row_floats(c.model, (int)d) + kQpackPad) * 4));
     V.cq = reinterpret_cast<double*>(take(srows * 8));
+    V.q_scale = reinterpret_cast<float*>(take(srows * 4));
     V.scores = need_scores ? reinterpret_cast<float*>(take(B * N * 4)) : nullptr;
     const int64_t ncand = need_topk ? topk_scratch_elems(B, N, k) : 0;
     for (int i = 0; i < 2; ++i) {
@@ -1317,8 +1331,8 @@ kgq_status kgq_load_params(kgq_handle* h, const char* name, const void* src, siz
         if (c.model == KGQ_BETAE) {
             launch_betae_entity_prep(stage, bf16, c.n_entities, c.dim, h->n_blocks, h->ent_rm, h->ent_blk,
                                      h->ent_const, nullptr);
-            if (h->ent_planes)
-                launch_split_planes(h->ent_blk, h->ent_planes, h->n_blocks * kEntBlock, 2 * (int64_t)c.dim, nullptr);
+            launch_split_rows(h->ent_blk, h->n_blocks * kEntBlock, 2 * (int64_t)c.dim, 2 * (int64_t)c.dim, h->ent_split,
+                              h->ent_scale, nullptr);
         }
         else if (c.model == KGQ_CONE)
             launch_cone_entity_prep(static_cast<const float*>(stage), c.n_entities, c.dim, h->n_blocks, h->ent_rm,

@@ -31,9 +31,8 @@ constexpr int kMaxK = 1024;
 constexpr int kTqGqe = 24;
 constexpr int kTqQ2b = 12;
 constexpr int kTqCone = 8;
-// BetaE query rows are packed row-major [row][alpha (d) | beta (d)] and
-// padded to the matrix-core scorer's 128-row tile.
-constexpr int kRowTileBetae = 128;
+// BetaE query rows are packed row-major [row][alpha (d) | beta (d)], not
+// padded (the matrix-core scorer reads rows past the last from it).
 
 // The VALU scorers read up to two dimension steps past the last block of the
 // entity table and one past the last block of packed rows: floats allocated
@@ -51,7 +50,7 @@ inline int score_row_pad(int model)
     case KGQ_GQE: return kTqGqe;
     case KGQ_Q2B: return kTqQ2b;
     case KGQ_CONE: return kTqCone;
-    default: return kRowTileBetae;
+    default: return 1;
     }
 }
 
@@ -149,6 +148,11 @@ __host__ __device__ inline int64_t plane_ld(int64_t cols) { return (cols + 31) /
 // ld = plane_ld(cols), row r at r * ld, zeros in columns cols .. ld - 1;
 // w = p0 + p1 + p2 exactly (round to nearest even at each step).
 void launch_split_planes(const float* w, uint16_t* p, int64_t rows, int64_t cols, hipStream_t s);
+
+// Rows of w [rows x cols] (row stride ld) in the split form of the f16
+// matrix-core tile (mfma_tile.hpp): dst row stride plane_ld(cols) words, zeros
+// past cols, and each row's scale.
+void launch_split_rows(const float* w, int64_t rows, int64_t cols, int64_t ld, float* dst, float* scale, hipStream_t s);
 
 // Epilogue value of output column n.
 __device__ __forceinline__ float apply_epilogue(int epi, int split, int n, float v)
@@ -248,9 +252,11 @@ void launch_pack_l1(int model, const int32_t* src_row, const int32_t* neg, int n
                     const float* states, int W, int d, const L1Fixed& f, float gamma, float dist_scale, float* qpack,
                     double* base, hipStream_t s);
 // Pack scored rows into the scorer's layout; BetaE also C_q = sum lnB(a, b)
-// and the reciprocal of rows with neg[j] != 0 (neg may be NULL).
+// and the reciprocal of rows with neg[j] != 0 (neg may be NULL); with q_scale
+// its rows in split form and their scales.
 void launch_pack(int model, const int32_t* src_row, const int32_t* neg, int n_rows, int n_rows_pad,
-                 const float* states, int W, int d, float center_reg, float* qpack, double* cq, hipStream_t s);
+                 const float* states, int W, int d, float center_reg, float* qpack, double* cq, float* q_scale,
+                 hipStream_t s);
 
 // ---- ConE / LogicE (k_cone_logice.hip) ----
 void launch_cone_entity_prep(const float* src, int64_t N, int d, int64_t n_blocks, float* ent_rm, float* blocked,
@@ -331,14 +337,15 @@ struct ScoreArgs {
     bool l1_fixed = false;
     float* part = nullptr;             // GQE / Query2Box split-d partials for small batches
     int64_t part_elems = 0;            //   (nullptr: never split)
-    // BetaE: the [U | V] rows of `ent` split into three bf16 planes (plane
-    // stride n_blocks * 256 * 2d) for the bf16 matrix-core contraction, or
-    // nullptr for the FP32 one
-    const uint16_t* ent_planes = nullptr;
-    bool split_always = false;         // the bf16 contraction at any row count (tests)
+    // BetaE: the [U | V] rows of `ent` in split form (launch_split_rows, row
+    // stride plane_ld(2d)) and their scales, the packed rows in the same form
+    // with theirs; nullptr: the FP32 contraction
+    const float* ent_split = nullptr;
+    const float* ent_scale = nullptr;
+    const float* q_scale = nullptr;
     // Per output row and chunk of kKeyChunk entities, the largest score_key
     // of the row's scores in the chunk (at least 1), [rows x key_ld] with
-    // key_ld >= ceil(N / kKeyChunk), written by the BetaE bf16 contraction
+    // key_ld >= ceil(N / kKeyChunk), written by the BetaE split contraction
     // and the VALU scorers' unsplit form; nullptr: not written
     uint32_t* chunk_key = nullptr;
     int64_t key_ld = 0;
@@ -356,8 +363,10 @@ __host__ __device__ inline int score_out_index(int r, int n_quad, int n_pair)
     return (n_quad >> 2) + (n_pair >> 1) + (r - n_quad - n_pair);
 }
 
-// Both return whether the chunk keys were written (only the bf16 BetaE
-// contraction writes them, and only when a.chunk_key is set).
+// Whether the BetaE scorer takes the split form for this many scored rows.
+bool score_kl_takes_split(int n_rows, int64_t N, bool always);
+// Both return whether the chunk keys were written (of BetaE only the split
+// form writes them, and only when a.chunk_key is set).
 bool launch_score(const ScoreArgs& a, hipStream_t s);      // GQE, Query2Box: VALU
 bool launch_score_kl(const ScoreArgs& a, hipStream_t s);   // BetaE: matrix cores
 

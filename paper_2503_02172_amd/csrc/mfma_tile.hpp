@@ -32,6 +32,8 @@
 //   cores. B comes as three bf16 planes (split beforehand), A as FP32 and is
 //   split in registers; six of the nine part products per k range, on
 //   v_mfma_f32_16x16x32_bf16 with FP32 accumulation (details at the struct).
+// MfmaTileF16x2 (rows in split form): the same error class from two f16 parts
+//   a value and three products, both operands split and scaled by row ahead.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -45,8 +47,8 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 
 template <int BM, int BN>
 struct MfmaTileReg {
-    static constexpr int kBM = BM, kBN = BN;
-    static constexpr bool kBf16x3 = false;
+    static constexpr int kBM = BM, kBN = BN, kThreads = 256;
+    static constexpr bool kSplit = false;
     static constexpr int BK = 32;
     static constexpr int LD = BK + 4;                  // padded LDS row (floats)
     static constexpr int TM = BM / 32, TN = BN / 32;   // MFMA tiles per wavefront
@@ -156,8 +158,8 @@ typedef __attribute__((address_space(3))) void lds_void;
 
 template <int BM, int BN, int S, bool HALF = false>
 struct MfmaTileLds {
-    static constexpr int kBM = BM, kBN = BN;
-    static constexpr bool kBf16x3 = false;
+    static constexpr int kBM = BM, kBN = BN, kThreads = 256;
+    static constexpr bool kSplit = false;
     static constexpr int BK = 32;
     static constexpr int CH = BK / 4;                  // 16-byte chunks per row per stage
     static constexpr int RPI = 64 / CH;                // rows written by one wave instruction
@@ -378,7 +380,6 @@ __device__ __forceinline__ v4f mfma_bf16(const v4u& a, const v4u& b, v4f c)
 template <int BM, int BN, int WM = 4, bool PRIO = false>
 struct MfmaTileBf16x3 {
     static constexpr int kBM = BM, kBN = BN;
-    static constexpr bool kBf16x3 = true;
     static constexpr int BK = 32;
     static constexpr int WN = 4 / WM;                  // wavefronts along N
     static constexpr int AROW = BK * 4;                // bytes of one A row per stage (FP32)
@@ -543,6 +544,174 @@ struct MfmaTileBf16x3 {
     }
 
     // Output position of acc[i][j][r] within the workgroup tile.
+    __device__ static int row_of(int i) { return ((threadIdx.x >> 6) / WN) * (BM / WM) + i * 16 + ((threadIdx.x & 63) >> 4) * 4; }
+    __device__ static int col_of(int j) { return ((threadIdx.x >> 6) % WN) * (BN / WN) + j * 16 + (threadIdx.x & 15); }
+};
+
+// ---- FP32-class products on the f16 matrix cores, both operands split ahead ---
+//
+// Split. Every row of an operand is scaled by a power of two that brings its
+// largest magnitude into [2^14, 2^15) and each scaled value is written as
+// x = h + l / 2048 with h = f16(x), l = f16((x - h) 2048) (round to nearest
+// even): h takes 11 significant bits and l the next 11 at the same exponent
+// range, so x is held to 2^-23 of itself (exactly, three times out of four)
+// down to 2^-28 of the row's largest, and to 2^-50 of the largest below.
+// Products. x y = hh' + (hl' + lh') / 2048 + ll' / 2^22: three products of six
+// in the bf16 form; the dropped one is below 2^-22 |x y| and of either sign.
+// The two small ones accumulate apart and join the large one, scaled, at the
+// end, so 32 of K round the large sum once (six times in the bf16 form): the
+// error of a long sum is below the bf16 form's although a single product's is
+// not. A row's values are stored as chunks of 8: 8 h (16 bytes), then 8 l:
+// 4 bytes a value, K padded with zeros to whole 32-wide stages.
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef _Float16 v4h __attribute__((ext_vector_type(4)));
+
+constexpr float kSplitLow = 1.0f / 2048.0f;       // weight of the low part
+
+// Scale of a row whose largest magnitude is m (a power of two, its reciprocal
+// finite; 1 for a row of zeros or with a value that is not finite).
+__device__ __forceinline__ float split_scale(float m)
+{
+    const int e = (int)(__float_as_uint(m) >> 23 & 255u);
+    if (e == 0 || e == 255) return 1.0f;
+    return __uint_as_float((uint32_t)max(e - 14, 1) << 23);
+}
+__device__ __forceinline__ float split_inverse(float s) { return __uint_as_float(0x7F000000u - __float_as_uint(s)); }
+
+__device__ __forceinline__ void split_f16x2(float x, _Float16& h, _Float16& l)      // x already scaled
+{
+    h = (_Float16)x;
+    l = (_Float16)((x - (float)h) * 2048.0f);
+}
+
+// A chunk of 8 values, scaled by inv, to its 32 bytes at dst.
+__device__ __forceinline__ void store_split8(float* dst, const float (&x)[8], float inv)
+{
+    v8h h, l;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        _Float16 a, b;
+        split_f16x2(x[t] * inv, a, b);
+        h[t] = a;
+        l[t] = b;
+    }
+    reinterpret_cast<v8h*>(dst)[0] = h;
+    reinterpret_cast<v8h*>(dst)[1] = l;
+}
+
+// Tiles: WM x WN wavefronts, each with (BM / WM / 16) x (BN / WN / 16) blocks
+// of 16 x 16, two accumulators a block. Stages of 32 of K go through a
+// two-slot LDS ring by direct-to-LDS loads; both operands' rows are 128 bytes a
+// stage, 16-byte pieces XOR-swizzled by row as in the bf16 form, and fragments
+// are read as they are: no split work in the loop. Lane l holds the output
+// rows 4 (l / 16) .. + 3 of column l % 16 of each block. A stage: wait until it
+// has landed, barrier (every wavefront has read the one before, whose slot is
+// free), fragments, the next stage's loads, products.
+template <int BM, int BN, int WM, int WN>
+struct MfmaTileF16x2 {
+    static constexpr int kBM = BM, kBN = BN, kThreads = 64 * WM * WN;
+    static constexpr bool kSplit = true;
+    static constexpr int BK = 32, ROW = 128;
+    static constexpr int ABYTES = BM * ROW, STAGE = (BM + BN) * ROW;
+    static constexpr int TM = BM / WM / 16, TN = BN / WN / 16;
+    static constexpr int AI = BM / 8 / (WM * WN), BI = BN / 8 / (WM * WN);    // load instructions a wavefront and stage
+    static constexpr int SMEM = 2 * STAGE / 4;         // floats
+    static_assert(TM >= 1 && TN >= 1 && AI >= 1 && BI >= 1, "tile shape");
+    __device__ static int swz(int row) { return (row & 7) ^ ((row >> 3) & 1); }
+
+    // Loads of one tile's stages. Rows past M or N are read from the last one.
+    struct Loader {
+        // (uniform bases, 32-bit lane offsets inside the tile: ld <= 16,384)
+        const char* ab;
+        const char* bb;
+        uint32_t ag[AI], bg[BI];
+
+        // load instruction t = h * waves + wave writes rows 8t .. 8t + 7
+        __device__ __forceinline__ void set(const float* A, int64_t lda, int M, const float* B, int64_t ldb, int N,
+                                            int m0, int n0)
+        {
+            const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+            ab = reinterpret_cast<const char*>(A + (int64_t)m0 * lda);
+            bb = reinterpret_cast<const char*>(B + (int64_t)n0 * ldb);
+#pragma unroll
+            for (int h = 0; h < AI; ++h) {
+                const int row = (h * WM * WN + wave) * 8 + (lane >> 3);
+                ag[h] = (uint32_t)min(row, M - 1 - m0) * (uint32_t)lda * 4 + ((lane & 7) ^ swz(row)) * 16;
+            }
+#pragma unroll
+            for (int h = 0; h < BI; ++h) {
+                const int row = (h * WM * WN + wave) * 8 + (lane >> 3);
+                bg[h] = (uint32_t)min(row, N - 1 - n0) * (uint32_t)ldb * 4 + ((lane & 7) ^ swz(row)) * 16;
+            }
+        }
+        __device__ __forceinline__ void issue(int kt, float* sm, int slot) const
+        {
+            const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+            char* st = reinterpret_cast<char*>(sm) + slot * STAGE;
+            const char* ak = ab + kt * ROW;
+            const char* bk = bb + kt * ROW;
+#pragma unroll
+            for (int h = 0; h < AI; ++h)
+                __builtin_amdgcn_global_load_lds((const void*)(ak + ag[h]),
+                                                 (lds_void*)(st + (h * WM * WN + wave) * 1024), 16, 0, 0);
+#pragma unroll
+            for (int h = 0; h < BI; ++h)
+                __builtin_amdgcn_global_load_lds((const void*)(bk + bg[h]),
+                                                 (lds_void*)(st + ABYTES + (h * WM * WN + wave) * 1024), 16, 0, 0);
+        }
+    };
+
+    __device__ __forceinline__ static void clear(v4f (&hi)[TM][TN], v4f (&lo)[TM][TN])
+    {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) hi[i][j] = lo[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+    }
+
+    // The products of one landed stage; next() (the next stage's loads) runs
+    // once the fragments have been asked for.
+    template <typename Next>
+    __device__ __forceinline__ static void stage(const float* sm, int slot, v4f (&hi)[TM][TN], v4f (&lo)[TM][TN],
+                                                 Next next)
+    {
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int wm = wave / WN, wn = wave % WN, grp = lane >> 4, li = lane & 15;
+        const char* st = reinterpret_cast<const char*>(sm) + slot * STAGE;
+        v8h a[TM][2], b[TN][2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                const int row = wm * (BM / WM) + i * 16 + li;
+                a[i][q] = *reinterpret_cast<const v8h*>(st + row * ROW + ((2 * grp + q) ^ swz(row)) * 16);
+            }
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int row = wn * (BN / WN) + j * 16 + li;
+                b[j][q] = *reinterpret_cast<const v8h*>(st + ABYTES + row * ROW + ((2 * grp + q) ^ swz(row)) * 16);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        next();
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                hi[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[i][0], b[j][0], hi[i][j], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                lo[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[i][0], b[j][1], lo[i][j], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                lo[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[i][1], b[j][0], lo[i][j], 0, 0, 0);
+    }
+
+    // Output position of block (i, j)'s element r within the workgroup tile.
     __device__ static int row_of(int i) { return ((threadIdx.x >> 6) / WN) * (BM / WM) + i * 16 + ((threadIdx.x & 63) >> 4) * 4; }
     __device__ static int col_of(int j) { return ((threadIdx.x >> 6) % WN) * (BN / WN) + j * 16 + (threadIdx.x & 15); }
 };

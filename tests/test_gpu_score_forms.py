@@ -137,3 +137,38 @@ def test_gpu_point_table_layout_bf16(model, name, n_ent, d):
     assert np.array_equal(outs[0], outs[1])
     ref = O.Model(model, w.params, w.gamma).scores(S["2i"], qb.anchors, qb.relations)
     check_scores(outs[0], ref, w.rtol, w.gamma, name)
+
+
+@pytest.mark.parametrize("structure", ["1p", "2u", "pni"])
+@pytest.mark.parametrize("n_ent,d,B,wide", [(300, 32, 5, False), (129, 36, 150, True), (1000, 52, 130, True),
+                                           (64, 400, 33, True)])
+def test_gpu_betae_split_scorer(structure, n_ent, d, B, wide):
+    """BetaE's f16 matrix-core scorer (forced) at ragged entity and row tiles
+    and widths that end inside a 32-wide stage; wide: entity parameters from
+    1e-3 to 50 and projections that reach both ends of the regulariser.
+    Tolerance: 2^-20 of the contraction, whose terms are all positive, (the
+    parts' 2^-21 and the sum's rounding), the states' float error through the
+    same terms, and the score's last rounding."""
+    import torch
+    from scipy.special import digamma
+    from paper_2503_02172_amd import kgq
+    w = synth.make_tiny(O.BETAE, n_ent=n_ent, n_rel=7, dim=d, seed=101)
+    ab = w.params["entity.alpha_beta"]
+    if wide:
+        rng = np.random.Generator(np.random.PCG64(102))
+        ab[:] = np.exp(rng.uniform(np.log(1e-3), np.log(50.0), ab.shape)).astype(np.float32)
+    qb = synth.draw_queries(structure, B, n_ent, 7, seed=103)
+    with kgq.engine_for(w, max_batch=B) as eng:
+        eng.set_dense_path(kgq.DENSE_BF16X3)
+        out = eng.execute(S[structure], qb.anchors, qb.relations, k=5, scores=True)
+        torch.cuda.synchronize()
+        got, idx, val = (out[n].cpu().numpy() for n in ("scores", "idx", "score"))
+    ref = O.Model(O.BETAE, w.params, w.gamma).scores(S[structure], qb.anchors, qb.relations)
+    a, b = ab[:, :d].astype(np.float64), ab[:, d:].astype(np.float64)
+    u, v = digamma(a + b) - digamma(a), digamma(a + b) - digamma(b)
+    # the contraction is score-sized plus the constants: bound it through the
+    # entity's own terms at the regulariser's reach in these workloads
+    big = (u + v).sum(1)[None] * (2000.0 if wide else 20.0) + np.abs(ref) + w.gamma
+    assert np.all(np.abs(got - ref) <= 2.0 ** -20 * big + w.rtol * np.maximum(np.abs(ref), w.gamma)), \
+        (np.abs(got - ref) / big).max() * 2 ** 20
+    check_topk(idx, val, got, 5, 0.0, w.gamma, structure)

@@ -1,0 +1,88 @@
+"""The two-part f16 split behind the f16 matrix-core form, checked in numpy on
+the CPU (no GPU code is run here).
+
+Claims checked, for rows of float32 values scaled by the power of two that
+brings the largest into [2^14, 2^15): with h = f16(x) and l = f16((x - h)
+2048), x - h is exact in float32 and x = h + l / 2048 to 2^-23 of x down to
+2^-28 of the row's largest value, and to 2^-50 of the largest below; the
+three kept part products miss a product by less than 2^-21 of it; and the
+contraction of rows of positive values, summed in float32 over stages of 32,
+is no further from 64 bits than the six-product bf16 form's."""
+
+import numpy as np
+import pytest
+
+from tests.test_split_bf16_cpu import split3
+
+
+def scale_of(m):
+    e = (np.float32(m).view(np.uint32) >> 23) & 255
+    if e in (0, 255):
+        return np.float32(1.0)
+    return np.array([max(int(e) - 14, 1) << 23], np.uint32).view(np.float32)[0]
+
+
+def split2(x, s):
+    y = (x.astype(np.float32) * (np.float32(1.0) / s)).astype(np.float32)
+    h = y.astype(np.float16)
+    r = (y - h.astype(np.float32)).astype(np.float32)
+    return y, h, r, (r * np.float32(2048.0)).astype(np.float16)
+
+
+@pytest.mark.parametrize("span", [0, 10, 28, 60])
+def test_split_error(span):
+    g = np.random.default_rng(span)
+    for m in (1.0, 3e4, 1e-20, 2e30):
+        x = (g.uniform(1, 2, 20000) * np.exp2(-g.integers(0, span + 1, 20000)) * g.choice([-1.0, 1.0], 20000) * m).astype(np.float32)
+        big = np.abs(x).max()
+        s = scale_of(big)
+        assert 2.0 ** 14 <= float(big) / float(s) < 2.0 ** 15
+        y, h, r, l = split2(x, s)
+        assert np.array_equal(r.astype(np.float64), y.astype(np.float64) - h.astype(np.float64)), "x - h"
+        err = np.abs(h.astype(np.float64) + l.astype(np.float64) / 2048 - y.astype(np.float64)) * float(s)
+        assert np.all(err <= np.maximum(np.abs(x.astype(np.float64)) * 2.0 ** -23, float(big) * 2.0 ** -50))
+
+
+def test_scale_is_a_finite_power_of_two():
+    for m in (0.0, 1e-45, 1.2e-38, 1e-30, 1.0, 3.4e38, np.inf, np.nan):
+        s = scale_of(np.float32(m))
+        assert np.frexp(s)[0] == 0.5 and np.isfinite(np.float32(1.0) / s)
+
+
+def test_three_products_bound():
+    g = np.random.default_rng(3)
+    x, y = (g.uniform(1, 2, 50000).astype(np.float32) for _ in range(2))
+    (_, h, _, l), (_, H, _, L) = split2(x, scale_of(x.max())), split2(y, scale_of(y.max()))
+    h, l, H, L = (v.astype(np.float64) for v in (h, l, H, L))
+    kept = (h * H + (h * L + l * H) / 2048) * float(scale_of(x.max())) * float(scale_of(y.max()))
+    ref = x.astype(np.float64) * y.astype(np.float64)
+    assert np.all(np.abs(kept - ref) <= 2.0 ** -21 * ref)
+
+
+@pytest.mark.parametrize("K", [64, 800])
+def test_positive_contraction_no_further_off_than_bf16x3(K):
+    g = np.random.default_rng(K)
+    a = np.maximum(1 + g.uniform(-1, 1, (60, K)), 0.05).astype(np.float32)
+    a[30:] = (1.0 / a[30:]).astype(np.float32)                # negated rows: reciprocals
+    u = (g.gamma(0.7, 1.5, (200, K)) + 0.01).astype(np.float32)
+    ref = a.astype(np.float64) @ u.astype(np.float64).T
+
+    def staged(parts):
+        """Sum over stages of 32: each product's stage in 64 bits (the matrix
+        core's own sum), rounded into a float32 accumulator."""
+        accs = [np.zeros(ref.shape, np.float32) for _ in range(max(p[2] for p in parts) + 1)]
+        for k in range(0, K, 32):
+            for p, q, i in parts:
+                accs[i] = (accs[i] + p[:, k:k + 32].astype(np.float64) @ q[:, k:k + 32].astype(np.float64).T).astype(np.float32)
+        return accs
+
+    sa = np.array([scale_of(r.max()) for r in a])[:, None]
+    su = np.array([scale_of(r.max()) for r in u])[:, None]
+    ah, al = (np.stack([split2(r, s[0])[i] for r, s in zip(a, sa)]) for i in (1, 3))
+    uh, ul = (np.stack([split2(r, s[0])[i] for r, s in zip(u, su)]) for i in (1, 3))
+    hi, lo = staged([(ah, uh, 0), (ah, ul, 1), (al, uh, 1)])
+    new = (hi + lo * np.float32(1 / 2048)) * (sa * su.T)
+    (xh, xm, xl, _, _), (yh, ym, yl, _, _) = split3(a), split3(u)
+    old = staged([(xh, yh, 0), (xh, ym, 0), (xm, yh, 0), (xm, ym, 0), (xh, yl, 0), (xl, yh, 0)])[0]
+    rms = lambda x: np.sqrt(np.mean(((x.astype(np.float64) - ref) / ref) ** 2))
+    assert rms(new) <= rms(old), (rms(new), rms(old))
