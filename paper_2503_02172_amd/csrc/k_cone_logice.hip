@@ -35,6 +35,7 @@
 #include <algorithm>
 
 #include "kgq_internal.hpp"
+#include "mfma_tile.hpp"
 
 namespace kgq {
 
@@ -140,13 +141,79 @@ __global__ __launch_bounds__(1024) void k_mlp_proj_prep(const int32_t* src_row, 
     }
 }
 
+// The same in split form: a wavefront per row.
+template <int MODEL>
+__global__ __launch_bounds__(256) void k_mlp_proj_prep_split(const int32_t* src_row, const int32_t* anchor_ref,
+                                                             const int32_t* rel_ref, const int32_t* neg,
+                                                             const int32_t* anchors, const int32_t* rels,
+                                                             const float* states, const float* ent_rm,
+                                                             const float* rel, int64_t n_ent, int n_rel, int d, int M,
+                                                             SplitRows x, int* flag)
+{
+    const int m = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (m >= M) return;
+    const int W = 2 * d;
+    const int32_t sr = src_row[m];
+    const float* base = sr >= 0 ? states + (int64_t)sr * W
+                                : ent_rm + (int64_t)checked_id_cl(anchors[anchor_ref[m]], n_ent, flag) * W;
+    const bool inv = neg && neg[m];
+    const int64_t r = checked_id_cl(rels[rel_ref[m]], n_rel, flag);
+    const int width = MODEL == KGQ_CONE ? W : 3 * d, n8 = (int)(plane_ld(width) / 8);
+    // four columns at a time: none straddles two fields (d is a multiple of 4)
+    auto four = [&](int k) {
+        if (k >= width) return make_float4(0.f, 0.f, 0.f, 0.f);
+        auto at = [](const float* p) { return *reinterpret_cast<const float4*>(p); };
+        float4 v;
+        if (MODEL == KGQ_CONE) {
+            v = at(base + k);
+            const float4 q = at(rel + r * W + k);
+            if (inv) {
+                float z = 0.f;
+                if (k < d) {
+                    cone_negate(v.x, z);
+                    cone_negate(v.y, z);
+                    cone_negate(v.z, z);
+                    cone_negate(v.w, z);
+                } else {
+                    cone_negate(z, v.x);
+                    cone_negate(z, v.y);
+                    cone_negate(z, v.z);
+                    cone_negate(z, v.w);
+                }
+            }
+            return make_float4(v.x + q.x, v.y + q.y, v.z + q.z, v.w + q.w);
+        }
+        if (k >= W) return at(rel + r * d + k - W);
+        if (!inv) return at(base + k);
+        v = at(base + (k < d ? k + d : k - d));
+        return make_float4(1.0f - v.x, 1.0f - v.y, 1.0f - v.z, 1.0f - v.w);
+    };
+    split_row_wave([&](int c, float (&v)[8]) {
+#pragma unroll
+                       for (int h = 0; h < 2; ++h) {
+                           const float4 q = four(8 * c + 4 * h);
+                           v[4 * h] = q.x;
+                           v[4 * h + 1] = q.y;
+                           v[4 * h + 2] = q.z;
+                           v[4 * h + 3] = q.w;
+                       }
+                   },
+                   n8, x.rows + (int64_t)m * n8 * 8, x.scale + m, lane);
+}
+
 void launch_mlp_proj_prep(int model, const int32_t* src_row, const int32_t* anchor_ref, const int32_t* rel_ref,
                           const int32_t* neg, int M, const int32_t* anchors, const int32_t* rels,
                           const float* states, const float* ent_rm, const float* rel, int64_t n_ent, int n_rel,
-                          int d, float* x, int* flag, hipStream_t s)
+                          int d, float* x, SplitRows split, int* flag, hipStream_t s)
 {
     if (M <= 0) return;
-    if (model == KGQ_CONE)
+    if (split.rows && model == KGQ_CONE)
+        hipLaunchKernelGGL(k_mlp_proj_prep_split<KGQ_CONE>, dim3((M + 3) / 4), dim3(256), 0, s, src_row, anchor_ref,
+                           rel_ref, neg, anchors, rels, states, ent_rm, rel, n_ent, n_rel, d, M, split, flag);
+    else if (split.rows)
+        hipLaunchKernelGGL(k_mlp_proj_prep_split<KGQ_LOGICE>, dim3((M + 3) / 4), dim3(256), 0, s, src_row, anchor_ref,
+                           rel_ref, neg, anchors, rels, states, ent_rm, rel, n_ent, n_rel, d, M, split, flag);
+    else if (model == KGQ_CONE)
         hipLaunchKernelGGL(k_mlp_proj_prep<KGQ_CONE>, dim3(M), dim3(row_threads(d)), 0, s, src_row, anchor_ref, rel_ref, neg,
                            anchors, rels, states, ent_rm, rel, n_ent, n_rel, d, x, flag);
     else
@@ -197,18 +264,60 @@ __global__ __launch_bounds__(256) void k_cone_int_prep(GroupArgs g, const float*
     }
 }
 
-void launch_cone_int_prep(const GroupArgs& g, const float* states, int d, float* x_int, hipStream_t s)
+// The same in split form: a wavefront per input row.
+__global__ __launch_bounds__(256) void k_cone_int_prep_split(GroupArgs g, const float* states, int d, SplitRows x)
+{
+    const int gi = blockIdx.x, lane = threadIdx.x & 63, j = threadIdx.x >> 6;
+    if (j >= g.n_in[gi]) return;
+    const int64_t row = g.in_start[gi] + j;
+    const bool inv = (g.neg_mask[gi] >> j) & 1;
+    const float* src = states + row * 2 * d;
+    const int n8 = (int)(plane_ld(2 * d) / 8);
+    split_row_wave([&](int c, float (&v)[8]) {
+                       // (d is a multiple of 4: four values lie on one side of it)
+#pragma unroll
+                       for (int h = 0; h < 2; ++h) {
+                           const int k = 8 * c + 4 * h, i = k < d ? k : k - d;
+                           float th[4] = {}, ps[4] = {};
+                           if (k < 2 * d) {
+                               *reinterpret_cast<float4*>(th) = *reinterpret_cast<const float4*>(src + i);
+                               *reinterpret_cast<float4*>(ps) = *reinterpret_cast<const float4*>(src + d + i);
+                           }
+#pragma unroll
+                           for (int t = 0; t < 4; ++t) {
+                               if (inv && k < 2 * d) cone_negate(th[t], ps[t]);
+                               v[4 * h + t] = k < d ? th[t] - ps[t] : th[t] + ps[t];
+                           }
+                       }
+                   },
+                   n8, x.rows + row * n8 * 8, x.scale + row, lane);
+}
+
+void launch_cone_int_prep(const GroupArgs& g, const float* states, int d, float* x_int, SplitRows split, hipStream_t s)
 {
     if (g.n_groups <= 0) return;
-    hipLaunchKernelGGL(k_cone_int_prep, dim3(g.n_groups), dim3(256), 0, s, g, states, d, x_int);
+    if (split.rows)
+        hipLaunchKernelGGL(k_cone_int_prep_split, dim3(g.n_groups), dim3(64 * kGroupInputs), 0, s, g, states, d, split);
+    else
+        hipLaunchKernelGGL(k_cone_int_prep, dim3(g.n_groups), dim3(256), 0, s, g, states, d, x_int);
 }
 
 // ConE axis: attention-weighted mean of the branch axes' unit vectors; and
 // the mean over branches of the aperture set function's hidden features
 // (columns d .. 2d-1 of the stacked first layer's output).
-__global__ __launch_bounds__(1024) void k_cone_combine_axis(GroupArgs g, const float* states, const float* logits,
-                                                           const float* hid, int d, float* zmean, float* out_states)
+// Value k of a row in split form.
+__device__ __forceinline__ float split_value(const float* row, float scale, int k)
 {
+    const _Float16* p = reinterpret_cast<const _Float16*>(row + (k & ~7)) + (k & 7);
+    return fmaf((float)p[8], kSplitLow, (float)p[0]) * scale;
+}
+
+template <bool SPLIT>
+__global__ __launch_bounds__(1024) void k_cone_combine_axis(GroupArgs g, const float* states, const float* logits,
+                                                           const float* hid, const float* hid_scale, int d, float* zmean,
+                                                           SplitRows zsplit, float* out_states)
+{
+    extern __shared__ __align__(16) float zrow[];      // SPLIT: the mean, d floats padded to whole stages
     const int gi = blockIdx.x;
     const int i0 = g.in_start[gi];
     const int n = g.n_in[gi];
@@ -227,20 +336,38 @@ __global__ __launch_bounds__(1024) void k_cone_combine_axis(GroupArgs g, const f
             z += w;
             cx += w * cs;
             sy += w * sn;
-            zm += hid[(int64_t)(i0 + j) * 2 * d + d + k];
+            if (SPLIT) zm += split_value(hid + (i0 + j) * plane_ld(2 * d), hid_scale[i0 + j], d + k);
+            else zm += hid[(int64_t)(i0 + j) * 2 * d + d + k];
         }
         // the weights' common factor 1/z does not change the angle
         out_states[orow * 2 * d + k] = atan2f(sy / z, cx / z);
-        zmean[(int64_t)gi * d + k] = zm / (float)n;
+        if (SPLIT) zrow[k] = zm / (float)n;
+        else zmean[(int64_t)gi * d + k] = zm / (float)n;
+    }
+    if constexpr (SPLIT) {
+        const int ld = (int)plane_ld(d);
+        for (int k = d + threadIdx.x; k < ld; k += blockDim.x) zrow[k] = 0.f;
+        __syncthreads();
+        if (threadIdx.x < 64)
+            split_row_wave([&](int c, float (&v)[8]) {
+#pragma unroll
+                               for (int t = 0; t < 8; ++t) v[t] = zrow[c * 8 + t];
+                           },
+                           ld / 8, zsplit.rows + (int64_t)gi * ld, zsplit.scale + gi, threadIdx.x);
     }
 }
 
-void launch_cone_combine_axis(const GroupArgs& g, const float* states, const float* logits, const float* hid, int d,
-                              float* zmean, float* out_states, hipStream_t s)
+void launch_cone_combine_axis(const GroupArgs& g, const float* states, const float* logits, const float* hid,
+                              const float* hid_scale, int d, float* zmean, SplitRows zsplit, float* out_states,
+                              hipStream_t s)
 {
     if (g.n_groups <= 0) return;
-    hipLaunchKernelGGL(k_cone_combine_axis, dim3(g.n_groups), dim3(row_threads(d)), 0, s, g, states, logits, hid, d, zmean,
-                       out_states);
+    if (hid_scale)
+        hipLaunchKernelGGL(k_cone_combine_axis<true>, dim3(g.n_groups), dim3(row_threads(d)), plane_ld(d) * 4, s, g, states,
+                           logits, hid, hid_scale, d, zmean, zsplit, out_states);
+    else
+        hipLaunchKernelGGL(k_cone_combine_axis<false>, dim3(g.n_groups), dim3(row_threads(d)), 0, s, g, states, logits, hid,
+                           nullptr, d, zmean, zsplit, out_states);
 }
 
 // ConE half-aperture: min over branches (complemented where negated) times

@@ -492,6 +492,19 @@ void launch_combine_offset(const GroupArgs& g, const float* states, int W, const
                        rel_o, n_rel, d, out_states, flag);
 }
 
+// Eight values k .. k + 7 of a row of `width` (a multiple of 4), zeros past it.
+__device__ __forceinline__ void load8(const float* row, int k, int width, float (&v)[8])
+{
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const float4 q = k + 4 * h < width ? *reinterpret_cast<const float4*>(row + k + 4 * h) : make_float4(0.f, 0.f, 0.f, 0.f);
+        v[4 * h] = q.x;
+        v[4 * h + 1] = q.y;
+        v[4 * h + 2] = q.z;
+        v[4 * h + 3] = q.w;
+    }
+}
+
 // BetaE: copy each intersection input row, inverting both shape parameters
 // of negated branches (negation), into the attention MLP input buffer.
 __global__ void k_betae_int_prep(GroupArgs g, const float* states, int d, float* x_int)
@@ -517,38 +530,62 @@ __global__ void k_betae_int_prep(GroupArgs g, const float* states, int d, float*
     }
 }
 
-
-void launch_betae_int_prep(const GroupArgs& g, const float* states, int d, float* x_int, hipStream_t s)
+// The same in split form: a wavefront per input row.
+__global__ __launch_bounds__(256) void k_betae_int_prep_split(GroupArgs g, const float* states, int d, SplitRows x)
 {
-    if (g.n_groups <= 0) return;
-    hipLaunchKernelGGL(k_betae_int_prep, dim3(g.n_groups), dim3(row_threads(2 * d)), 0, s, g, states, d, x_int);
+    const int gi = blockIdx.x, lane = threadIdx.x & 63, j = threadIdx.x >> 6;
+    if (j >= g.n_in[gi]) return;
+    const int64_t row = g.in_start[gi] + j;
+    const bool inv = (g.neg_mask[gi] >> j) & 1;
+    const int W = 2 * d, n8 = (int)(plane_ld(W) / 8);
+    const float* src = states + row * W;
+    split_row_wave([&](int c, float (&v)[8]) { load8(src, c * 8, W, v);
+                       if (inv)
+#pragma unroll
+                           for (int t = 0; t < 8; ++t) v[t] = c * 8 + t < W ? 1.0f / v[t] : 0.f; },
+                   n8, x.rows + row * n8 * 8, x.scale + row, lane);
 }
 
-__global__ void k_betae_combine(GroupArgs g, const float* x_int, const float* logits, int d, float* states)
+void launch_betae_int_prep(const GroupArgs& g, const float* states, int d, float* x_int, SplitRows split, hipStream_t s)
+{
+    if (g.n_groups <= 0) return;
+    if (split.rows)
+        hipLaunchKernelGGL(k_betae_int_prep_split, dim3(g.n_groups), dim3(64 * kGroupInputs), 0, s, g, states, d, split);
+    else
+        hipLaunchKernelGGL(k_betae_int_prep, dim3(g.n_groups), dim3(row_threads(2 * d)), 0, s, g, states, d, x_int);
+}
+
+__global__ void k_betae_combine(GroupArgs g, const float* sin, const float* logits, int d, float* states)
 {
     const int gi = blockIdx.x;
     const int i0 = g.in_start[gi];
     const int n = g.n_in[gi];
     const int64_t orow = g.out_row[gi];
+    const int neg = g.neg_mask[gi];
     const int W = 2 * d;
     for (int k = threadIdx.x; k < d; k += blockDim.x) {
         float w[kGroupInputs];
         softmax_branches(logits + (int64_t)i0 * d, d, n, k, w);
         float al = 0.f, be = 0.f;
         for (int j = 0; j < n; ++j) {
-            al += w[j] * x_int[(int64_t)(i0 + j) * W + k];
-            be += w[j] * x_int[(int64_t)(i0 + j) * W + d + k];
+            float a = sin[(int64_t)(i0 + j) * W + k], b = sin[(int64_t)(i0 + j) * W + d + k];
+            if ((neg >> j) & 1) {
+                a = 1.0f / a;
+                b = 1.0f / b;
+            }
+            al += w[j] * a;
+            be += w[j] * b;
         }
         states[orow * W + k] = al;
         states[orow * W + d + k] = be;
     }
 }
 
-void launch_betae_combine(const GroupArgs& g, const float* x_int, const float* logits, int d,
+void launch_betae_combine(const GroupArgs& g, const float* sin, const float* logits, int d,
                           float* states, hipStream_t s)
 {
     if (g.n_groups <= 0) return;
-    hipLaunchKernelGGL(k_betae_combine, dim3(g.n_groups), dim3(row_threads(d)), 0, s, g, x_int, logits, d, states);
+    hipLaunchKernelGGL(k_betae_combine, dim3(g.n_groups), dim3(row_threads(d)), 0, s, g, sin, logits, d, states);
 }
 
 __global__ void k_betae_proj_prep(const int32_t* src_row, const int32_t* anchor_ref, const int32_t* rel_ref,
@@ -576,14 +613,45 @@ __global__ void k_betae_proj_prep(const int32_t* src_row, const int32_t* anchor_
     }
 }
 
+// The same in split form: a wavefront per row.
+__global__ __launch_bounds__(256) void k_betae_proj_prep_split(const int32_t* src_row, const int32_t* anchor_ref,
+                                                               const int32_t* rel_ref, const int32_t* neg,
+                                                               const int32_t* anchors, const int32_t* rels,
+                                                               const float* states, const float* ent_ab,
+                                                               const float* rel, int64_t n_ent, int n_rel, int d, int M,
+                                                               SplitRows x, int* flag)
+{
+    const int m = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (m >= M) return;
+    const int W = 2 * d, n8 = (int)(plane_ld(W) / 8);
+    const int32_t sr = src_row[m];
+    const float* base = sr >= 0 ? states + (int64_t)sr * W
+                                : ent_ab + (int64_t)checked_id(anchors[anchor_ref[m]], n_ent, flag) * W;
+    const bool inv = neg && neg[m];
+    const float* rr = rel + (int64_t)checked_id(rels[rel_ref[m]], n_rel, flag) * W;
+    split_row_wave([&](int c, float (&v)[8]) {
+                       float r[8];
+                       load8(base, c * 8, W, v);
+                       load8(rr, c * 8, W, r);
+#pragma unroll
+                       for (int t = 0; t < 8; ++t)
+                           v[t] = c * 8 + t < W ? (inv ? 1.0f / v[t] : v[t]) + r[t] : 0.f;
+                   },
+                   n8, x.rows + (int64_t)m * n8 * 8, x.scale + m, lane);
+}
+
 void launch_betae_proj_prep(const int32_t* src_row, const int32_t* anchor_ref, const int32_t* rel_ref,
                             const int32_t* neg, int M, const int32_t* anchors, const int32_t* rels,
                             const float* states, const float* ent_ab, const float* rel,
-                            int64_t n_ent, int n_rel, int d, float* x, int* flag, hipStream_t s)
+                            int64_t n_ent, int n_rel, int d, float* x, SplitRows split, int* flag, hipStream_t s)
 {
     if (M <= 0) return;
-    hipLaunchKernelGGL(k_betae_proj_prep, dim3(M), dim3(row_threads(2 * d)), 0, s, src_row, anchor_ref, rel_ref, neg, anchors,
-                       rels, states, ent_ab, rel, n_ent, n_rel, d, x, flag);
+    if (split.rows)
+        hipLaunchKernelGGL(k_betae_proj_prep_split, dim3((M + 3) / 4), dim3(256), 0, s, src_row, anchor_ref, rel_ref, neg,
+                           anchors, rels, states, ent_ab, rel, n_ent, n_rel, d, M, split, flag);
+    else
+        hipLaunchKernelGGL(k_betae_proj_prep, dim3(M), dim3(row_threads(2 * d)), 0, s, src_row, anchor_ref, rel_ref, neg,
+                           anchors, rels, states, ent_ab, rel, n_ent, n_rel, d, x, flag);
 }
 
 // BetaE first-hop projection, first layer, from the precomputed tables: the
@@ -612,13 +680,38 @@ __global__ __launch_bounds__(256) void k_betae_proj1(const int32_t* anchor_ref, 
     }
 }
 
+// The same in split form: a wavefront per row.
+__global__ __launch_bounds__(256) void k_betae_proj1_split(const int32_t* anchor_ref, const int32_t* rel_ref,
+                                                           const int32_t* anchors, const int32_t* rels,
+                                                           const float* pe, const float* pr, int64_t n_ent, int n_rel,
+                                                           int w, int M, SplitRows h1, int* flag)
+{
+    const int m = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (m >= M) return;
+    const float* x = pe + (int64_t)checked_id(anchors[anchor_ref[m]], n_ent, flag) * w;
+    const float* y = pr + (int64_t)checked_id(rels[rel_ref[m]], n_rel, flag) * w;
+    const int n8 = (int)(plane_ld(w) / 8);
+    split_row_wave([&](int c, float (&v)[8]) {
+                       float r[8];
+                       load8(x, c * 8, w, v);
+                       load8(y, c * 8, w, r);
+#pragma unroll
+                       for (int t = 0; t < 8; ++t) v[t] = fmaxf(v[t] + r[t], 0.f);
+                   },
+                   n8, h1.rows + (int64_t)m * n8 * 8, h1.scale + m, lane);
+}
+
 void launch_betae_proj1(const int32_t* anchor_ref, const int32_t* rel_ref, int M, const int32_t* anchors,
                         const int32_t* rels, const float* pe, const float* pr, int64_t n_ent, int n_rel, int w,
-                        float* h1, int* flag, hipStream_t s)
+                        float* h1, SplitRows split, int* flag, hipStream_t s)
 {
     if (M <= 0) return;
-    hipLaunchKernelGGL(k_betae_proj1, dim3(M), dim3(256), 0, s, anchor_ref, rel_ref, anchors, rels, pe, pr, n_ent,
-                       n_rel, w, h1, flag);
+    if (split.rows)
+        hipLaunchKernelGGL(k_betae_proj1_split, dim3((M + 3) / 4), dim3(256), 0, s, anchor_ref, rel_ref, anchors, rels, pe,
+                           pr, n_ent, n_rel, w, M, split, flag);
+    else
+        hipLaunchKernelGGL(k_betae_proj1, dim3(M), dim3(256), 0, s, anchor_ref, rel_ref, anchors, rels, pe, pr, n_ent,
+                           n_rel, w, h1, flag);
 }
 
 // ---------------------------------------------------------------------------

@@ -166,33 +166,53 @@ void launch_split_planes(const float* w, uint16_t* p, int64_t rows, int64_t cols
     hipLaunchKernelGGL(k_split_planes, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, w, p, cols, ld, n);
 }
 
-// One wavefront per row: its largest magnitude, then its chunks of 8.
 __global__ __launch_bounds__(256) void k_split_rows(const float* __restrict__ w, int64_t rows, int cols, int64_t ld,
-                                                    float* __restrict__ dst, float* __restrict__ scale)
+                                                    float* __restrict__ dst, float* __restrict__ scale,
+                                                    float* __restrict__ norm)
 {
     const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= rows) return;
     const int lane = threadIdx.x & 63;
     const float* src = w + row * ld;
-    float m = 0.f;
-    for (int k = lane; k < cols; k += 64) m = fmaxf(m, fabsf(src[k]));
-    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    const float sc = split_scale(m), inv = split_inverse(sc);
     const int n8 = (int)(plane_ld(cols) / 8);
-    float* out = dst + row * (int64_t)n8 * 8;
-    for (int c = lane; c < n8; c += 64) {
-        float x[8];
+    split_row_wave(
+        [&](int c, float (&x)[8]) {
 #pragma unroll
-        for (int t = 0; t < 8; ++t) x[t] = c * 8 + t < cols ? src[c * 8 + t] : 0.f;
-        store_split8(out + c * 8, x, inv);
+            for (int t = 0; t < 8; ++t) x[t] = c * 8 + t < cols ? src[c * 8 + t] : 0.f;
+        },
+        n8, dst + row * (int64_t)n8 * 8, scale + row, lane);
+    if (norm) {
+        float m = 0.f;
+        for (int k = lane; k < cols; k += 64) m += fabsf(src[k]);
+        for (int off = 32; off > 0; off >>= 1) m += __shfl_xor(m, off, 64);
+        if (lane == 0) atomicMax(reinterpret_cast<unsigned int*>(norm), __float_as_uint(m));   // (bits order as values)
     }
-    if (lane == 0) scale[row] = sc;
 }
 
-void launch_split_rows(const float* w, int64_t rows, int64_t cols, int64_t ld, float* dst, float* scale, hipStream_t s)
+__global__ void k_zero_word(float* p) { *p = 0.f; }
+
+void launch_split_rows(const float* w, int64_t rows, int64_t cols, int64_t ld, float* dst, float* scale, float* norm,
+                       hipStream_t s)
 {
     if (rows <= 0) return;
-    hipLaunchKernelGGL(k_split_rows, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, w, rows, (int)cols, ld, dst, scale);
+    if (norm) hipLaunchKernelGGL(k_zero_word, dim3(1), dim3(1), 0, s, norm);
+    hipLaunchKernelGGL(k_split_rows, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, w, rows, (int)cols, ld, dst,
+                       scale, norm);
+}
+
+// The largest bias, or 0: what a bias adds to a rectified layer's bound (a
+// unit switched off by a huge negative bias doesn't widen it).
+__global__ __launch_bounds__(64) void k_bias_max(const float* b, int64_t n, float* out)
+{
+    float m = 0.f;
+    for (int64_t i = threadIdx.x; i < n; i += 64) m = fmaxf(m, b[i]);
+    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+    if (threadIdx.x == 0) *out = m;
+}
+
+void launch_bias_max(const float* b, int64_t n, float* out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_bias_max, dim3(1), dim3(64), 0, s, b, n, out);
 }
 
 template <int BM, int BN, bool PRIO>
@@ -369,6 +389,240 @@ void launch_gemm(const GemmArgs& g, hipStream_t s)
         hipLaunchKernelGGL(k_gemm<GemmTileLdsHalf>, grid, dim3(256), 0, s, g, tm, tn, per_xcd);
     else
         hipLaunchKernelGGL(k_gemm<GemmTileReg>, grid, dim3(256), 0, s, g, tm, tn, per_xcd);
+}
+
+// ---- layers on rows in split form --------------------------------------------
+//
+// y[m] = epi(W x[m] + b) with W's rows as operand A and x's as B
+// (MfmaTileF16x2): a lane then holds four consecutive outputs of one row m, 16
+// bytes as float32, or 8 + 8 bytes of a split row's chunk. Three f16 products
+// where the bf16 form takes six and splits its inputs in every tile. Measured
+// on 1600 outputs of K = 1600: 4096 rows 124 -> 75 us, 1000 rows 42 -> 27 us,
+// 280 rows 17 + 5 (split K, then the sum) -> 16 us, 60 rows 15 -> 12 us, one
+// row 11 -> 7.4 us. The large ones run 63 GFLOP of products at 0.84 PFLOP/s:
+// two or three tiles of 64 to 128 rows a CU, each a chain of 50 stages.
+
+// Four consecutive outputs n .. n + 3 of row m (v: the products' sum, in the
+// operands' scales).
+__device__ __forceinline__ void store_split_outputs(const SplitGemm& g, int m, int n, int64_t row, float xs, float ys,
+                                                    const float4& ws, const float4& bias, const v4f& v)
+{
+    const float w4[4] = {ws.x, ws.y, ws.z, ws.w}, b4[4] = {bias.x, bias.y, bias.z, bias.w};
+    float o[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o[q] = apply_epilogue(g.epi, g.epi_split, n + q, fmaf(v[q], xs * w4[q], b4[q]));
+    if (!g.y_split) {
+        if (n < g.N) *reinterpret_cast<float4*>(g.y + row * g.ldy + n) = make_float4(o[0], o[1], o[2], o[3]);
+        return;
+    }
+    const int64_t ld = plane_ld(g.N);
+    if (n >= ld) return;
+    const float inv = split_inverse(ys);
+    v4h h, l;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        _Float16 a, b;
+        split_f16x2(n < g.N ? o[q] * inv : 0.f, a, b);      // (N is a multiple of 4; zeros to the stage's end)
+        h[q] = a;
+        l[q] = b;
+    }
+    char* dst = reinterpret_cast<char*>(g.y_split + (int64_t)m * ld + (n & ~7)) + (n & 4) * 2;
+    *reinterpret_cast<v4h*>(dst) = h;
+    *reinterpret_cast<v4h*>(dst + 16) = l;
+    if (n == 0) g.y_scale[m] = ys;
+}
+
+// Scale of output row m when it is written in split form.
+__device__ __forceinline__ float split_output_scale(const SplitGemm& g, float xs)
+{
+    return g.y_split ? split_scale(fmaf(xs * 32768.0f, g.bound[0], g.bound[1])) : 1.0f;
+}
+
+template <class Tile>
+__global__ __launch_bounds__(Tile::kThreads, 2) void k_gemm_split(SplitGemm g, int tn, int tm, int per_xcd)
+{
+    extern __shared__ __align__(16) float sm_split[];
+    // workgroup b runs on XCD b % 8, which takes positions
+    // [x * per_xcd, (x + 1) * per_xcd) of the row-tile-major order
+    const int b = blockIdx.x;
+    const int L = (b & 7) * per_xcd + (b >> 3);
+    if (L >= tn * tm) return;
+    const int mt = L / tn, nt = L - mt * tn;
+    const int n0 = nt * Tile::kBM, m0 = mt * Tile::kBN;
+    v4f acc[Tile::TM][Tile::TN], low[Tile::TM][Tile::TN];
+    Tile::clear(acc, low);
+    typename Tile::Loader loader;
+    const int64_t ldw = plane_ld(g.K);
+    const int nk = (int)(ldw / 32);
+    loader.set(g.w, ldw, g.N, g.x, g.ldx, g.M, n0, m0);
+    constexpr int S = Tile::kSlots;
+#pragma unroll
+    for (int t = 0; t < S - 1; ++t)
+        if (t < nk) loader.issue(t, sm_split, t);
+    int slot = 0, free = S - 1;                        // the stage's slot, and the one the stage before left
+    for (int kt = 0; kt < nk; ++kt) {
+        // stage kt has landed; the S - 2 after it may be in flight
+        if (S > 2 && kt + S - 2 < nk) wait_vm_barrier<(S - 2) * Tile::LPS>();
+        else wait_vm_barrier<0>();
+        Tile::stage(sm_split, slot, acc, low, [&] {
+            if (kt + S - 1 < nk) loader.issue(kt + S - 1, sm_split, free);
+        });
+        free = slot;
+        slot = slot + 1 == S ? 0 : slot + 1;
+    }
+    // everything the epilogue reads first (indices clamped), then the stores
+    float4 ws[Tile::TM], bias[Tile::TM];
+#pragma unroll
+    for (int i = 0; i < Tile::TM; ++i) {
+        const int n = min(n0 + Tile::row_of(i), g.N - 4);
+        ws[i] = *reinterpret_cast<const float4*>(g.w_scale + n);
+        bias[i] = *reinterpret_cast<const float4*>(g.bias + n);
+    }
+    float xs[Tile::TN], ys[Tile::TN];
+    int64_t row[Tile::TN];
+#pragma unroll
+    for (int j = 0; j < Tile::TN; ++j) {
+        const int m = min(m0 + Tile::col_of(j), g.M - 1);
+        xs[j] = g.x_scale[m];
+        ys[j] = split_output_scale(g, xs[j]);
+        row[j] = g.y_rowmap ? (int64_t)g.y_rowmap[m] : (int64_t)m;
+    }
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+#pragma unroll
+    for (int j = 0; j < Tile::TN; ++j) {
+        const int m = m0 + Tile::col_of(j);
+        if (m >= g.M) continue;
+#pragma unroll
+        for (int i = 0; i < Tile::TM; ++i) {
+            v4f v;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = fmaf(low[i][j][q], kSplitLow, acc[i][j][q]);
+            store_split_outputs(g, m, n0 + Tile::row_of(i), row[j], xs[j], ys[j], ws[i], bias[i], v);
+        }
+    }
+}
+
+// Few rows: a workgroup owns 16 outputs of 16 TN rows and its W wavefronts
+// split K, each taking every W-th stage with its fragments loaded straight from
+// memory, U stages at a time (no LDS ring, no barrier in the loop); the
+// partial sums meet in LDS, added in wavefront order, and the first TN
+// wavefronts finish a block of 16 rows each. One launch, where the split-K
+// form of the tile loop takes a second one to add its slices.
+template <int TN, int W, int U>
+__global__ __launch_bounds__(64 * W) void k_gemm_split_few(SplitGemm g)
+{
+    __shared__ v4f part[W][TN][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int grp = lane >> 4, li = lane & 15;
+    const int n0 = blockIdx.x * 16, m0 = blockIdx.y * 16 * TN;
+    const int64_t ldw = plane_ld(g.K);
+    const int nk = (int)(ldw / 32);
+    const float* wp = g.w + (int64_t)min(n0 + li, g.N - 1) * ldw + grp * 8;
+    const float* xp[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) xp[j] = g.x + (int64_t)min(m0 + j * 16 + li, g.M - 1) * g.ldx + grp * 8;
+    v4f hi[TN], lo[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) hi[j] = lo[j] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = wave; k0 < nk; k0 += W * U) {
+        v8h a[U][2], b[U][TN][2];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int kt = min(k0 + u * W, nk - 1);          // (past the end: in bounds, not multiplied)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                a[u][q] = *reinterpret_cast<const v8h*>(wp + kt * 32 + q * 4);
+#pragma unroll
+                for (int j = 0; j < TN; ++j) b[u][j][q] = *reinterpret_cast<const v8h*>(xp[j] + kt * 32 + q * 4);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);                   // every load of the batch in flight before a product
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (k0 + u * W >= nk) break;
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                hi[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[u][0], b[u][j][0], hi[j], 0, 0, 0);
+                lo[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[u][0], b[u][j][1], lo[j], 0, 0, 0);
+                lo[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[u][1], b[u][j][0], lo[j], 0, 0, 0);
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        v4f v;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = fmaf(lo[j][q], kSplitLow, hi[j][q]);
+        part[wave][j][lane] = v;
+    }
+    // what the finishing wavefronts need, asked for before the barrier
+    const int n = n0 + 4 * grp, nc = min(n, g.N - 4);
+    const int m = m0 + min(wave, TN - 1) * 16 + li, mc = min(m, g.M - 1);
+    const float4 ws = *reinterpret_cast<const float4*>(g.w_scale + nc);
+    const float4 bias = *reinterpret_cast<const float4*>(g.bias + nc);
+    const float xs = g.x_scale[mc], ys = split_output_scale(g, xs);
+    const int64_t row = g.y_rowmap ? (int64_t)g.y_rowmap[mc] : (int64_t)mc;
+    __syncthreads();
+    if (wave >= TN || m >= g.M) return;
+    v4f v = part[0][wave][lane];
+#pragma unroll
+    for (int w = 1; w < W; ++w) v += part[w][wave][lane];
+    store_split_outputs(g, m, n, row, xs, ys, ws, bias, v);
+}
+
+template <class Tile>
+static void launch_split_tile(const SplitGemm& g, hipStream_t s)
+{
+    static bool raised[64] = {};
+    int dev = 0;
+    if (Tile::SMEM * 4 > 65536 && hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64 && !raised[dev])
+        raised[dev] = hipFuncSetAttribute((const void*)k_gemm_split<Tile>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                          Tile::SMEM * 4) == hipSuccess;
+    const int tn = ((g.y_split ? (int)plane_ld(g.N) : g.N) + Tile::kBM - 1) / Tile::kBM;
+    const int tm = (g.M + Tile::kBN - 1) / Tile::kBN, per_xcd = (tn * tm + 7) / 8;
+    hipLaunchKernelGGL(k_gemm_split<Tile>, dim3(per_xcd * 8), dim3(Tile::kThreads), Tile::SMEM * 4, s, g, tn, tm, per_xcd);
+}
+
+// Enough wavefronts and loads in flight that K is one or two batches: 32 stages
+// (K = 1024) on 8 wavefronts of 4; more on 8 of 7 for one block of rows (K =
+// 1600: 7.4 us, against 8.5 on 16 of 4), on 16 of 4 for two, whose registers
+// 7 would not leave room for.
+template <int TN>
+static void launch_split_few(const SplitGemm& g, hipStream_t s)
+{
+    const int n = g.y_split ? (int)plane_ld(g.N) : g.N;
+    const dim3 grid((n + 15) / 16, (g.M + 16 * TN - 1) / (16 * TN));
+    if (plane_ld(g.K) / 32 <= 32)
+        hipLaunchKernelGGL((k_gemm_split_few<TN, 8, 4>), grid, dim3(512), 0, s, g);
+    else if constexpr (TN == 1)
+        hipLaunchKernelGGL((k_gemm_split_few<TN, 8, 7>), grid, dim3(512), 0, s, g);
+    else
+        hipLaunchKernelGGL((k_gemm_split_few<TN, 16, 4>), grid, dim3(1024), 0, s, g);
+}
+
+// Which form: a launch ends with its slowest CU, so the largest tile of which
+// every CU still gets work, in whole rounds of what fits the chip (256 CUs of
+// 160 KB of LDS). 128 x 128 (64 KB, two on a CU) from 384 tiles: 416 tiles 75
+// us, against 85 on twice as many of 128 x 64. 128 x 64 (72 KB) while one round
+// holds them: 448 tiles 42 us against 51 on 64 x 64; 696 tiles, a second round,
+// 81 against 75. 64 x 64 with three slots (48 KB, three on a CU) where two on a
+// CU are not enough: 624 tiles 25 us against 28 with four slots, which are
+// better in one round: 400 tiles 27.5 against 28.6. Below 192 tiles halves of
+// 32 outputs: 76 tiles 17 us against 29 (two slots). Up to 32 rows the
+// workgroups that split K: 125 rows measured 22 us there against 16.
+void launch_gemm_split(const SplitGemm& g, hipStream_t s)
+{
+    if (g.M <= 0 || g.N <= 0) return;
+    constexpr int64_t kLarge = 384, kRound = 512, kSmall = 192;
+    auto tiles = [&](int bn, int bm) { return (int64_t)((g.N + bn - 1) / bn) * ((g.M + bm - 1) / bm); };
+    const int64_t wide = tiles(128, 64), t64 = tiles(64, 64);
+    if (g.M <= 16) launch_split_few<1>(g, s);
+    else if (g.M <= 32) launch_split_few<2>(g, s);
+    else if (tiles(128, 128) >= kLarge) launch_split_tile<MfmaTileF16x2<128, 128, 2, 2, 2>>(g, s);
+    else if (wide >= kLarge && wide <= kRound) launch_split_tile<MfmaTileF16x2<128, 64, 2, 2, 3>>(g, s);
+    else if (t64 > kRound) launch_split_tile<MfmaTileF16x2<64, 64, 2, 2, 3>>(g, s);
+    else if (t64 >= kSmall) launch_split_tile<MfmaTileF16x2<64, 64, 2, 2, 4>>(g, s);
+    else launch_split_tile<MfmaTileF16x2<32, 64, 2, 2, 4>>(g, s);
 }
 
 }  // namespace kgq

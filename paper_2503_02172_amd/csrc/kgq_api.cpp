@@ -42,6 +42,7 @@ struct Lane {
     float* xbuf = nullptr;        // BetaE MLP input / intersection input
     float* h1 = nullptr;
     float* h2 = nullptr;
+    float* row_scale[4]{};        // scales of the rows of xbuf, h1, h2, zmean in split form
     float* logits = nullptr;
     float* zfeat = nullptr;
     float* zmean = nullptr;
@@ -120,6 +121,14 @@ struct kgq_handle {
     // for the FP32-accurate bf16 matrix-core GEMM; the split is redone when a
     // weight is loaded
     std::map<const float*, uint16_t*> wplanes;
+    // BetaE, ConE, LogicE: the dense weights' rows in split form instead (the
+    // f16 matrix-core layers), with the bound of an output row's values
+    struct SplitWeight {
+        float* rows = nullptr;
+        float* scale = nullptr;
+        float* bound = nullptr;   // {largest row sum of magnitudes, largest bias or 0}
+    };
+    std::map<const float*, SplitWeight> wsplit;
     int dense_path = KGQ_DENSE_AUTO;
 
     // structure id -> compiled program: the built-ins for this model, then
@@ -331,8 +340,25 @@ void free_all(kgq_handle* h)
 // fields of k_pack_cone).
 int64_t qpack_row_floats(int model, int d)
 {
-    if (model == KGQ_BETAE) return plane_ld(2 * d);   // rows in split form end in whole stages
+    if (model == KGQ_BETAE && d >= kSplitDim) return plane_ld(2 * d);   // rows in split form end in whole stages
     return (int64_t)d * (model == KGQ_GQE ? 1 : model == KGQ_CONE ? 5 : 2);
+}
+
+// Floats of a row of `width` values that may be in split form (whole stages),
+// and of the widest dense-layer row.
+int64_t split_row_floats(int width) { return width >= kSplitDim ? plane_ld(width) : width; }
+int64_t mlp_row_floats(int d) { return d >= kSplitDim ? plane_ld(4 * d) : 4 * d; }
+
+// The dense-layer buffers that live in h2's rows: a layer's input x is dead
+// once its first layer has run, before h2 is written; an intersection writes no
+// h2, but its logits (after its x is dead) and ConE's gate (beside them). Their
+// scales likewise.
+void share_mlp_rows(Lane& L, int64_t m, int d)
+{
+    L.xbuf = L.h2;
+    L.logits = L.h2;
+    L.gate = L.h2 + m * d;
+    L.row_scale[2] = L.row_scale[0];
 }
 
 kgq_status allocate_all(kgq_handle* h)
@@ -370,22 +396,35 @@ kgq_status allocate_all(kgq_handle* h)
         ALLOC(h->ent_blk, n_pad * d + kEntPad);
         if (c.model == KGQ_Q2B) ALLOC(h->rel_o_sp, (int64_t)c.n_relations * d);
     }
-    // bf16 planes of every dense-layer weight whose K (its columns) the
-    // bf16 matrix-core GEMM takes, rows padded to whole 32-wide stages
+    // one piece of memory for a weight's split form: rows, scales, bound
+    auto split_weight = [&](const float* of, int64_t rows, int64_t cols) -> kgq_status {
+        if (d < kSplitDim) return KGQ_OK;
+        kgq_handle::SplitWeight w;
+        ALLOC(w.rows, rows * plane_ld(cols) + rows + 2);
+        w.scale = w.rows + rows * plane_ld(cols);
+        w.bound = w.scale + rows;
+        h->wsplit[of] = w;
+        return KGQ_OK;
+    };
+    // every dense-layer weight in the form its matrix-core path reads: split
+    // rows (BetaE, ConE, LogicE), or bf16 planes where K (its columns) is one
+    // the bf16 form takes, rows padded to whole 32-wide stages either way
     for (auto& kv : h->specs) {
         const std::string& n = kv.first;
         const bool weight = n.size() > 3 && n[n.size() - 3] == '.' && n[n.size() - 2] == 'w' &&
                             n.back() >= '1' && n.back() <= '3';
-        if (kv.second.entity || !weight || kv.second.cols % 4 != 0 || kv.second.cols < 32) continue;
+        if (kv.second.entity || !weight) continue;
+        if (mlp_model(c.model)) {
+            if ((n == "inter.axis.w1" || n == "inter.arg.w1") && h->int_cat_w) continue;   // (run stacked)
+            if ((s = split_weight(h->dparam.at(n), kv.second.rows, kv.second.cols)) != KGQ_OK) return s;
+            continue;
+        }
+        if (kv.second.cols % 4 != 0 || kv.second.cols < 32) continue;
         uint16_t* planes = nullptr;
         ALLOC(planes, 3 * kv.second.rows * plane_ld(kv.second.cols));
         h->wplanes[h->dparam.at(n)] = planes;
     }
-    if (h->int_cat_w && (2 * d) % 4 == 0 && 2 * d >= 32) {
-        uint16_t* planes = nullptr;
-        ALLOC(planes, 3 * 2 * d * plane_ld(2 * d));
-        h->wplanes[h->int_cat_w] = planes;
-    }
+    if (h->int_cat_w && (s = split_weight(h->int_cat_w, 2 * d, 2 * d)) != KGQ_OK) return s;
     h->bytes_params = h->bytes_total;   // everything after this is execute scratch
     const int n_lanes = c.concurrency > 0 ? c.concurrency : 1;
     for (int li = 0; li < n_lanes; ++li) {
@@ -394,13 +433,16 @@ kgq_status allocate_all(kgq_handle* h)
         ALLOC(L.states, h->cap_rows * W);
         const int64_t m_max = h->cap_mlp;   // rows of one MLP level / intersection stage inputs
         if (mlp_model(c.model)) {
-            ALLOC(L.xbuf, m_max * (c.model == KGQ_LOGICE ? 3 : 2) * d);
-            ALLOC(L.h1, m_max * 4 * d);
-            ALLOC(L.h2, m_max * 4 * d);
+            const int64_t ld4 = mlp_row_floats((int)d);
+            ALLOC(L.h1, m_max * ld4);
+            ALLOC(L.h2, m_max * ld4);
+            ALLOC(L.row_scale[0], m_max);
+            ALLOC(L.row_scale[1], m_max);
             if (c.model == KGQ_CONE) {
-                ALLOC(L.zmean, h->cap_groups * d);
-                ALLOC(L.gate, h->cap_groups * d);
+                ALLOC(L.zmean, h->cap_groups * split_row_floats((int)d));
+                ALLOC(L.row_scale[3], h->cap_groups);
             }
+            share_mlp_rows(L, m_max, (int)d);
         } else {
             ALLOC(L.h1, m_max * d);
             if (c.model == KGQ_Q2B) {
@@ -409,7 +451,7 @@ kgq_status allocate_all(kgq_handle* h)
                 ALLOC(L.gate, h->cap_groups * d);
             }
         }
-        ALLOC(L.logits, m_max * d);
+        if (!mlp_model(c.model)) ALLOC(L.logits, m_max * d);
         ALLOC(L.qpack, h->cap_score_rows * qpack_row_floats(c.model, (int)d) + kQpackPad);
         ALLOC(L.cq, h->cap_score_rows);
         ALLOC(L.q_scale, h->cap_score_rows);
@@ -617,6 +659,16 @@ kgq_status run_plan(kgq_handle* h, Lane& L, const Plan& p, const int32_t* P, con
         launch_gemm(g, s);
     };
 
+    // the f16 form of a layer: rows x in split form, weights named by `w`
+    const bool split_mlp = mlp_model(c.model) && d >= kSplitDim && h->dense_path != KGQ_DENSE_FP32;
+    auto split_gemm = [&](const float* x, int64_t ldx, const float* xs, const float* w, const float* bias, float* y,
+                          int64_t ldy, const int32_t* rowmap, SplitRows out, int M, int Nn, int K, int epi) {
+        const kgq_handle::SplitWeight& sw = h->wsplit.at(w);
+        launch_gemm_split({x, ldx, xs, sw.rows, sw.scale, bias, y, ldy, rowmap, out.rows, out.scale, sw.bound, M, Nn, K,
+                           epi, d}, s);
+    };
+    const SplitRows none;
+
     if (h->checked) {
         launch_clear_flag(L.dflag, s);
         launch_validate(anchors, rels, mixed ? P + p.off_arity : nullptr, p.B, sa, sr, fixed_na, fixed_nr,
@@ -640,38 +692,54 @@ kgq_status run_plan(kgq_handle* h, Lane& L, const Plan& p, const int32_t* P, con
             // projection at this stage and hop
             const int M = st.count;
             const int in_w = logice ? 3 * d : 2 * d;   // LogicE concatenates Rel[r] to the state
+            const SplitRows xs{split_mlp ? L.xbuf : nullptr, L.row_scale[0]};
+            const SplitRows h1s{split_mlp ? L.h1 : nullptr, L.row_scale[1]}, h2s{L.h2, L.row_scale[2]};
             if (st.table) {
                 // first hop from the anchors: the first layer is a gather
                 // from the precomputed tables
                 StageTimer t(h, 0, s);
                 launch_betae_proj1(P + st.b, P + st.c, M, anchors, rels, h->proj1_ent, h->proj1_rel, N, n_rel, 4 * d,
-                                   L.h1, L.dflag, s);
+                                   L.h1, h1s, L.dflag, s);
             } else {
                 {
                     StageTimer t(h, 0, s);
                     if (betae)
                         launch_betae_proj_prep(P + st.a, P + st.b, P + st.c, P + st.d, M, anchors, rels, L.states,
-                                               h->ent_rm, rel_ab, N, n_rel, d, L.xbuf, L.dflag, s);
+                                               h->ent_rm, rel_ab, N, n_rel, d, L.xbuf, xs, L.dflag, s);
                     else
                         launch_mlp_proj_prep(c.model, P + st.a, P + st.b, P + st.c, P + st.d, M, anchors, rels,
-                                             L.states, h->ent_rm, rel_ab, N, n_rel, d, L.xbuf, L.dflag, s);
+                                             L.states, h->ent_rm, rel_ab, N, n_rel, d, L.xbuf, xs, L.dflag, s);
                 }
                 StageTimer t(h, 1, s);
-                gemm({L.xbuf, in_w, param("proj.w1"), in_w, param("proj.b1"), L.h1, 4 * d, nullptr, M, 4 * d, in_w,
-                      EPI_RELU});
-            }
-            {
-                StageTimer t(h, 1, s);
-                gemm({L.h1, 4 * d, param("proj.w2"), 4 * d, param("proj.b2"), L.h2, 4 * d, nullptr, M, 4 * d, 4 * d,
-                      EPI_RELU});
+                if (split_mlp)
+                    split_gemm(L.xbuf, plane_ld(in_w), L.row_scale[0], param("proj.w1"), param("proj.b1"), nullptr, 0,
+                               nullptr, h1s, M, 4 * d, in_w, EPI_RELU);
+                else
+                    gemm({L.xbuf, in_w, param("proj.w1"), in_w, param("proj.b1"), L.h1, 4 * d, nullptr, M, 4 * d, in_w,
+                          EPI_RELU});
             }
             // the last layer writes the model's output map through the row map
-            GemmArgs g3{L.h2, 4 * d, param("proj.w3"), 4 * d, param("proj.b3"), L.states, 2 * d, P + st.e, M, 2 * d,
-                        4 * d, betae ? EPI_BETA_REG : cone ? EPI_CONE_ANGLES : EPI_SIGMOID};
-            g3.epi_split = d;
+            const int out_epi = betae ? EPI_BETA_REG : cone ? EPI_CONE_ANGLES : EPI_SIGMOID;
             {
                 StageTimer t(h, 1, s);
-                gemm(g3);
+                if (split_mlp)
+                    split_gemm(L.h1, plane_ld(4 * d), L.row_scale[1], param("proj.w2"), param("proj.b2"), nullptr, 0,
+                               nullptr, h2s, M, 4 * d, 4 * d, EPI_RELU);
+                else
+                    gemm({L.h1, 4 * d, param("proj.w2"), 4 * d, param("proj.b2"), L.h2, 4 * d, nullptr, M, 4 * d, 4 * d,
+                          EPI_RELU});
+            }
+            {
+                StageTimer t(h, 1, s);
+                if (split_mlp) {
+                    split_gemm(L.h2, plane_ld(4 * d), L.row_scale[2], param("proj.w3"), param("proj.b3"), L.states, 2 * d,
+                               P + st.e, none, M, 2 * d, 4 * d, out_epi);
+                } else {
+                    GemmArgs g3{L.h2, 4 * d, param("proj.w3"), 4 * d, param("proj.b3"), L.states, 2 * d, P + st.e, M, 2 * d,
+                                4 * d, out_epi};
+                    g3.epi_split = d;
+                    gemm(g3);
+                }
             }
             if (logice) {
                 StageTimer t(h, 0, s);
@@ -688,30 +756,48 @@ kgq_status run_plan(kgq_handle* h, Lane& L, const Plan& p, const int32_t* P, con
                 launch_logic_combine(c.tnorm, g, sin, d, L.states, s);
                 continue;
             }
+            const SplitRows xs{split_mlp ? L.xbuf : nullptr, L.row_scale[0]}, h1s{L.h1, L.row_scale[1]};
+            const int64_t ld2 = plane_ld(2 * d);
             if (cone) {
+                const SplitRows zs{L.zmean, L.row_scale[3]};
                 {
                     StageTimer t(h, 2, s);
-                    launch_cone_int_prep(g, sin, d, L.xbuf, s);
+                    launch_cone_int_prep(g, sin, d, L.xbuf, xs, s);
                 }
                 {
                     // both set functions' first layers, stacked: [attention | aperture] hidden
                     StageTimer t(h, 1, s);
-                    gemm({L.xbuf, 2 * d, h->int_cat_w, 2 * d, h->int_cat_b, L.h1, 2 * d, nullptr, n_in, 2 * d, 2 * d,
-                          EPI_RELU});
+                    if (split_mlp)
+                        split_gemm(L.xbuf, ld2, L.row_scale[0], h->int_cat_w, h->int_cat_b, nullptr, 0, nullptr, h1s, n_in,
+                                   2 * d, 2 * d, EPI_RELU);
+                    else
+                        gemm({L.xbuf, 2 * d, h->int_cat_w, 2 * d, h->int_cat_b, L.h1, 2 * d, nullptr, n_in, 2 * d, 2 * d,
+                              EPI_RELU});
                 }
                 {
+                    // (reads the first d columns; what follows them up to the
+                    // stage's end meets the weights' zero padding)
                     StageTimer t(h, 1, s);
-                    gemm({L.h1, 2 * d, param("inter.axis.w2"), d, param("inter.axis.b2"), L.logits, d, nullptr, n_in,
-                          d, d, EPI_NONE});
+                    if (split_mlp)
+                        split_gemm(L.h1, ld2, L.row_scale[1], param("inter.axis.w2"), param("inter.axis.b2"), L.logits, d,
+                                   nullptr, none, n_in, d, d, EPI_NONE);
+                    else
+                        gemm({L.h1, 2 * d, param("inter.axis.w2"), d, param("inter.axis.b2"), L.logits, d, nullptr, n_in,
+                              d, d, EPI_NONE});
                 }
                 {
                     StageTimer t(h, 2, s);
-                    launch_cone_combine_axis(g, sin, L.logits, L.h1, d, L.zmean, L.states, s);
+                    launch_cone_combine_axis(g, sin, L.logits, L.h1, split_mlp ? L.row_scale[1] : nullptr, d, L.zmean, zs,
+                                             L.states, s);
                 }
                 {
                     StageTimer t(h, 1, s);
-                    gemm({L.zmean, d, param("inter.arg.w2"), d, param("inter.arg.b2"), L.gate, d, nullptr, st.count,
-                          d, d, EPI_NONE});
+                    if (split_mlp)
+                        split_gemm(L.zmean, plane_ld(d), L.row_scale[3], param("inter.arg.w2"), param("inter.arg.b2"),
+                                   L.gate, d, nullptr, none, st.count, d, d, EPI_NONE);
+                    else
+                        gemm({L.zmean, d, param("inter.arg.w2"), d, param("inter.arg.b2"), L.gate, d, nullptr, st.count,
+                              d, d, EPI_NONE});
                 }
                 StageTimer t(h, 2, s);
                 launch_cone_combine_arg(g, sin, L.gate, d, L.states, s);
@@ -720,20 +806,28 @@ kgq_status run_plan(kgq_handle* h, Lane& L, const Plan& p, const int32_t* P, con
             if (betae) {
                 {
                     StageTimer t(h, 2, s);
-                    launch_betae_int_prep(g, sin, d, L.xbuf, s);
+                    launch_betae_int_prep(g, sin, d, L.xbuf, xs, s);
                 }
                 {
                     StageTimer t(h, 1, s);
-                    gemm({L.xbuf, 2 * d, param("inter.w1"), 2 * d, param("inter.b1"), L.h1, 2 * d, nullptr, n_in,
-                          2 * d, 2 * d, EPI_RELU});
+                    if (split_mlp)
+                        split_gemm(L.xbuf, ld2, L.row_scale[0], param("inter.w1"), param("inter.b1"), nullptr, 0, nullptr,
+                                   h1s, n_in, 2 * d, 2 * d, EPI_RELU);
+                    else
+                        gemm({L.xbuf, 2 * d, param("inter.w1"), 2 * d, param("inter.b1"), L.h1, 2 * d, nullptr, n_in,
+                              2 * d, 2 * d, EPI_RELU});
                 }
                 {
                     StageTimer t(h, 1, s);
-                    gemm({L.h1, 2 * d, param("inter.w2"), 2 * d, param("inter.b2"), L.logits, d, nullptr, n_in, d,
-                          2 * d, EPI_NONE});
+                    if (split_mlp)
+                        split_gemm(L.h1, ld2, L.row_scale[1], param("inter.w2"), param("inter.b2"), L.logits, d, nullptr,
+                                   none, n_in, d, 2 * d, EPI_NONE);
+                    else
+                        gemm({L.h1, 2 * d, param("inter.w2"), 2 * d, param("inter.b2"), L.logits, d, nullptr, n_in, d,
+                              2 * d, EPI_NONE});
                 }
                 StageTimer t(h, 2, s);
-                launch_betae_combine(g, L.xbuf, L.logits, d, L.states, s);
+                launch_betae_combine(g, sin, L.logits, d, L.states, s);
                 continue;
             }
             {
@@ -768,11 +862,10 @@ kgq_status run_plan(kgq_handle* h, Lane& L, const Plan& p, const int32_t* P, con
         }
     }
 
-    const int tq = score_row_pad(c.model);
-    const int n_rows_pad = ((p.n_score_rows + tq - 1) / tq) * tq;
+    const int n_rows_pad = packed_rows(c.model, p.n_score_rows);
     const int d_score = logice ? 2 * d : d;    // LogicE scores its 2d bound coordinates as one vector
     // BetaE: query and entity rows in split form on the f16 matrix cores
-    const bool split = betae && h->dense_path != KGQ_DENSE_FP32 &&
+    const bool split = betae && d >= kSplitDim && h->dense_path != KGQ_DENSE_FP32 &&
                        score_kl_takes_split(p.n_score_rows, N, h->dense_path == KGQ_DENSE_BF16X3);
     {
         StageTimer t(h, 3, s);
@@ -880,18 +973,25 @@ int64_t carve_scratch(const kgq_handle* h, const Plan& p, int32_t k, bool need_s
         off += std::max<int64_t>(bytes, 16);
         return q;
     };
+    // the packed rows first: the scorer reads up to kQpackPad floats past them,
+    // which the pieces behind hold
+    const int64_t srows = packed_rows(c.model, p.n_score_rows);
+    V.qpack = reinterpret_cast<float*>(take(srows * qpack_row_floats(c.model, (int)d) * 4));
     *plan_dev = reinterpret_cast<int32_t*>(take((int64_t)p.image.size() * 4));
     V.dflag = reinterpret_cast<int*>(take(sizeof(int)));
     V.states = reinterpret_cast<float*>(take((int64_t)p.n_state_rows * W * 4));
     const int64_t m = std::max(p.max_level, p.max_and_in), groups = p.max_and_groups;
     if (mlp_model(c.model)) {
-        V.xbuf = reinterpret_cast<float*>(take(m * (c.model == KGQ_LOGICE ? 3 : 2) * d * 4));
-        V.h1 = reinterpret_cast<float*>(take(m * 4 * d * 4));
-        V.h2 = reinterpret_cast<float*>(take(m * 4 * d * 4));
+        const int64_t ld4 = mlp_row_floats((int)d);
+        V.h1 = reinterpret_cast<float*>(take(m * ld4 * 4));
+        V.h2 = reinterpret_cast<float*>(take(m * ld4 * 4));
+        V.row_scale[0] = reinterpret_cast<float*>(take(m * 4));
+        V.row_scale[1] = reinterpret_cast<float*>(take(m * 4));
         if (c.model == KGQ_CONE) {
-            V.zmean = reinterpret_cast<float*>(take(groups * d * 4));
-            V.gate = reinterpret_cast<float*>(take(groups * d * 4));
+            V.zmean = reinterpret_cast<float*>(take(groups * split_row_floats((int)d) * 4));
+            V.row_scale[3] = reinterpret_cast<float*>(take(groups * 4));
         }
+        share_mlp_rows(V, m, (int)d);
     } else {
         V.h1 = reinterpret_cast<float*>(take(m * d * 4));
         if (c.model == KGQ_Q2B) {
@@ -900,12 +1000,9 @@ int64_t carve_scratch(const kgq_handle* h, const Plan& p, int32_t k, bool need_s
             V.gate = reinterpret_cast<float*>(take(groups * d * 4));
         }
     }
-    V.logits = reinterpret_cast<float*>(take(m * d * 4));
-    const int tq = score_row_pad(c.model);
-    const int64_t srows = ((int64_t)(p.n_score_rows + tq - 1) / tq) * tq;
-    V.qpack = reinterpret_cast<float*>(take((srows * qpack_row_floats(c.model, (int)d) + kQpackPad) * 4));
+    if (!mlp_model(c.model)) V.logits = reinterpret_cast<float*>(take(m * d * 4));
     V.cq = reinterpret_cast<double*>(take(srows * 8));
-    V.q_scale = reinterpret_cast<float*>(take(srows * 4));
+    if (c.model == KGQ_BETAE) V.q_scale = reinterpret_cast<float*>(take(srows * 4));
     V.scores = need_scores ? reinterpret_cast<float*>(take(B * N * 4)) : nullptr;
     const int64_t ncand = need_topk ? topk_scratch_elems(B, N, k) : 0;
     for (int i = 0; i < 2; ++i) {
@@ -1292,16 +1389,23 @@ kgq_status kgq_load_params(kgq_handle* h, const char* name, const void* src, siz
             HIP_TRY(h, hipGetLastError());
             HIP_TRY(h, hipStreamSynchronize(nullptr));
         }
-        auto split = [&](const float* w, int64_t rows, int64_t cols) -> kgq_status {
+        auto split = [&](const float* w, int64_t rows, int64_t cols) {
             auto pl = h->wplanes.find(w);
-            if (pl == h->wplanes.end()) return KGQ_OK;
-            launch_split_planes(w, pl->second, rows, cols, nullptr);
-            HIP_TRY(h, hipGetLastError());
-            HIP_TRY(h, hipStreamSynchronize(nullptr));
-            return KGQ_OK;
+            auto sw = h->wsplit.find(w);
+            if (pl != h->wplanes.end()) launch_split_planes(w, pl->second, rows, cols, nullptr);
+            if (sw != h->wsplit.end())
+                launch_split_rows(w, rows, cols, cols, sw->second.rows, sw->second.scale, sw->second.bound, nullptr);
         };
-        kgq_status st = split(dst, ps.rows, ps.cols);
-        if (st != KGQ_OK) return st;
+        split(dst, ps.rows, ps.cols);
+        // a bias: its largest value, for its weight's bound (".b1" -> ".w1")
+        std::string wname = name;
+        const size_t dot = wname.rfind(".b");
+        if (dot != std::string::npos) wname[dot + 1] = 'w';
+        auto bound_of_bias = [&](const float* w, const float* b, int64_t n) {
+            auto sw = h->wsplit.find(w);
+            if (sw != h->wsplit.end()) launch_bias_max(b, n, sw->second.bound + 1, nullptr);
+        };
+        if (dot != std::string::npos && h->dparam.count(wname)) bound_of_bias(h->dparam.at(wname), dst, ps.cols);
         if (c.model == KGQ_CONE) {
             // the two set functions' first layers, stacked for one GEMM
             const size_t half_w = (size_t)2 * c.dim * c.dim, half_b = (size_t)c.dim;
@@ -1309,12 +1413,16 @@ kgq_status kgq_load_params(kgq_handle* h, const char* name, const void* src, siz
             if (!std::strcmp(name, "inter.arg.w1"))
                 HIP_TRY(h, hipMemcpy(h->int_cat_w + half_w, dst, nbytes, hipMemcpyDeviceToDevice));
             if (!std::strcmp(name, "inter.axis.w1") || !std::strcmp(name, "inter.arg.w1"))
-                if ((st = split(h->int_cat_w, 2 * (int64_t)c.dim, 2 * (int64_t)c.dim)) != KGQ_OK) return st;
+                split(h->int_cat_w, 2 * (int64_t)c.dim, 2 * (int64_t)c.dim);
             if (!std::strcmp(name, "inter.axis.b1")) HIP_TRY(h, hipMemcpy(h->int_cat_b, dst, nbytes, hipMemcpyDeviceToDevice));
             if (!std::strcmp(name, "inter.arg.b1"))
                 HIP_TRY(h, hipMemcpy(h->int_cat_b + half_b, dst, nbytes, hipMemcpyDeviceToDevice));
+            if (!std::strcmp(name, "inter.axis.b1") || !std::strcmp(name, "inter.arg.b1"))
+                bound_of_bias(h->int_cat_w, h->int_cat_b, 2 * (int64_t)c.dim);
             if (!std::strcmp(name, "modulus")) HIP_TRY(h, hipMemcpy(&h->cone_modulus, dst, sizeof(float), hipMemcpyDeviceToHost));
         }
+        HIP_TRY(h, hipGetLastError());
+        HIP_TRY(h, hipStreamSynchronize(nullptr));
         h->loaded[name] = true;
         if (mlp_model(c.model) && (!std::strcmp(name, "relation") || !std::strcmp(name, "proj.w1") ||
                                    !std::strcmp(name, "proj.b1")))
@@ -1332,7 +1440,7 @@ kgq_status kgq_load_params(kgq_handle* h, const char* name, const void* src, siz
             launch_betae_entity_prep(stage, bf16, c.n_entities, c.dim, h->n_blocks, h->ent_rm, h->ent_blk,
                                      h->ent_const, nullptr);
             launch_split_rows(h->ent_blk, h->n_blocks * kEntBlock, 2 * (int64_t)c.dim, 2 * (int64_t)c.dim, h->ent_split,
-                              h->ent_scale, nullptr);
+                              h->ent_scale, nullptr, nullptr);
         }
         else if (c.model == KGQ_CONE)
             launch_cone_entity_prep(static_cast<const float*>(stage), c.n_entities, c.dim, h->n_blocks, h->ent_rm,

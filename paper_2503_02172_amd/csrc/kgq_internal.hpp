@@ -32,7 +32,9 @@ constexpr int kTqGqe = 24;
 constexpr int kTqQ2b = 12;
 constexpr int kTqCone = 8;
 // BetaE query rows are packed row-major [row][alpha (d) | beta (d)], not
-// padded (the matrix-core scorer reads rows past the last from it).
+// padded (the matrix-core scorer reads rows past the last from it); the
+// scratch holds them in multiples of this.
+constexpr int kRowGrainBetae = 128;
 
 // The VALU scorers read up to two dimension steps past the last block of the
 // entity table and one past the last block of packed rows: floats allocated
@@ -43,14 +45,14 @@ constexpr int kQpackPad = 64;
 // LogicE scores with GQE's L1 kernel over its 2d bound coordinates.
 inline int valu_form(int model) { return model == KGQ_LOGICE ? KGQ_GQE : model; }
 
-// Scored rows are padded to a multiple of this per model.
+// The scratch holds scored rows in multiples of this per model.
 inline int score_row_pad(int model)
 {
     switch (valu_form(model)) {
     case KGQ_GQE: return kTqGqe;
     case KGQ_Q2B: return kTqQ2b;
     case KGQ_CONE: return kTqCone;
-    default: return 1;
+    default: return kRowGrainBetae;
     }
 }
 
@@ -97,6 +99,14 @@ __device__ __forceinline__ uint32_t l1_fixed_bits(float x, const L1Fixed& f, dou
     const float c = fminf(fmaxf(x, f.lo), f.hi);
     excess += fabs((double)x - (double)c);             // NaN and infinities pass through here
     return 0x4B000000u + (uint32_t)__double2uint_rn(((double)c - (double)f.lo) * inv_quantum);
+}
+
+// Rows that the pack writes: a whole number of the VALU scorers' row blocks.
+inline int packed_rows(int model, int n_rows)
+{
+    if (model == KGQ_BETAE) return n_rows;
+    const int tq = score_tq(model, n_rows);
+    return (n_rows + tq - 1) / tq * tq;
 }
 
 // Models whose projection is an MLP (one dense-layer pass per hop) and that
@@ -151,8 +161,38 @@ void launch_split_planes(const float* w, uint16_t* p, int64_t rows, int64_t cols
 
 // Rows of w [rows x cols] (row stride ld) in the split form of the f16
 // matrix-core tile (mfma_tile.hpp): dst row stride plane_ld(cols) words, zeros
-// past cols, and each row's scale.
-void launch_split_rows(const float* w, int64_t rows, int64_t cols, int64_t ld, float* dst, float* scale, hipStream_t s);
+// past cols, and each row's scale. norm (or nullptr): the largest row sum of
+// magnitudes.
+void launch_split_rows(const float* w, int64_t rows, int64_t cols, int64_t ld, float* dst, float* scale, float* norm,
+                       hipStream_t s);
+// The largest of b[0 .. n) and 0.
+void launch_bias_max(const float* b, int64_t n, float* out, hipStream_t s);
+
+// A dense layer on rows in split form: y[m] = epi(W x[m] + b), float32 rows
+// through the row map, or (y_split) rows in split form again for the next
+// layer (EPI_RELU only). Their scale follows from a bound of the row's values,
+// the largest |x| times the weights' largest row sum plus the largest b, so no
+// row has to be complete before it is written; a bound 2^k above the row's
+// largest value takes k of the 28 binades that the form holds to 2^-23.
+struct SplitGemm {
+    const float* x; int64_t ldx; const float* x_scale;       // [M], stride ldx words >= plane_ld(K)
+    const float* w; const float* w_scale;                     // [N], stride plane_ld(K)
+    const float* bias;
+    float* y; int64_t ldy; const int32_t* y_rowmap;           // float32 output, or
+    float* y_split; float* y_scale; const float* bound;       // split output (stride plane_ld(N)); {norm of w, max(b, 0)}
+    int M, N, K, epi, epi_split;
+};
+void launch_gemm_split(const SplitGemm& g, hipStream_t s);
+// Rows in split form, where a kernel that makes layer inputs is to write them
+// so (rows == nullptr: as float32).
+struct SplitRows {
+    float* rows = nullptr;
+    float* scale = nullptr;
+};
+
+// Embedding dimensions from which the split forms are used: below, rows padded
+// to whole stages hold more padding than values.
+constexpr int kSplitDim = 16;
 
 // Epilogue value of output column n.
 __device__ __forceinline__ float apply_epilogue(int epi, int split, int n, float v)
@@ -189,7 +229,7 @@ void launch_softplus(const float* src, float* dst, int64_t n, hipStream_t s);
 // (rows of width w = 4d). Ids are range-checked like the other gathers.
 void launch_betae_proj1(const int32_t* anchor_ref, const int32_t* rel_ref, int M, const int32_t* anchors,
                         const int32_t* rels, const float* pe, const float* pr, int64_t n_ent, int n_rel, int w,
-                        float* h1, int* flag, hipStream_t s);
+                        float* h1, SplitRows split, int* flag, hipStream_t s);
 
 void launch_clear_flag(int* flag, hipStream_t s);
 
@@ -232,10 +272,11 @@ void launch_combine_offset(const GroupArgs& g, const float* states, int W, const
                            float* out_states, int* flag, hipStream_t s);
 
 // BetaE: intersection inputs (reciprocal where the branch is negated).
-void launch_betae_int_prep(const GroupArgs& g, const float* states, int d, float* x_int,
+void launch_betae_int_prep(const GroupArgs& g, const float* states, int d, float* x_int, SplitRows split,
                            hipStream_t s);
-// BetaE: attention-weighted alpha/beta over branches.
-void launch_betae_combine(const GroupArgs& g, const float* x_int, const float* logits, int d,
+// BetaE: attention-weighted alpha/beta over branches (sin: the stage's input
+// rows, negated ones inverted here).
+void launch_betae_combine(const GroupArgs& g, const float* sin, const float* logits, int d,
                           float* states, hipStream_t s);
 // BetaE projection input rows x = base + Rel[r] (base = a state row, or an
 // anchor entity when src_row < 0; its reciprocal where neg[m] != 0, neg may
@@ -243,7 +284,7 @@ void launch_betae_combine(const GroupArgs& g, const float* x_int, const float* l
 void launch_betae_proj_prep(const int32_t* src_row, const int32_t* anchor_ref, const int32_t* rel_ref,
                             const int32_t* neg, int M, const int32_t* anchors, const int32_t* rels,
                             const float* states, const float* ent_ab, const float* rel,
-                            int64_t n_ent, int n_rel, int d, float* x, int* flag, hipStream_t s);
+                            int64_t n_ent, int n_rel, int d, float* x, SplitRows split, int* flag, hipStream_t s);
 
 // Pack scored rows in fixed point for the L1 scorer's integer form
 // ([row_block][k][TQ] words), and each row's base: gamma minus dist_scale
@@ -268,12 +309,16 @@ void launch_cone_entity_prep(const float* src, int64_t N, int d, int64_t n_block
 void launch_mlp_proj_prep(int model, const int32_t* src_row, const int32_t* anchor_ref, const int32_t* rel_ref,
                           const int32_t* neg, int M, const int32_t* anchors, const int32_t* rels,
                           const float* states, const float* ent_rm, const float* rel, int64_t n_ent, int n_rel,
-                          int d, float* x, int* flag, hipStream_t s);
+                          int d, float* x, SplitRows split, int* flag, hipStream_t s);
 // LogicE: u = l + s (1 - l) in the destination rows of a projection level.
 void launch_logic_bounds(const int32_t* rowmap, int M, int d, float* states, hipStream_t s);
-void launch_cone_int_prep(const GroupArgs& g, const float* states, int d, float* x_int, hipStream_t s);
-void launch_cone_combine_axis(const GroupArgs& g, const float* states, const float* logits, const float* hid, int d,
-                              float* zmean, float* out_states, hipStream_t s);
+void launch_cone_int_prep(const GroupArgs& g, const float* states, int d, float* x_int, SplitRows split,
+                          hipStream_t s);
+// hid: the stacked first layer's output, float32 [2d] rows, or (hid_scale)
+// rows in split form; the mean goes to zmean or zsplit.
+void launch_cone_combine_axis(const GroupArgs& g, const float* states, const float* logits, const float* hid,
+                              const float* hid_scale, int d, float* zmean, SplitRows zsplit, float* out_states,
+                              hipStream_t s);
 void launch_cone_combine_arg(const GroupArgs& g, const float* states, const float* gate, int d, float* out_states,
                              hipStream_t s);
 void launch_logic_combine(int tnorm, const GroupArgs& g, const float* states, int d, float* out_states,

@@ -569,11 +569,12 @@ typedef _Float16 v4h __attribute__((ext_vector_type(4)));
 constexpr float kSplitLow = 1.0f / 2048.0f;       // weight of the low part
 
 // Scale of a row whose largest magnitude is m (a power of two, its reciprocal
-// finite; 1 for a row of zeros or with a value that is not finite).
+// finite; 2^-100 for a row of zeros, 1 for one with a value that is not finite).
 __device__ __forceinline__ float split_scale(float m)
 {
     const int e = (int)(__float_as_uint(m) >> 23 & 255u);
-    if (e == 0 || e == 255) return 1.0f;
+    if (e == 0) return 0x1p-100f;
+    if (e == 255) return 1.0f;
     return __uint_as_float((uint32_t)max(e - 14, 1) << 23);
 }
 __device__ __forceinline__ float split_inverse(float s) { return __uint_as_float(0x7F000000u - __float_as_uint(s)); }
@@ -599,15 +600,53 @@ __device__ __forceinline__ void store_split8(float* dst, const float (&x)[8], fl
     reinterpret_cast<v8h*>(dst)[1] = l;
 }
 
+// One row by one wavefront: f(c, x) gives chunk c's 8 values (zeros past the
+// row's end); writes the row's n8 chunks at dst and its scale. Up to 256 chunks
+// are held in registers between the maximum and the store, later ones asked
+// for twice.
+template <typename F>
+__device__ __forceinline__ void split_row_wave(F f, int n8, float* dst, float* scale, int lane)
+{
+    float v[4][8], m = 0.f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        if (lane + 64 * u < n8) f(lane + 64 * u, v[u]);
+        else
+#pragma unroll
+            for (int t = 0; t < 8; ++t) v[u][t] = 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) m = fmaxf(m, fabsf(v[u][t]));
+    for (int c = lane + 256; c < n8; c += 64) {
+        float x[8];
+        f(c, x);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) m = fmaxf(m, fabsf(x[t]));
+    }
+    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+    const float sc = split_scale(m), inv = split_inverse(sc);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (lane + 64 * u < n8) store_split8(dst + (lane + 64 * u) * 8, v[u], inv);
+    for (int c = lane + 256; c < n8; c += 64) {
+        float x[8];
+        f(c, x);
+        store_split8(dst + c * 8, x, inv);
+    }
+    if (lane == 0) *scale = sc;
+}
+
 // Tiles: WM x WN wavefronts, each with (BM / WM / 16) x (BN / WN / 16) blocks
-// of 16 x 16, two accumulators a block. Stages of 32 of K go through a
-// two-slot LDS ring by direct-to-LDS loads; both operands' rows are 128 bytes a
+// of 16 x 16, two accumulators a block. Stages of 32 of K go through an
+// S-slot LDS ring by direct-to-LDS loads, S - 1 stages ahead; both operands' rows are 128 bytes a
 // stage, 16-byte pieces XOR-swizzled by row as in the bf16 form, and fragments
 // are read as they are: no split work in the loop. Lane l holds the output
 // rows 4 (l / 16) .. + 3 of column l % 16 of each block. A stage: wait until it
 // has landed, barrier (every wavefront has read the one before, whose slot is
 // free), fragments, the next stage's loads, products.
-template <int BM, int BN, int WM, int WN>
+template <int BM, int BN, int WM, int WN, int S = 2>
 struct MfmaTileF16x2 {
     static constexpr int kBM = BM, kBN = BN, kThreads = 64 * WM * WN;
     static constexpr bool kSplit = true;
@@ -615,8 +654,10 @@ struct MfmaTileF16x2 {
     static constexpr int ABYTES = BM * ROW, STAGE = (BM + BN) * ROW;
     static constexpr int TM = BM / WM / 16, TN = BN / WN / 16;
     static constexpr int AI = BM / 8 / (WM * WN), BI = BN / 8 / (WM * WN);    // load instructions a wavefront and stage
-    static constexpr int SMEM = 2 * STAGE / 4;         // floats
-    static_assert(TM >= 1 && TN >= 1 && AI >= 1 && BI >= 1, "tile shape");
+    static constexpr int LPS = AI + BI;
+    static constexpr int kSlots = S;
+    static constexpr int SMEM = S * STAGE / 4;         // floats
+    static_assert(TM >= 1 && TN >= 1 && AI >= 1 && BI >= 1 && (S - 2) * LPS < 64, "tile shape");
     __device__ static int swz(int row) { return (row & 7) ^ ((row >> 3) & 1); }
 
     // Loads of one tile's stages. Rows past M or N are read from the last one.

@@ -172,3 +172,22 @@ def test_gpu_betae_split_scorer(structure, n_ent, d, B, wide):
     assert np.all(np.abs(got - ref) <= 2.0 ** -20 * big + w.rtol * np.maximum(np.abs(ref), w.gamma)), \
         (np.abs(got - ref) / big).max() * 2 ** 20
     check_topk(idx, val, got, 5, 0.0, w.gamma, structure)
+
+
+@pytest.mark.parametrize("model", [O.BETAE, O.CONE, O.LOGICE], ids=["betae", "cone", "logice"])
+@pytest.mark.parametrize("structure,d,B", [("2p", 16, 1), ("pni", 20, 16), ("2p", 36, 17), ("pni", 52, 32),
+                                           ("pni", 36, 33), ("2p", 268, 32), ("2p", 52, 129), ("2p", 400, 512),
+                                           ("2p", 400, 1990), ("2p", 128, 4100), ("2p", 128, 12289)])
+def test_gpu_split_layers(model, structure, d, B):
+    """Dense layers on rows in split form: every tile form (16 and 32 rows,
+    one and two batches of K, the five tile shapes) at its edges, widths that
+    end inside a 32-wide stage and outputs that end inside a tile. The layers'
+    error (2^-21 of the sum of magnitudes, then float32 results) is inside the
+    model's own score tolerance, which float32 layers have to meet too."""
+    w = synth.make_tiny(model, n_ent=70, n_rel=7, dim=d, seed=111)
+    qb = synth.draw_queries(structure, B, 70, 7, seed=112)
+    out = _scores(w, model, structure, qb, 5)
+    kw = {"center_reg": w.center_reg} if model == O.CONE else {}
+    ref = O.Model(model, w.params, w.gamma, **kw).scores(S[structure], qb.anchors, qb.relations)
+    check_scores(out["scores"], ref, w.rtol, w.gamma, structure)
+    check_topk(out["idx"], out["score"], ref, 5, w.rtol, w.gamma, structure)
