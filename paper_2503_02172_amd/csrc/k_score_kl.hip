@@ -16,14 +16,15 @@
 // both operands split ahead into two f16 parts and scaled by row (the entity
 // rows at load, the query rows by the pack kernel) and three part products
 // kept (MfmaTileF16x2, tiles of 128 entities x 128 query rows, 64 KiB of LDS,
-// two workgroups per compute unit): k_score_kl_split. All its terms are
-// positive, and its error against 64 bits is that of the 32-bit sum. At the
-// 63,361-entity workload it took the scorer from 1.21 ms (three bf16 parts,
-// six products, the query rows split in the loop) to 0.69 ms.
-// Small calls, and KGQ_DENSE_FP32: 64-row x 64-entity tiles on
-// v_mfma_f32_16x16x4_f32 with full FP32 inputs, through the direct-to-LDS
-// ring of three stages when 2d is a multiple of 16, else the register-staged
-// loop. Its epilogue adds C_q + E_e in double precision, stages the output
+// two workgroups per compute unit; smaller ones for small calls):
+// k_score_kl_split. All its terms are positive, and its error against 64 bits
+// is that of the 32-bit sum. At the 63,361-entity workload it took the scorer
+// from 1.21 ms (three bf16 parts, six products, the query rows split in the
+// loop) to 0.69 ms; 61 queries at 14,505 entities from 25.8 us to 14.2.
+// The smallest calls, below 16 dimensions, and KGQ_DENSE_FP32: tiles of 64 or
+// 32 rows x 64 entities on v_mfma_f32_16x16x4_f32 with full FP32 inputs,
+// through the direct-to-LDS ring of three stages when 2d is a multiple of 16,
+// else the register-staged loop. Its epilogue adds C_q + E_e in double precision, stages the output
 // tile in LDS, takes the max over union groups of four and pairs of rows and
 // writes each output row with 16-byte non-temporal stores.
 // The split kernel also writes, per output row and chunk of 64 entities, the
@@ -189,9 +190,7 @@ __global__ __launch_bounds__(Tile::kThreads, 2) void k_score_kl_split(ScoreArgs 
     const int n_mine = min(per_xcd, total - xcd0), n_wg = gridDim.x >> 3;
     const int64_t ld = plane_ld(2 * a.d);
     const int nk = (int)(ld / 32);
-    typename Tile::Loader loader;
-    int e0 = 0, q0 = 0;
-    auto locate = [&](int p) {
+    auto locate = [&](int p, int& e0, int& q0) {
         const int L = xcd0 + p;
         const int chunk_wg = qchunk * n_et;
         const int c = L / chunk_wg;
@@ -200,31 +199,48 @@ __global__ __launch_bounds__(Tile::kThreads, 2) void k_score_kl_split(ScoreArgs 
         const int et = r / qcc;
         e0 = et * BE;
         q0 = (c * qchunk + (r - et * qcc)) * BQ;
-        loader.set(a.ent_split, ld, (int)(a.n_blocks * kEntBlock), a.qpack, ld, a.n_rows, e0, q0);
     };
-    int pos = blockIdx.x >> 3, slot = 0;
+    int pos = blockIdx.x >> 3;
     if (pos >= n_mine) return;
-    locate(pos);
-    loader.issue(0, sm, slot);
+    // the ring's requests run S - 1 stages ahead of the products, over the ends
+    // of tiles: the next stage to ask for, its tile and slot
+    constexpr int S = Tile::kSlots;
+    typename Tile::Loader loader;
+    int ipos = pos, ikt = 0, islot = 0;
+    auto request = [&] {
+        if (ipos >= n_mine) return;
+        if (ikt == 0) {
+            int e0, q0;
+            locate(ipos, e0, q0);
+            loader.set(a.ent_split, ld, (int)(a.n_blocks * kEntBlock), a.qpack, ld, a.n_rows, e0, q0);
+        }
+        loader.issue(ikt, sm, islot);
+        islot = islot + 1 == S ? 0 : islot + 1;
+        if (++ikt == nk) {
+            ikt = 0;
+            ipos += n_wg;
+        }
+    };
+    int slot = 0;
+#pragma unroll
+    for (int t = 0; t < S - 1; ++t) request();
     wait_vm_barrier<0>();
     for (;;) {
         v4f acc[Tile::TM][Tile::TN], low[Tile::TM][Tile::TN];
         Tile::clear(acc, low);
-        const int te0 = e0, tq0 = q0;              // this tile; the next one's from the last stage on
-        const bool more = pos + n_wg < n_mine;
+        int te0, tq0;
+        locate(pos, te0, tq0);
         for (int kt = 0; kt < nk; ++kt) {
-            if (kt > 0) wait_vm_barrier<0>();      // (the first stage landed before the loop or the last stores)
-            Tile::stage(sm, slot, acc, low, [&] {
-                if (kt + 1 < nk) {
-                    loader.issue(kt + 1, sm, slot ^ 1);
-                } else if (more) {
-                    locate(pos + n_wg);
-                    loader.issue(0, sm, slot ^ 1);
-                }
-            });
-            slot ^= 1;
+            // (a tile's first stage landed before the loop or the last stores)
+            if (kt > 0) {
+                if (S > 2 && ipos < n_mine) wait_vm_barrier<(S - 2) * Tile::LPS>();   // S - 2 later stages asked for
+                else wait_vm_barrier<0>();
+            }
+            Tile::stage(sm, slot, acc, low, request);
+            slot = slot + 1 == S ? 0 : slot + 1;
         }
         pos += n_wg;
+        const bool more = pos < n_mine;
 
         // The lane's query rows (one per block column; past the last: the last's
         // constants, nothing stored) and entities (the table's constants are
@@ -351,8 +367,10 @@ static void launch_split(const ScoreArgs& a, hipStream_t s)
     const int total = n_qt * n_et, per_xcd = (total + 7) / 8;
     static bool raised[64] = {};
     raise_lds(k_score_kl_split<Tile>, Tile::SMEM * 4, raised);
-    const int n_wg = std::min(per_xcd, 64);    // per XCD: two on each of 32 compute units
-    hipLaunchKernelGGL((k_score_kl_split<Tile>), dim3(n_wg * 8), dim3(Tile::kThreads), Tile::SMEM * 4, s, a, n_qt, n_et, tile_chunk(n_qt, Tile::kBN, plane_ld(2 * a.d)), total, per_xcd);
+    // per XCD: as many as LDS takes on each of 32 compute units (160 KB), at most 4
+    const int n_wg = std::min(per_xcd, 32 * std::min(4, 163840 / (Tile::SMEM * 4)));
+    hipLaunchKernelGGL((k_score_kl_split<Tile>), dim3(n_wg * 8), dim3(Tile::kThreads), Tile::SMEM * 4, s, a, n_qt, n_et,
+                       tile_chunk(n_qt, Tile::kBN, plane_ld(2 * a.d)), total, per_xcd);
 }
 
 template <class Tile>
@@ -370,34 +388,51 @@ static void launch_tiles(const ScoreArgs& a, hipStream_t s)
                        tile_chunk(n_mt, BM, 2 * a.d), total, per_xcd);
 }
 
-// The split form from more than one FP32 tile (64 x 64) per compute unit on:
-// below, its tiles of 128 x 128 leave most of the chip idle. One 1p query: 80
-// us a call split and 75 FP32 at 14,505 entities (227 tiles), 106 and 126 at
-// 63,361 (990); 96 rows at 14,505 (454 tiles): 91 and 98; 192 rows at 3,000
-// (141 tiles): 87 and 81.
+// The split form from more than one FP32 tile (64 x 64) per compute unit on.
+// Below, the FP32 tiles take about as long (one query at 14,505 entities 13.8
+// us against 12.8, 64 at 3,000 13.2 against 13.0).
 bool score_kl_takes_split(int n_rows, int64_t N, bool always)
 {
     return always || (int64_t)((n_rows + 63) / 64) * ((N + 63) / 64) > 256;
 }
 
+// FP32 tiles on the direct-to-LDS ring: 64 x 64, or 32 rows as long as every
+// tile has a compute unit to itself, whose chain of products is the time (one
+// query at 14,505 entities 21.2 -> 13.8 us, 64 at 3,000 19.9 -> 13.2; with two
+// tiles on a unit both take 21). The sums are the same; more slots give nothing.
+template <bool HALF>
+static void launch_lds(const ScoreArgs& a, hipStream_t s)
+{
+    if (((a.n_rows + 31) / 32) * ((a.N + 63) / 64) <= 256) launch_tiles<MfmaTileLds<32, 64, 3, HALF>>(a, s);
+    else launch_tiles<MfmaTileLds<64, 64, 3, HALF>>(a, s);
+}
+
 bool launch_score_kl(const ScoreArgs& a, hipStream_t s)
 {
     if (a.n_rows <= 0) return false;
-    using LdsTile = MfmaTileLds<64, 64, 3>;
-    using LdsTileHalf = MfmaTileLds<64, 64, 3, true>;
-    // 128 x 128 with 4 wavefronts: 0.73 ms a launch at the 63,361-entity
-    // workload (before the workgroups stayed), 256 entities x 128 rows 0.80,
-    // 128 x 256 0.90, both with 8 wavefronts; 128 x 64 1.40 against 1.31 ms a
-    // step, 4 x 1 wavefronts 1.325
-    using SplitTile = MfmaTileF16x2<128, 128, 2, 2>;
+    // Split tiles: the largest that still gives every compute unit work, on
+    // rings that keep enough bytes in flight where a tile has few products.
+    // Measured at d = 400, us a launch, by (entities, rows), 128 x 128 | 128 x
+    // 64 | 64 x 64 | 64 x 32: (14505, 1) 26 | 18 | 14.3 | 12.8; (14505, 61)
+    // 25.8 | 17.8 | 14.2 | 14.7; (14505, 128) 26 | 19.6 | 18.0 | 23; (14505,
+    // 256) 28 | 25.6 | 30 | 37; (14505, 512) 38.6 | 44 | 54 | 60; (63361, 1)
+    // 41 | 33.5 | 35 | 33.3; (63361, 64) 42 | 35 | 37.5 | 41; (63361, 128) 46 |
+    // 53 | 66 | 74. So 64 x 64 and 128 x 64 while one round of two a compute
+    // unit holds them. The large tile with 4 wavefronts: 256 entities x 128 rows and 128 x
+    // 256 with 8 took 10 and 23 % longer at 63,361 x 2,341.
     if (a.ent_split) {
-        launch_split<SplitTile>(a, s);
+        auto tiles = [&](int be, int bq) { return ((a.N + be - 1) / be) * ((a.n_rows + bq - 1) / bq); };
+        constexpr int64_t kRound = 512;
+        if (a.n_rows <= 32) launch_split<MfmaTileF16x2<64, 32, 1, 2, 4>>(a, s);
+        else if (tiles(64, 64) <= kRound) launch_split<MfmaTileF16x2<64, 64, 1, 4, 4>>(a, s);
+        else if (tiles(128, 64) <= kRound) launch_split<MfmaTileF16x2<128, 64, 2, 2, 3>>(a, s);
+        else launch_split<MfmaTileF16x2<128, 128, 2, 2, 2>>(a, s);
         return a.chunk_key != nullptr;
     }
-    if (LdsTile::supports(2 * a.d)) {
-        launch_tiles<LdsTile>(a, s);
-    } else if (LdsTileHalf::supports(2 * a.d)) {
-        launch_tiles<LdsTileHalf>(a, s);
+    if (2 * a.d % 32 == 0) {
+        launch_lds<false>(a, s);
+    } else if (2 * a.d % 32 == 16) {
+        launch_lds<true>(a, s);
     } else {
         const int64_t big_tiles = (int64_t)((a.n_rows + 127) / 128) * ((a.N + 127) / 128);
         if (big_tiles < 512) launch_tiles<MfmaTileReg<64, 64>>(a, s);

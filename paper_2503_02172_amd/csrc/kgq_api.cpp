@@ -874,8 +874,8 @@ kgq_status run_plan(kgq_handle* h, Lane& L, const Plan& p, const int32_t* P, con
                            n_rows_pad, L.states, W, d_score, h->l1, c.gamma, logice ? 1.0f / (float)(2 * d) : 1.0f,
                            L.qpack, L.cq, s);
         else
-        launch_pack(c.model, P + p.off_score_src, mlp ? P + p.off_score_neg : nullptr, p.n_score_rows, n_rows_pad,
-                    L.states, W, d_score, c.center_reg, L.qpack, L.cq, split ? L.q_scale : nullptr, s);
+            launch_pack(c.model, P + p.off_score_src, mlp ? P + p.off_score_neg : nullptr, p.n_score_rows, n_rows_pad,
+                        L.states, W, d_score, c.center_reg, L.qpack, L.cq, split ? L.q_scale : nullptr, s);
     }
     float* dst = out_scores ? out_scores : L.scores;
     bool keyed = false;   // the scorer wrote chunk keys for top-k

@@ -141,10 +141,12 @@ def test_gpu_point_table_layout_bf16(model, name, n_ent, d):
 
 @pytest.mark.parametrize("structure", ["1p", "2u", "pni"])
 @pytest.mark.parametrize("n_ent,d,B,wide", [(300, 32, 5, False), (129, 36, 150, True), (1000, 52, 130, True),
-                                           (64, 400, 33, True)])
+                                           (64, 400, 33, True), (8200, 36, 260, False), (8200, 36, 530, False),
+                                           (50100, 16, 3, False)])
 def test_gpu_betae_split_scorer(structure, n_ent, d, B, wide):
-    """BetaE's f16 matrix-core scorer (forced) at ragged entity and row tiles
-    and widths that end inside a 32-wide stage; wide: entity parameters from
+    """BetaE's f16 matrix-core scorer at ragged entity and row tiles of all its
+    forms, widths that end inside a 32-wide stage, and workgroups that take
+    several tiles (of one stage each at d = 16); wide: entity parameters from
     1e-3 to 50 and projections that reach both ends of the regulariser.
     Tolerance: 2^-20 of the contraction, whose terms are all positive, (the
     parts' 2^-21 and the sum's rounding), the states' float error through the
