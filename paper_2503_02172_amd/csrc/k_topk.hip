@@ -19,8 +19,9 @@
 // than throughput): one workgroup of 256 threads selects the top k of one
 // segment of at most 16 Ki scores, held in registers (KPT keys per thread,
 // element i = j * 256 + tid), all loads issued at once.
-//   Common case (k <= 256): each thread's largest key is taken, and the k-th
-//   largest of those 256 maxima, L, is a lower bound of the segment's k-th
+//   Common case (k <= 256): each thread's largest key is taken, and a bound L
+//   that exactly k of those 256 maxima reach (more where they are equal; a
+//   radix select by ballots) is a lower bound of the segment's k-th
 //   key (k distinct keys, one per thread, are at least L). Only slightly
 //   more than k keys usually reach L (about 120 for k = 100 among 14,505
 //   scores); they are compacted into LDS, with ranges per wavefront from
@@ -75,20 +76,118 @@ __device__ __forceinline__ void store_one(const TopkArgs& a, int64_t orow, int p
     a.out_score[orow * a.out_ld + p] = key_score((uint32_t)(c >> 32));
 }
 
-// Sort the n selected entries inside one wavefront (P = 64 * E >= n
-// positions, lane l holds positions e * 64 + l; padding sorts last) and
-// write out the first k. Entry p is the composite of sel_key[p] and sel_idx[p].
-template <int E>
-__device__ __forceinline__ void bitonic_wave(const uint32_t* sel_key, const uint32_t* sel_idx, int n, int k,
-                                             int64_t orow, int lane, const TopkArgs& a)
+__device__ __forceinline__ uint64_t ballot64(bool f) { return __builtin_amdgcn_ballot_w64(f); }
+
+__device__ __forceinline__ int lanes_below(uint64_t m)
 {
-    constexpr int P = 64 * E;
-    uint64_t v[E];
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// Number of keys at or above x >= 1 (empty slots hold key 0).
+template <int E>
+__device__ __forceinline__ int stream_count_ge(const uint32_t (&key)[E], uint32_t x)
+{
+    int c = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) c += __popcll(ballot64(key[e] >= x));
+    return c;
+}
+
+// Raise the threshold (tk, ti) so that at least k and at most `keep` of the
+// cnt buffered entries reach it (cnt > keep >= k). key[e] holds the key of
+// entry e * 64 + lane (0 past cnt); inv_of(e) gives its inverted index.
+template <int E, bool TIES = true, typename Inv>
+__device__ __forceinline__ void stream_threshold(const uint32_t (&key)[E], Inv inv_of, int cnt, int k, int keep,
+                                                 uint32_t& tk, uint32_t& ti)
+{
+    // common leading bits of the buffered keys (valid keys are >= 1; empty
+    // slots drop out of the maximum, and out of the minimum over key - 1)
+    uint32_t mx = 0u, mn1 = 0xFFFFFFFFu;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        const int p = e * 64 + lane;
-        v[e] = p < n ? (((uint64_t)sel_key[p] << 32) | sel_idx[p]) : 0ull;
+        mx = max(mx, key[e]);
+        mn1 = min(mn1, key[e] - 1u);
     }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        mx = max(mx, (uint32_t)__shfl_xor(mx, off, 64));
+        mn1 = min(mn1, (uint32_t)__shfl_xor(mn1, off, 64));
+    }
+    // (the reduced values are uniform: keep them, and all that follows from
+    // them, in scalar registers)
+    mx = __builtin_amdgcn_readfirstlane(mx);
+    mn1 = __builtin_amdgcn_readfirstlane(mn1);
+    const uint32_t diff = mx ^ (mn1 + 1u);
+    const int top = diff ? 31 - __clz(diff) : -1;
+    // p: the k-th largest key with the bits below the current one cleared
+    // (every key >= p until the loop moves it); np = keys >= p
+    uint32_t p = diff ? mx & ~((2u << top) - 1u) : mx;
+    int np = cnt;
+    for (int b = top; b >= 0 && np > keep; --b) {
+        const uint32_t c = p | (1u << b);
+        const int n = stream_count_ge(key, c);
+        if (n >= k) { p = c; np = n; }
+    }
+    uint32_t q = 0u;
+    if (TIES && np > keep) {
+        // p is the k-th largest key and too many keys equal it: select among
+        // those by inverted index, down to k entries (distinct indices)
+        const int above = p == 0xFFFFFFFFu ? 0 : stream_count_ge(key, p + 1u);
+        const int need = k - above;
+        int nq = np - above;
+        for (int b = 31; b >= 0 && above + nq > keep; --b) {
+            const uint32_t c = q | (1u << b);
+            int n = 0;
+#pragma unroll
+            for (int e = 0; e < E; ++e) n += __popcll(ballot64(key[e] == p && inv_of(e) >= c));
+            if (n >= need) { q = c; nq = n; }
+        }
+    }
+    // the threshold only rises
+    if (p > tk || (p == tk && q > ti)) { tk = p; ti = q; }
+}
+
+// x of lane ^ STRIDE, without LDS: DPP inside a row of 16 lanes, gfx950's lane
+// swaps across rows. A sort step through ds_bpermute waits about 100 cycles
+// for its exchange, and the sort of a row is one serial chain of 28 (k <= 128)
+// to 36 steps: 1 to 2 us of a small batch's 15.
+__device__ __forceinline__ uint32_t lane_xor(uint32_t x, int stride)
+{
+    switch (stride) {
+    case 1: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, true);     // quad 1, 0, 3, 2
+    case 2: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, true);     // quad 2, 3, 0, 1
+    case 4: {
+        // lane ^ 3 in the quad, then 7 - lane in the half row
+        const int q = __builtin_amdgcn_update_dpp(0, (int)x, 0x1B, 0xF, 0xF, true);
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, q, 0x141, 0xF, 0xF, true);
+    }
+    case 8: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xF, 0xF, true);    // row rotated by 8
+    case 16: {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);   // {even rows twice, odd rows twice}
+        return __builtin_amdgcn_inverse_ballot_w64(0xFFFF0000FFFF0000ull) ? r[0] : r[1];
+    }
+    default: {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);   // {lower half twice, upper half twice}
+        return __builtin_amdgcn_inverse_ballot_w64(0xFFFFFFFF00000000ull) ? r[0] : r[1];
+    }
+    }
+}
+
+// Lanes whose bit `bit` of the position e * 64 + lane is clear.
+constexpr uint64_t clear_lanes(int e, int bit)
+{
+    uint64_t m = 0;
+    for (int l = 0; l < 64; ++l) m |= (uint64_t)(((e * 64 + l) & bit) == 0) << l;
+    return m;
+}
+
+// Sort 64 E composites descending inside one wavefront (bitonic network):
+// lane l holds positions e * 64 + l in v[e]. (Which lanes keep the larger is a
+// literal mask: compared for, the masks would be held in scalar registers.)
+template <int E>
+__device__ __forceinline__ void sort_desc(uint64_t (&v)[E])
+{
+    constexpr int P = 64 * E;
 #pragma unroll
     for (int size = 2; size <= P; size <<= 1) {
 #pragma unroll
@@ -99,7 +198,8 @@ __device__ __forceinline__ void bitonic_wave(const uint32_t* sel_key, const uint
                 for (int e = 0; e < E; ++e) {
                     const int f = e ^ es;
                     if (f > e) {
-                        const bool desc = ((e * 64 + lane) & size) == 0;
+                        // (size > stride >= 64: the same for all lanes)
+                        const bool desc = ((e * 64) & size) == 0;
                         const uint64_t a0 = v[e], a1 = v[f];
                         const bool sw = desc ? (a0 < a1) : (a0 > a1);
                         v[e] = sw ? a1 : a0;
@@ -109,55 +209,38 @@ __device__ __forceinline__ void bitonic_wave(const uint32_t* sel_key, const uint
             } else {
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
-                    const uint32_t lo = __shfl_xor((uint32_t)v[e], stride, 64);
-                    const uint32_t hi = __shfl_xor((uint32_t)(v[e] >> 32), stride, 64);
+                    const uint32_t lo = lane_xor((uint32_t)v[e], stride);
+                    const uint32_t hi = lane_xor((uint32_t)(v[e] >> 32), stride);
                     const uint64_t w = ((uint64_t)hi << 32) | lo;
-                    const bool desc = ((e * 64 + lane) & size) == 0;
-                    const bool lower = (lane & stride) == 0;   // this position is the lower of the pair
-                    const uint64_t mx = v[e] > w ? v[e] : w, mn = v[e] > w ? w : v[e];
-                    v[e] = (desc == lower) ? mx : mn;
+                    // the larger goes to the lower position of a descending pair
+                    // and to the upper one of an ascending
+                    const uint64_t large = ~(clear_lanes(e, size) ^ clear_lanes(e, stride));
+                    const uint64_t swap = ballot64(v[e] < w) ^ ~large;
+                    v[e] = __builtin_amdgcn_inverse_ballot_w64(swap) ? w : v[e];
                 }
             }
         }
     }
+}
+
+// Sort the n selected entries inside one wavefront (P = 64 * E >= n
+// positions, lane l holds positions e * 64 + l; padding sorts last) and
+// write out the first k. Entry p is the composite of sel_key[p] and sel_idx[p].
+template <int E>
+__device__ __forceinline__ void bitonic_wave(const uint32_t* sel_key, const uint32_t* sel_idx, int n, int k,
+                                             int64_t orow, int lane, const TopkArgs& a)
+{
+    uint64_t v[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int p = e * 64 + lane;
+        v[e] = p < n ? (((uint64_t)sel_key[p] << 32) | sel_idx[p]) : 0ull;
+    }
+    sort_desc<E>(v);
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int p = e * 64 + lane;
         if (p < k) store_one(a, orow, p, v[e]);
-    }
-}
-
-// Sort 256 keys descending inside one wavefront: lane l holds positions
-// e * 64 + l in v[e] (the network of bitonic_wave, on 32-bit keys).
-__device__ __forceinline__ void sort256_desc(uint32_t (&v)[4], int lane)
-{
-#pragma unroll
-    for (int size = 2; size <= 256; size <<= 1) {
-#pragma unroll
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            if (stride >= 64) {
-                const int es = stride >> 6;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int f = e ^ es;
-                    if (f > e) {
-                        const bool desc = ((e * 64 + lane) & size) == 0;
-                        const uint32_t a0 = v[e], a1 = v[f];
-                        const bool sw = desc ? (a0 < a1) : (a0 > a1);
-                        v[e] = sw ? a1 : a0;
-                        v[f] = sw ? a0 : a1;
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const uint32_t w = __shfl_xor(v[e], stride, 64);
-                    const bool desc = ((e * 64 + lane) & size) == 0;
-                    const bool lower = (lane & stride) == 0;
-                    v[e] = (desc == lower) ? max(v[e], w) : min(v[e], w);
-                }
-            }
-        }
     }
 }
 
@@ -314,7 +397,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5))) void k_
 
     // --- threshold from the thread maxima --------------------------------
     // At least k threads hold a key (positions 0 .. n-1 are spread over the
-    // threads and k <= n), and the k-th largest of their maxima, L, has k
+    // threads and k <= n), and L, which k or more of their maxima reach, has k
     // distinct keys at or above it: L is at most the k-th largest key, so
     // every key of the top k is >= L. Typically only a few more than k keys
     // are (about 120 for k = 100 among 14,505 normal scores), so they are
@@ -326,10 +409,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5))) void k_
             uint32_t v[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = e * 64 + lane < TK_THREADS ? hist[e * 64 + lane] : 0u;
-            sort256_desc(v, lane);
-            const int p = k - 1, ep = p >> 6;
-            const uint32_t sel = ep == 0 ? v[0] : ep == 1 ? v[1] : ep == 2 ? v[2] : v[3];
-            const uint32_t L = __shfl(sel, p & 63, 64);
+            uint32_t L = 0u, ti = 0u;
+            stream_threshold<4, false>(v, [](int) { return 0u; }, TK_THREADS + 1, k, k, L, ti);
             if (lane == 0) sh_bin = (int)L;
         }
         __syncthreads();
@@ -624,77 +705,6 @@ constexpr int kStreamCap = 768;      // candidate buffer entries per wavefront
 template <int H, bool IDX>
 constexpr int stream_min_cap() { return kStreamK + (IDX ? kStreamK : 0) + 256 * H; }
 
-__device__ __forceinline__ uint64_t ballot64(bool f) { return __builtin_amdgcn_ballot_w64(f); }
-
-__device__ __forceinline__ int lanes_below(uint64_t m)
-{
-    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-
-// Number of keys at or above x >= 1 (empty slots hold key 0).
-template <int E>
-__device__ __forceinline__ int stream_count_ge(const uint32_t (&key)[E], uint32_t x)
-{
-    int c = 0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) c += __popcll(ballot64(key[e] >= x));
-    return c;
-}
-
-// Raise the threshold (tk, ti) so that at least k and at most `keep` of the
-// cnt buffered entries reach it (cnt > keep >= k). key[e] holds the key of
-// entry e * 64 + lane (0 past cnt); inv_of(e) gives its inverted index.
-template <int E, bool TIES = true, typename Inv>
-__device__ __forceinline__ void stream_threshold(const uint32_t (&key)[E], Inv inv_of, int cnt, int k, int keep,
-                                                 uint32_t& tk, uint32_t& ti)
-{
-    // common leading bits of the buffered keys (valid keys are >= 1; empty
-    // slots drop out of the maximum, and out of the minimum over key - 1)
-    uint32_t mx = 0u, mn1 = 0xFFFFFFFFu;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        mx = max(mx, key[e]);
-        mn1 = min(mn1, key[e] - 1u);
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        mx = max(mx, (uint32_t)__shfl_xor(mx, off, 64));
-        mn1 = min(mn1, (uint32_t)__shfl_xor(mn1, off, 64));
-    }
-    // (the reduced values are uniform: keep them, and all that follows from
-    // them, in scalar registers)
-    mx = __builtin_amdgcn_readfirstlane(mx);
-    mn1 = __builtin_amdgcn_readfirstlane(mn1);
-    const uint32_t diff = mx ^ (mn1 + 1u);
-    const int top = diff ? 31 - __clz(diff) : -1;
-    // p: the k-th largest key with the bits below the current one cleared
-    // (every key >= p until the loop moves it); np = keys >= p
-    uint32_t p = diff ? mx & ~((2u << top) - 1u) : mx;
-    int np = cnt;
-    for (int b = top; b >= 0 && np > keep; --b) {
-        const uint32_t c = p | (1u << b);
-        const int n = stream_count_ge(key, c);
-        if (n >= k) { p = c; np = n; }
-    }
-    uint32_t q = 0u;
-    if (TIES && np > keep) {
-        // p is the k-th largest key and too many keys equal it: select among
-        // those by inverted index, down to k entries (distinct indices)
-        const int above = p == 0xFFFFFFFFu ? 0 : stream_count_ge(key, p + 1u);
-        const int need = k - above;
-        int nq = np - above;
-        for (int b = 31; b >= 0 && above + nq > keep; --b) {
-            const uint32_t c = q | (1u << b);
-            int n = 0;
-#pragma unroll
-            for (int e = 0; e < E; ++e) n += __popcll(ballot64(key[e] == p && inv_of(e) >= c));
-            if (n >= need) { q = c; nq = n; }
-        }
-    }
-    // the threshold only rises
-    if (p > tk || (p == tk && q > ti)) { tk = p; ti = q; }
-}
-
 // Prune while the stream runs (its loads in flight hold registers): keys in
 // registers, indices read from LDS. Entries reaching the new threshold are
 // compacted to the front, in place, as (score bits, index). Copies of one
@@ -764,48 +774,17 @@ __device__ __forceinline__ void stream_prune_final(uint2* buf, int& cnt, uint32_
 }
 
 // Sort the n (key, inverted index) entries of buf inside one wavefront and
-// write the first k (the network of bitonic_wave).
+// write the first k.
 template <int E>
 __device__ __forceinline__ void stream_sort(const uint2* buf, int n, int k, int64_t orow, int lane, const TopkArgs& a)
 {
-    constexpr int P = 64 * E;
     uint64_t v[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int p = e * 64 + lane;
         v[e] = p < n ? (((uint64_t)buf[p].x << 32) | buf[p].y) : 0ull;
     }
-#pragma unroll
-    for (int size = 2; size <= P; size <<= 1) {
-#pragma unroll
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            if (stride >= 64) {
-                const int es = stride >> 6;
-#pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    const int f = e ^ es;
-                    if (f > e) {
-                        const bool desc = ((e * 64 + lane) & size) == 0;
-                        const uint64_t a0 = v[e], a1 = v[f];
-                        const bool sw = desc ? (a0 < a1) : (a0 > a1);
-                        v[e] = sw ? a1 : a0;
-                        v[f] = sw ? a0 : a1;
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    const uint32_t lo = __shfl_xor((uint32_t)v[e], stride, 64);
-                    const uint32_t hi = __shfl_xor((uint32_t)(v[e] >> 32), stride, 64);
-                    const uint64_t w = ((uint64_t)hi << 32) | lo;
-                    const bool desc = ((e * 64 + lane) & size) == 0;
-                    const bool lower = (lane & stride) == 0;
-                    const uint64_t mx = v[e] > w ? v[e] : w, mn = v[e] > w ? w : v[e];
-                    v[e] = (desc == lower) ? mx : mn;
-                }
-            }
-        }
-    }
+    sort_desc<E>(v);
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int p = e * 64 + lane;
@@ -1130,6 +1109,12 @@ int64_t topk_scratch_elems(int64_t n_rows, int64_t N, int k)
 // costs one more (short) round over the per-segment lists. Below that the
 // chip is mostly idle and the register-resident kernel, which issues a whole
 // segment's loads at once, has the lower latency.
+// With chunk keys, at least two for each of the k, one wavefront per whole row
+// at any number of rows: it reads about k chunks only, in one round where a
+// row longer than kTopkSegment would take two (63,361 entities: one row 87 ->
+// 76 us a call, 512 rows 264 -> 251; 14,505: 128 rows, k = 10, 83 -> 78, the
+// same at k = 100). With fewer keys the list is most of the row: k = 256 at
+// 14,505, 512 rows, 312 us against 283.
 constexpr int64_t kStreamMinUnits = 2048;
 
 static void launch_stream(const TopkArgs& a, hipStream_t s)
@@ -1167,8 +1152,10 @@ bool launch_topk(const TopkArgs& in, hipStream_t s)
         const int64_t fit = a.n_rows >= kStreamMinUnits
                                 ? 1
                                 : std::min<int64_t>(max_segs, (kStreamMinUnits + a.n_rows - 1) / a.n_rows);
-        const bool stream = a.k <= kStreamK && a.n_rows * fit >= kStreamMinUnits;
-        int64_t segs = stream ? fit : max_segs;
+        const int64_t chunks = (a.N + kKeyChunk - 1) / kKeyChunk;
+        const bool listed = a.k <= kStreamK && !a.in_idx && a.chunk_key && chunks <= kPruneChunks && chunks >= 2 * a.k;
+        const bool stream = listed || (a.k <= kStreamK && a.n_rows * fit >= kStreamMinUnits);
+        int64_t segs = listed ? 1 : stream ? fit : max_segs;
         int64_t seg_len = a.N;
         if (segs > 1) {
             seg_len = stream ? ((a.N + segs - 1) / segs + 255) / 256 * 256 : kTopkSegment;

@@ -193,3 +193,27 @@ def test_gpu_split_layers(model, structure, d, B):
     ref = O.Model(model, w.params, w.gamma, **kw).scores(S[structure], qb.anchors, qb.relations)
     check_scores(out["scores"], ref, w.rtol, w.gamma, structure)
     check_topk(out["idx"], out["score"], ref, 5, w.rtol, w.gamma, structure)
+
+
+@pytest.mark.parametrize("n_ent,B,k", [(9001, 3, 1), (9001, 33, 70), (9001, 33, 71), (9001, 130, 64), (20011, 5, 156),
+                                       (20011, 40, 157), (65600, 3, 256)])
+@pytest.mark.parametrize("structure", ["1p", "2u"])
+def test_gpu_topk_listed_small(structure, n_ent, B, k):
+    """Top-k of small batches over a matrix with chunk keys, at both sides of
+    two keys for each of the k and of the longest listed row (65,536), over
+    entities in groups of eight equal ones (ties inside and across chunks):
+    exactly the ranking of the returned scores, equal ones by index."""
+    import torch
+    from paper_2503_02172_amd import kgq
+    w = synth.make_tiny(O.BETAE, n_ent=n_ent, n_rel=7, dim=16, seed=121)
+    ab = w.params["entity.alpha_beta"]
+    ab[:] = ab[(np.arange(n_ent) * 5 // 8) % n_ent]
+    qb = synth.draw_queries(structure, B, n_ent, 7, seed=122)
+    with kgq.engine_for(w, max_batch=B) as eng:
+        eng.set_dense_path(kgq.DENSE_BF16X3)
+        out = eng.execute(S[structure], qb.anchors, qb.relations, k=k, scores=True)
+        torch.cuda.synchronize()
+        got, idx, val = (out[n].cpu().numpy() for n in ("scores", "idx", "score"))
+    want = np.argsort(-got, axis=1, kind="stable")[:, :k]
+    assert np.array_equal(idx, want)
+    assert np.array_equal(val, np.take_along_axis(got, want, 1))
