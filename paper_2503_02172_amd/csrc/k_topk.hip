@@ -404,13 +404,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5))) void k_
     // compacted directly: no histogram, no atomics. More than 256 (masses of
     // equal scores at L) take the histogram passes below instead.
     int n_sel = -1;            // entries placed in sel_key[] / sel_idx[]
-    if (k <= TK_THREADS && top >= 0) {
+    if (k <= 256 && top >= 0) {
         if (tid < 64) {
+            // (more threads: the maxima of groups of threads, still 256)
             uint32_t v[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = e * 64 + lane < TK_THREADS ? hist[e * 64 + lane] : 0u;
+            for (int e = 0; e < 4; ++e) {
+                v[e] = hist[e * 64 + lane];
+#pragma unroll
+                for (int t = 256; t < TK_THREADS; t += 256) v[e] = max(v[e], hist[t + e * 64 + lane]);
+            }
             uint32_t L = 0u, ti = 0u;
-            stream_threshold<4, false>(v, [](int) { return 0u; }, TK_THREADS + 1, k, k, L, ti);
+            stream_threshold<4, false>(v, [](int) { return 0u; }, 257, k, k, L, ti);
             if (lane == 0) sh_bin = (int)L;
         }
         __syncthreads();
@@ -1089,8 +1094,17 @@ static void launch_segments(const TopkArgs& a, hipStream_t s)
     dim3 grid((unsigned)(((a.N + a.seg_len - 1) / a.seg_len) * a.n_rows));
     // 256 threads with up to 64 keys each for long segments; short ones
     // (k-candidate lists of later rounds) use as many keys per thread as fit
+    // Few segments (at most 64): 1,024 threads each, 4 wavefronts a SIMD to
+    // overlap the passes over the keys, which one wavefront runs as one chain:
+    // one row of 14,505, k = 100, 104.2 -> 99.4 us a call, 16 rows 55 -> 50, 8
+    // rows at k = 1,000 81 -> 65; 128 rows the same, 512 up to 7 us slower
+    // (k = 1,000), the chip being full of either.
     const int64_t per = (a.seg_len + 255) / 256;
-    if (per <= 4) hipLaunchKernelGGL((k_topk<256, 4>), grid, dim3(256), 0, s, a);
+    if (per > 8 && grid.x <= 64) {
+        if (per <= 16) hipLaunchKernelGGL((k_topk<1024, 4>), grid, dim3(1024), 0, s, a);
+        else if (per <= 32) hipLaunchKernelGGL((k_topk<1024, 8>), grid, dim3(1024), 0, s, a);
+        else hipLaunchKernelGGL((k_topk<1024, 16>), grid, dim3(1024), 0, s, a);
+    } else if (per <= 4) hipLaunchKernelGGL((k_topk<256, 4>), grid, dim3(256), 0, s, a);
     else if (per <= 8) hipLaunchKernelGGL((k_topk<256, 8>), grid, dim3(256), 0, s, a);
     else if (per <= 16) hipLaunchKernelGGL((k_topk<256, 16>), grid, dim3(256), 0, s, a);
     else if (per <= 32) hipLaunchKernelGGL((k_topk<256, 32>), grid, dim3(256), 0, s, a);

@@ -217,3 +217,21 @@ def test_gpu_topk_listed_small(structure, n_ent, B, k):
     want = np.argsort(-got, axis=1, kind="stable")[:, :k]
     assert np.array_equal(idx, want)
     assert np.array_equal(val, np.take_along_axis(got, want, 1))
+
+
+@pytest.mark.parametrize("k", [1, 256, 257, 1024])
+@pytest.mark.parametrize("n_ent,B", [(2049, 3), (4097, 64), (4096, 65), (8193, 5), (16384, 2), (16385, 33)])
+def test_gpu_topk_few_rows(n_ent, B, k):
+    """Register-resident top-k with 1,024 and with 256 threads a segment (at
+    most 64 segments, and more) at the ends of its key counts, over few
+    distinct scores: exactly the ranking of the returned scores."""
+    import torch
+    from paper_2503_02172_amd import kgq
+    w = synth.make_tiny(O.GQE, n_ent=n_ent, n_rel=7, dim=8, seed=131)
+    rng = np.random.Generator(np.random.PCG64(132))
+    w.params["entity"][:] = rng.integers(0, 40, (n_ent, 8)).astype(np.float32) / 8
+    qb = synth.draw_queries("1p", B, n_ent, 7, seed=133)
+    out = _scores(w, O.GQE, "1p", qb, k)
+    want = np.argsort(-out["scores"], axis=1, kind="stable")[:, :k]
+    assert np.array_equal(out["idx"], want)
+    assert np.array_equal(out["score"], np.take_along_axis(out["scores"], want, 1))
