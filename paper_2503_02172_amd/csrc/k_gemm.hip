@@ -1,14 +1,15 @@
-// Dense layers on the FP32 matrix cores of gfx950:  C = epi(A W^T + b).
+// Dense layers on the matrix cores of gfx950:  C = epi(A W^T + b).
 //
 // These are the dense contractions of the operators: the projection MLPs of
 // BetaE, ConE and LogicE (Eq. 4 of the paper: three matmul + bias layers with
 // ReLU between them) and the attention / set-function MLPs of the
-// intersection operators. Both
-// operands are K-contiguous (A rows, W rows). The tile loop (mfma_tile.hpp)
-// runs 64 x 64 workgroup tiles: at the path's shapes (M of a few hundred to a
-// few thousand rows, N and K of 400 to 1,600) they give enough workgroups to
-// fill the chip, and measured faster than 64 x 128, 128 x 64 or 128 x 128
-// tiles there. K a multiple of 16 takes the direct-to-LDS ring of three
+// intersection operators. Both operands are K-contiguous (A rows, W rows).
+// BetaE's, ConE's and LogicE's layers run on rows in split form (k_gemm_split,
+// at the end); the rest of this comment is about GQE's and Query2Box's, and
+// kgq_dense's. The FP32 tile loop (mfma_tile.hpp) runs 64 x 64 workgroup
+// tiles: at the path's shapes (M of a few hundred to a few thousand rows, N and
+// K of 400 to 1,600) they give enough workgroups to fill the chip, and measured
+// faster than 64 x 128, 128 x 64 or 128 x 128 tiles there. K a multiple of 16 takes the direct-to-LDS ring of three
 // stages, any other K the register-staged loop. Tiles are dispatched in
 // row-major order split into one contiguous range per XCD, so each XCD's L2
 // sees few distinct rows of A at a time.
@@ -238,7 +239,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16x3(GemmArgs g, int tm, int tn,
     gemm_bf16x3_tile<BM, BN, BM == 64>(g, tm, tn, per_xcd, sm);   // raised read priority: see the tile
 }
 
-// 128 x 128 tiles (the BetaE scorer's): an 80 KiB ring, above the static LDS
+// 128 x 128 tiles: an 80 KiB ring, above the static LDS
 // limit, two workgroups per compute unit, raised read priority
 __global__ __launch_bounds__(256, 2) void k_gemm_bf16x3_128(GemmArgs g, int tm, int tn, int per_xcd)
 {

@@ -412,7 +412,8 @@ __global__ __launch_bounds__(256, 4) void k_score(ScoreArgs a, int nqg, int qchu
                 if (FIXED)
                     sc[u][j] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(base_hi), i + u)) +
                                fmaf(-a.dist_scale, dist(i + u, j),
-                                    __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(base_lo), i + u)));
+                                    fmaf(-a.dist_low, dist(i + u, j),
+                                         __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(base_lo), i + u))));
                 else if (MODEL != 1) sc[u][j] = a.gamma - a.dist_scale * dist(i + u, j);
                 else sc[u][j] = a.gamma - acc[i + u][j] + (1.0f - a.center_reg) * acc2[i + u][j];
             }
@@ -473,7 +474,7 @@ __global__ __launch_bounds__(256) void k_score_sum(ScoreArgs a, int splits, int6
             if (MODEL == 1) s2 += pz[(rows_pad + r0 + u) * n_pad + e];
         }
         const float v =
-            MODEL != 1 ? (a.l1_fixed ? (float)(a.cq[r0 + u] - (double)a.dist_scale * (double)s1)
+            MODEL != 1 ? (a.l1_fixed ? (float)(a.cq[r0 + u] - ((double)a.dist_scale + (double)a.dist_low) * (double)s1)
                                      : a.gamma - a.dist_scale * s1) : a.gamma - s1 + (1.0f - a.center_reg) * s2;
         best = u == 0 ? v : fmaxf(best, v);
     }

@@ -885,7 +885,11 @@ kgq_status run_plan(kgq_handle* h, Lane& L, const Plan& p, const int32_t* P, con
                     p.n_quad_rows, p.n_pair_rows, d_score, N, h->n_blocks, c.gamma, c.center_reg, dst, N};
         a.dist_scale = logice ? 1.0f / (float)(2 * d) : cone ? h->cone_modulus : 1.0f;
         a.l1_fixed = h->l1.on;
-        if (h->l1.on) a.dist_scale *= h->l1.quantum;
+        if (h->l1.on) {
+            const double f = (logice ? 1.0 / (2.0 * d) : 1.0) * (double)h->l1.quantum;
+            a.dist_scale = (float)f;
+            a.dist_low = (float)(f - (double)a.dist_scale);
+        }
         if (split) {
             a.ent_split = h->ent_split;
             a.ent_scale = h->ent_scale;

@@ -377,6 +377,9 @@ struct ScoreArgs {
     // distance scale: score = gamma - dist_scale * distance (GQE 1, LogicE
     // 1 / (2d), ConE its modulus; Query2Box ignores it)
     float dist_scale = 1.0f;
+    // fixed point: what dist_scale rounded off the factor (a rounding shared by
+    // every score of a table, 2^-24 of the distance)
+    float dist_low = 0.0f;
     // GQE / LogicE: table and packed rows are fixed-point words (L1Fixed); cq
     // then holds each row's base, and dist_scale the quantum's factor too
     bool l1_fixed = false;

@@ -639,10 +639,10 @@ __device__ __forceinline__ void split_row_wave(F f, int n8, float* dst, float* s
 }
 
 // Tiles: WM x WN wavefronts, each with (BM / WM / 16) x (BN / WN / 16) blocks
-// of 16 x 16, two accumulators a block. Stages of 32 of K go through an
-// S-slot LDS ring by direct-to-LDS loads, S - 1 stages ahead; both operands' rows are 128 bytes a
-// stage, 16-byte pieces XOR-swizzled by row as in the bf16 form, and fragments
-// are read as they are: no split work in the loop. Lane l holds the output
+// of 16 x 16, two accumulators a block. Stages of 32 of K go through an S-slot
+// LDS ring by direct-to-LDS loads, S - 1 stages ahead; both operands' rows are
+// 128 bytes a stage, 16-byte pieces XOR-swizzled by row as in the bf16 form, and
+// fragments are read as they are: no split work in the loop. Lane l holds the output
 // rows 4 (l / 16) .. + 3 of column l % 16 of each block. A stage: wait until it
 // has landed, barrier (every wavefront has read the one before, whose slot is
 // free), fragments, the next stage's loads, products.
