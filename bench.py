@@ -14,8 +14,8 @@ Prints one JSON line. `value` is queries/s over the timed steps.
 `roofline` describes the dominant kernel (the entity scorer): the
 algorithmic operations of one launch divided by the launch's average
 duration (HIP events around each launch on the stream it runs on), against
-the chip's published peak for the units it runs on (for BetaE the bf16
-matrix cores at six bf16 products per FP32-accurate product, or the FP32
+the chip's published peak for the units it runs on (for BetaE the f16
+matrix cores at three f16 products per FP32-accurate product, or the FP32
 matrix cores with --matrix-path fp32; FP32 vector units for the others).
 `cpu_baseline` times the CPU oracle on a bounded sample of the same workload,
 on every host thread and on one. `others` reports the other workloads
@@ -39,15 +39,17 @@ sys.path.insert(0, ROOT)
 # Scorer rooflines.
 # BetaE scores on the matrix cores; each (row, entity, dimension) triple is 2
 # multiply-adds (alpha * U + beta * V), 4 flops. By default the contraction
-# runs on the bf16 matrix cores with each FP32 operand split exactly into
-# three bf16 parts and six part products kept (FP32 accuracy), so its ceiling
-# is the published dense bf16 MFMA peak, 2.5 PFLOP/s, over 6: 416.7 TFLOP/s of
-# FP32-accurate flops. On the FP32 matrix cores (--matrix-path fp32) it is the
+# runs on the f16 matrix cores with each FP32 operand row scaled and split into
+# two f16 parts and three part products kept (FP32 error class), so its ceiling
+# is the published dense f16 MFMA peak, 2.5 PFLOP/s (bf16's), over 3: 833.3
+# TFLOP/s of FP32-accurate flops. On the FP32 matrix cores (--matrix-path fp32) it is the
 # published dense FP32 MFMA peak, 157.3 TFLOP/s; that fraction is reported
 # beside the other as `frac_of_fp32_mfma_peak`.
 # GQE and Query2Box score on the vector units. Each sub / add / min of the
 # scorer is one flop and one lane-operation (the library is compiled without
-# packed FP32 instructions, so an instruction does one operation per lane).
+# packed FP32 instructions, so an instruction does one operation per lane). On
+# tables whose values allow it the L1 scorers (GQE, LogicE) run two rows of
+# three in fixed point, one sum-of-absolute-differences instruction a triple.
 # Two peaks are reported for them:
 #   flops against the published FP32 vector peak, 157.3 TFLOP/s (which counts
 #   a packed FMA, 4 flops per lane per clock: 256 CUs x 64 lanes x 4 x 2.4 GHz);
@@ -59,16 +61,17 @@ sys.path.insert(0, ROOT)
 PEAK_VALU_OPS = 256 * 4 * 32 * 2.4e9
 PEAK_VALU_F32 = 157.3e12
 PEAK_MFMA_F32 = 157.3e12
-PEAK_MFMA_BF16 = 2.5e15
-BF16X3_PRODUCTS = 6
+PEAK_MFMA_F16 = 2.5e15
+F16X2_PRODUCTS = 3
 HBM_PEAK = 8.0e12
 # algorithmic flops per (query row, entity, scored coordinate) triple, the
-# peak they are counted against, and its unit. ConE's sector distance is 10
-# VALU instructions per triple, 3 of them fused multiply-adds (13 flops);
+# peak they are counted against, and its unit. ConE's sector distance is 6
+# VALU instructions per triple, 5 of them fused multiply-adds (11 flops);
 # LogicE's triple is one of its 2d bound coordinates scored by GQE's L1 form.
-OPS_PER_TRIPLE = {0: 2, 1: 4, 2: 4, 3: 13, 4: 2}
-# VALU lane-operations per triple (instructions per lane), for the issue-rate fraction
-LANE_OPS_PER_TRIPLE = {0: 2, 1: 4, 3: 10, 4: 2}
+OPS_PER_TRIPLE = {0: 2, 1: 4, 2: 4, 3: 11, 4: 2}
+# VALU lane-operations per triple (instructions per lane), for the issue-rate
+# fraction; the L1 scorers' in fixed point (2 where a table keeps floats)
+LANE_OPS_PER_TRIPLE = {0: 4 / 3, 1: 4, 3: 6, 4: 4 / 3}
 SCORER_PEAK = {0: (PEAK_VALU_F32, "alu", "TFLOP/s"), 1: (PEAK_VALU_F32, "alu", "TFLOP/s"),
                2: (PEAK_MFMA_F32, "mfma", "TFLOP/s"), 3: (PEAK_VALU_F32, "alu", "TFLOP/s"),
                4: (PEAK_VALU_F32, "alu", "TFLOP/s")}
@@ -78,8 +81,8 @@ K_TOP = 100
 def scorer_peak(model: int, matrix_path: str):
     """(peak, bound, unit, basis) of a model's scorer on the given matrix path."""
     if model == 2 and matrix_path != "fp32":
-        return (PEAK_MFMA_BF16 / BF16X3_PRODUCTS, "mfma", "TFLOP/s",
-                "dense bf16 MFMA peak 2.5 PFLOP/s / 6 bf16 products per FP32-accurate product")
+        return (PEAK_MFMA_F16 / F16X2_PRODUCTS, "mfma", "TFLOP/s",
+                "dense f16 MFMA peak 2.5 PFLOP/s / 3 f16 products per FP32-accurate product")
     peak, bound, unit = SCORER_PEAK[model]
     basis = "dense FP32 MFMA peak" if model == 2 else "FP32 vector peak (packed FMA, 4 flops per lane per clock)"
     return peak, bound, unit, basis
@@ -472,8 +475,8 @@ def main():
                          "and output buffer each), so that one step's small kernels overlap another's scorer. "
                          "The other mode is timed after the headline and reported beside it")
     ap.add_argument("--matrix-path", choices=["auto", "fp32"], default="auto",
-                    help="dense contractions (MLP layers, BetaE scorer) on the bf16 matrix cores with the exact "
-                         "three-part split where it pays (auto, the library default) or on the FP32 matrix "
+                    help="dense contractions (MLP layers, BetaE scorer) on the f16 matrix cores with both "
+                         "operands in two parts (Query2Box and GQE layers: bf16, three) where it pays (auto, the library default) or on the FP32 matrix "
                          "cores only (fp32)")
     ap.add_argument("--sweep", default=None, metavar="SIZES",
                     help="instead of the benchmark: per-query time and device memory against batch size, per "
@@ -613,9 +616,9 @@ def main():
         "scaling": "weak",
         "vs_baseline": None,
         "dtype": "f32",
-        "arithmetic": ("dense contractions (BetaE scorer, MLP layers) on the bf16 matrix cores: "
-                       "each FP32 operand split exactly into three bf16 parts, six part products accumulated in FP32 "
-                       "(FP32 error class); the rest FP32"
+        "arithmetic": ("dense contractions (BetaE scorer, MLP layers) on the f16 matrix cores: "
+                       "each FP32 operand row scaled and split into two f16 parts, three part products accumulated in "
+                       "FP32 (FP32 error class); the rest FP32"
                        if args.matrix_path == "auto" else "FP32 throughout (FP32 matrix cores and vector units)"),
         "data": "synthetic (seeded random tables and queries of the workload's shapes)",
         "config": {"workload": WORKLOAD_DESC[args.workload], "name": args.workload,

@@ -167,7 +167,11 @@ kgq_status kgq_create(const kgq_config* cfg, kgq_handle** out);
  * state . W1^T [N x 4d] and relation . W1^T + b1 [R x 4d], where W1 is split
  * by columns for LogicE's concatenated input; the layer is linear in its
  * input, Eq. 4), rebuilt when the entity table, "relation", "proj.w1" or
- * "proj.b1" is loaded and all four are present.
+ * "proj.b1" is loaded and all four are present; GQE's and LogicE's entity
+ * coordinates as fixed-point words where their range and spread allow it
+ * (chosen by the table's values); and every dense weight, and BetaE's
+ * entity-side scoring rows, in the parts that the matrix-core paths read
+ * (kgq_set_dense_path).
  * Errors: INVALID_ARG (unknown name, wrong nbytes or dtype, null src), OOM, DEVICE. */
 kgq_status kgq_load_params(kgq_handle* h, const char* name, const void* src, size_t nbytes,
                            int32_t dtype, int32_t src_is_device);
@@ -258,23 +262,29 @@ kgq_status kgq_set_checked(kgq_handle* h, int32_t on);
  * MLPs of Eq. 4 and of the intersection operators, and kgq_dense) and
  * BetaE's scoring contraction (the regrouped KL of Eq. 3's embeddings). Both
  * paths compute in FP32 precision class:
- *   KGQ_DENSE_AUTO (the default): layers with K >= 32 (K is a multiple of 4
- *     on every path) and at least 384 output tiles of 64 x 64, or 1,024 rows
- *     and 192 such tiles, run on the bf16 matrix cores, each FP32 operand
+ *   KGQ_DENSE_AUTO (the default): BetaE's, ConE's and LogicE's layers (from 16
+ *     embedding dimensions on) run on the f16 matrix cores at every size: each
+ *     FP32 row, of the weights and of the layer's input, is scaled by a power
+ *     of two and split into two f16 parts, and three of the four part products
+ *     are kept (error 2^-22 of each product, in the class of the FP32 sum;
+ *     values more than 2^27 below a bound of their row's largest lose
+ *     precision against it). BetaE scores the same way when the call has more
+ *     than 256 tiles of 64 scored rows x 64 entities; smaller calls score on
+ *     the FP32 matrix cores.
+ *     GQE's and Query2Box's layers and kgq_dense, with K >= 32 (K is a multiple
+ *     of 4 on every path) and at least 384 output tiles of 64 x 64, or 1,024
+ *     rows and 192 such tiles, run on the bf16 matrix cores, each FP32 operand
  *     split exactly into three bf16 parts and six of the nine part products
  *     kept (the dropped ones are below 2^-23 of each product; the weight
  *     parts are zero-padded to a multiple of 32 columns); smaller layers of
  *     an execute with more than 64 rows and K >= 64 split K there; the
  *     others (K < 32, layers of at most 64 rows, and kgq_dense layers below
- *     the bounds) on the FP32 matrix cores. Inputs
- *     must be finite and below 3.39e38 in magnitude on the bf16 path.
- *     BetaE scores on the f16 matrix cores, each FP32 operand row scaled by a
- *     power of two and split into two f16 parts, three of the four part
- *     products kept, when the call has more than 256 tiles of 64 scored rows
- *     x 64 entities; smaller calls score on the FP32 matrix cores.
+ *     the bounds) on the FP32 matrix cores. Inputs must be finite and below
+ *     3.39e38 in magnitude on the bf16 path.
  *   KGQ_DENSE_FP32: every layer and the BetaE scorer on the FP32 matrix cores.
- *   KGQ_DENSE_BF16X3: every layer with K >= 32 on the bf16 path, and the
- *     BetaE scorer on the f16 matrix cores, whatever the size (for tests).
+ *   KGQ_DENSE_BF16X3: every layer with K >= 32 on the bf16 path (the f16 path
+ *     for the models that take it), and the BetaE scorer on the f16 matrix
+ *     cores, whatever the size (for tests).
  * The parts of the weights and of BetaE's entity-side scoring rows are made
  * when they are loaded, whatever the path. Takes effect for calls
  * enqueued after it. Errors: INVALID_ARG. */
