@@ -394,7 +394,9 @@ __global__ __launch_bounds__(256, 4) void k_score(ScoreArgs a, int nqg, int qchu
     if constexpr (FIXED) {
         const double base = a.cq[min(qb * TQ + min(lane, TQ - 1), a.n_rows - 1)];
         base_hi = (float)base;
-        base_lo = base_hi - base_hi == 0.f ? (float)(base - (double)base_hi) : 0.f;    // (infinite: no low part)
+        // (not finite: no low part; told by the bits, since this file is built
+        // without NaN semantics and base_hi - base_hi counts as 0)
+        base_lo = (__float_as_uint(base_hi) & 0x7F800000u) != 0x7F800000u ? (float)(base - (double)base_hi) : 0.f;
     }
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     int32_t od[TQ];

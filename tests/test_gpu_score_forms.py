@@ -114,6 +114,26 @@ def test_gpu_l1_infinite_query(bad):
     assert np.all(np.isfinite(np.delete(out, [2, 7], 0)))
 
 
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("n_ent,B", [(6000, 200), (3000, 1100)])
+def test_gpu_l1_not_finite_query_unsplit(n_ent, B, bad):
+    """The same where the dimensions are not split (128 or more workgroups,
+    small and large row form; d = 64 takes fixed point on this table): scores
+    of -inf, ranked by index, or NaN; other rows are finite and untouched."""
+    w = synth.make_tiny(O.GQE, n_ent=n_ent, n_rel=7, dim=64, seed=93)
+    w.params["relation"][2, 5] = bad
+    qb = synth.draw_queries("1p", B, n_ent, 7, seed=94)
+    out = _scores(w, O.GQE, "1p", qb, 5)
+    hit = qb.relations[:, 0] == 2
+    assert hit.any()
+    if np.isnan(bad):
+        assert np.isnan(out["scores"][hit]).all()
+    else:
+        assert np.isneginf(out["scores"][hit]).all()
+        assert np.array_equal(out["idx"][hit], np.tile(np.arange(5), (int(hit.sum()), 1)))
+    assert np.isfinite(out["scores"][~hit]).all()
+
+
 @pytest.mark.parametrize("model,name", [(O.GQE, "entity"), (O.Q2B, "entity"), (O.LOGICE, "entity.bounds")],
                          ids=["gqe", "q2b", "logice"])
 @pytest.mark.parametrize("n_ent,d", [(70, 36), (257, 64), (64, 132)])
