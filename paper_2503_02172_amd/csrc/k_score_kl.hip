@@ -322,11 +322,20 @@ __global__ __launch_bounds__(Tile::kThreads, 2) void k_score_kl_split(ScoreArgs 
                 nan = nan || __builtin_isunordered(v.x, v.y) || __builtin_isunordered(v.z, v.w);
             }
             if (a.chunk_key) {
-                // an upper bound of the keys of the chunk's scores: the key of
-                // their float maximum (the scores order as their keys, NaN
-                // aside), or the largest key when one is NaN
-                const uint32_t u = __float_as_uint(kmax == 0.0f ? 0.0f : kmax);
-                uint32_t kx = nan ? 0xFFFFFFFFu : u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+                // the largest key of the lane's scores: the key of their float
+                // maximum (the scores order as their keys, NaN aside), or
+                // where one is NaN of each key by itself. No bound above it:
+                // the k-th largest chunk key is top-k's first threshold, which
+                // k scores have to reach.
+                uint32_t kx = ew < a.N ? score_key(kmax) : 0u;
+                if (nan) {
+                    kx = 0u;
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            if (ew + i * 16 + q < a.N) kx = max(kx, score_key(acc[i][j][q]));
+                }
                 kx = max(kx, (uint32_t)__shfl_xor((int)kx, 16, 64));
                 kx = max(kx, (uint32_t)__shfl_xor((int)kx, 32, 64));
                 const int64_t chunk0 = te0 + (Tile::row_of(0) & ~(kKeyChunk - 1));

@@ -255,3 +255,32 @@ def test_gpu_topk_few_rows(n_ent, B, k):
     want = np.argsort(-out["scores"], axis=1, kind="stable")[:, :k]
     assert np.array_equal(out["idx"], want)
     assert np.array_equal(out["score"], np.take_along_axis(out["scores"], want, 1))
+
+
+@pytest.mark.parametrize("every,sign", [(64, 1.0), (64, -1.0), (200, 1.0), (1, 1.0)])
+@pytest.mark.parametrize("structure,B", [("1p", 3), ("2u", 130)])
+def test_gpu_topk_listed_nan(structure, B, every, sign):
+    """Top-k over a matrix with chunk keys in which whole entities score NaN:
+    one in each chunk (more such chunks than k), one in about every third, and
+    the first 300 entities. Exactly the ranking of the returned scores by their
+    keys: NaNs by their bits, above +inf or below -inf, equal ones by index."""
+    import torch
+    from paper_2503_02172_amd import kgq
+    n_ent, k = 9001, 64
+    w = synth.make_tiny(O.BETAE, n_ent=n_ent, n_rel=7, dim=16, seed=141)
+    bad = np.zeros(n_ent, bool)
+    bad[: 300 if every == 1 else n_ent : every] = True
+    w.params["entity.alpha_beta"][bad] = np.copysign(np.float32(np.nan), np.float32(sign))
+    qb = synth.draw_queries(structure, B, n_ent, 7, seed=142)
+    qb.anchors[:] = np.where(bad[qb.anchors], 8999, qb.anchors)
+    with kgq.engine_for(w, max_batch=B) as eng:
+        eng.set_dense_path(kgq.DENSE_BF16X3)
+        out = eng.execute(S[structure], qb.anchors, qb.relations, k=k, scores=True)
+        torch.cuda.synchronize()
+        got, idx, val = (out[n].cpu().numpy() for n in ("scores", "idx", "score"))
+    assert np.isnan(got[:, bad]).all() and np.isfinite(got[:, ~bad]).all()
+    u = (got + np.float32(0.0)).view(np.uint32)
+    key = np.where(u >> 31 != 0, ~u, u | np.uint32(0x80000000)).astype(np.int64)
+    want = np.argsort(-key, axis=1, kind="stable")[:, :k]
+    assert np.array_equal(idx, want)
+    assert np.array_equal(val.view(np.uint32), np.take_along_axis(got, want, 1).view(np.uint32))
