@@ -48,8 +48,8 @@ sys.path.insert(0, ROOT)
 # GQE and Query2Box score on the vector units. Each sub / add / min of the
 # scorer is one flop and one lane-operation (the library is compiled without
 # packed FP32 instructions, so an instruction does one operation per lane). On
-# tables whose values allow it the L1 scorers (GQE, LogicE) run two rows of
-# three in fixed point, one sum-of-absolute-differences instruction a triple.
+# tables whose values allow it the L1 scorers (GQE, LogicE) run in fixed point,
+# one sum-of-absolute-differences instruction a triple, at half rate.
 # Two peaks are reported for them:
 #   flops against the published FP32 vector peak, 157.3 TFLOP/s (which counts
 #   a packed FMA, 4 flops per lane per clock: 256 CUs x 64 lanes x 4 x 2.4 GHz);
@@ -71,7 +71,7 @@ HBM_PEAK = 8.0e12
 OPS_PER_TRIPLE = {0: 2, 1: 4, 2: 4, 3: 11, 4: 2}
 # VALU lane-operations per triple (instructions per lane), for the issue-rate
 # fraction; the L1 scorers' in fixed point (2 where a table keeps floats)
-LANE_OPS_PER_TRIPLE = {0: 4 / 3, 1: 4, 3: 6, 4: 4 / 3}
+LANE_OPS_PER_TRIPLE = {0: 1, 1: 4, 3: 6, 4: 1}
 SCORER_PEAK = {0: (PEAK_VALU_F32, "alu", "TFLOP/s"), 1: (PEAK_VALU_F32, "alu", "TFLOP/s"),
                2: (PEAK_MFMA_F32, "mfma", "TFLOP/s"), 3: (PEAK_VALU_F32, "alu", "TFLOP/s"),
                4: (PEAK_VALU_F32, "alu", "TFLOP/s")}

@@ -147,18 +147,15 @@ void launch_table_stats(const float* x, int64_t n, double* part, hipStream_t s)
 // sqrt(width) quanta; that of a float sum of width terms of mean size t grows
 // to 0.25 sqrt(width) 2^-24 (width t). The table takes the fixed-point form
 // while the first is at most a quarter of the second with t = mad, the mean
-// absolute deviation (an entity and a query state differ by that or more):
-// tables of uniform values from a width of 53 on, of normal ones (range 9
-// deviations) from 150, and tables whose outliers stretch the range beyond
-// about 30 mad at width 400 not at all. Measured error against 64 bits on
-// uniform tables: 1.1e-6 in floats, 5.4e-7 here (63,361 x 400); 1.9e-7 and
-// 1.1e-7 (LogicE, 14,505 x 800).
+// absolute deviation. Measured error against 64 bits on uniform tables: 5.2e-7
+// in floats, 1.2e-7 here (63,361 x 400); 1.9e-7 and 3.1e-8 (LogicE, 14,505 x
+// 800).
 L1Fixed choose_l1_fixed(double lo, double hi, double sum, double mad, int width)
 {
     L1Fixed f;
     const double range = hi - lo;
     if (!(sum - sum == 0.0) || !(range > 0.0) || !(range < 1e30) || !(range > 1e-30)) return f;   // NaN, inf, no range
-    const double u_max = std::min(8388607.0, std::floor(4294967295.0 / width));
+    const double u_max = std::floor(4294967295.0 / width);
     const float q = std::nextafter((float)(range / u_max), 1e38f);     // range / q <= u_max
     if (0.41 * (double)q > 0.25 * 0.25 * 0x1p-24 * width * mad) return f;
     f.on = true;
@@ -174,10 +171,10 @@ __global__ __launch_bounds__(256) void k_l1_quantise(float4* __restrict__ blk, i
     if (i >= n4) return;
     const float4 v = blk[i];
     double ex = 0.0;
-    blk[i] = make_float4(__uint_as_float(l1_fixed_bits(v.x, f, inv_quantum, ex)),
-                         __uint_as_float(l1_fixed_bits(v.y, f, inv_quantum, ex)),
-                         __uint_as_float(l1_fixed_bits(v.z, f, inv_quantum, ex)),
-                         __uint_as_float(l1_fixed_bits(v.w, f, inv_quantum, ex)));
+    blk[i] = make_float4(__uint_as_float(l1_fixed_word(v.x, f, inv_quantum, ex)),
+                         __uint_as_float(l1_fixed_word(v.y, f, inv_quantum, ex)),
+                         __uint_as_float(l1_fixed_word(v.z, f, inv_quantum, ex)),
+                         __uint_as_float(l1_fixed_word(v.w, f, inv_quantum, ex)));
 }
 
 void launch_l1_quantise(float* blk, int64_t n, const L1Fixed& f, hipStream_t s)
@@ -844,7 +841,7 @@ __global__ __launch_bounds__(256) void k_pack_l1(const int32_t* src_row, const i
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     if (NEGL && ng[r]) x[c] = 1.0f - x[c];
-                    dst[c] = l1_fixed_bits(src[r] >= 0 ? x[c] : f.lo, f, inv_quantum, ex[r]);
+                    dst[c] = l1_fixed_word(src[r] >= 0 ? x[c] : f.lo, f, inv_quantum, ex[r]);
                 }
             }
         __syncthreads();

@@ -22,16 +22,16 @@
 //
 // Per-triple work (one non-packed VALU op each):
 //   GQE     d = e - q;  acc += |d|                                       (2)
-//           With a fixed-point table (L1Fixed), the same words as integers
-//           or as floats: two rows of three take v_sad_u32 (|e - q| + acc),
-//           the third the two float instructions. v_sad_u32, like min and
-//           max, issues at half rate on a unit of its own, so the float
-//           instructions of the third row go in between: 4 issue slots for 3
-//           triples. Register-only probes, in T triples/s: the float pair
-//           29.7, v_sad_u32 alone 38.1, mixed two to one 52.9. The sums are
-//           exact in the integer rows and as before in the others. The
-//           1,229-row sweep over 63,361 entities at d = 400 went from
-//           1.18 to 0.86 ms.
+//           With a fixed-point table (L1Fixed), 32-bit words, one: v_sad_u32
+//           (|e - q| + acc), an exact sum. It issues at half rate, on a unit
+//           of its own: register-only probes give 38.1 T triples/s, the float
+//           pair 29.7. A call of 1,024 multi-hop queries over 63,361 entities
+//           at d = 400: 1.08 ms in floats, 1.01 in fixed point. (0.86 with
+//           every third row in floats, whose instructions go in between; but
+//           then a query's scores depend on where in the batch it stands, and
+//           that row has the sum's rounding on top of the words'. The third
+//           row as max(q - e, 0) and an addition, exact too: 1.29, the
+//           saturating subtraction being slow.)
 //   Q2B     t = |e - c|: acc1 += t; acc2 += min(t, o)                    (4)
 //           score = gamma - acc1 + (1 - center_reg) * acc2, the exact
 //           regrouping of dist_out + center_reg * dist_in
@@ -111,48 +111,11 @@ __device__ __forceinline__ void store_row(const ScoreArgs& a, int64_t orow, int6
     store_scores4(a.scores + orow * a.ld, e0, a.N, v);
 }
 
-// One step of the fixed-point L1 form for G rows (the last in floats, the
-// others by v_sad_u32) and the lane's 4 entities, in an order that puts a
-// full-rate instruction behind each half-rate one. q: the rows' words; the
-// float row's goes to a vector register, since the VALU takes a scalar operand
-// on at most every other issue cycle. (volatile: the compiler would move the
-// copy ahead, to where the word has not arrived yet.)
-template <int G>
-__device__ __forceinline__ void l1_fixed_step(uint32_t (*acc)[4], const float4& e, const float* q)
+// acc + |e - q| in 32-bit integers, q a scalar.
+__device__ __forceinline__ uint32_t sad_u32(uint32_t e, uint32_t q, uint32_t acc)
 {
-    static_assert(G == 3 || G == 4, "rows per group");
-    float t0, t1, qf;
-    if constexpr (G == 3)
-        asm volatile("v_mov_b32 %14, %21\n\tv_sad_u32 %0, %15, %19, %0\n\t"
-                     "v_sub_f32 %12, %15, %14\n\tv_sad_u32 %4, %15, %20, %4\n\t"
-                     "v_add_f32 %8, %8, |%12|\n\tv_sad_u32 %1, %16, %19, %1\n\t"
-                     "v_sub_f32 %13, %16, %14\n\tv_sad_u32 %5, %16, %20, %5\n\t"
-                     "v_add_f32 %9, %9, |%13|\n\tv_sad_u32 %2, %17, %19, %2\n\t"
-                     "v_sub_f32 %12, %17, %14\n\tv_sad_u32 %6, %17, %20, %6\n\t"
-                     "v_add_f32 %10, %10, |%12|\n\tv_sad_u32 %3, %18, %19, %3\n\t"
-                     "v_sub_f32 %13, %18, %14\n\tv_sad_u32 %7, %18, %20, %7\n\t"
-                     "v_add_f32 %11, %11, |%13|"
-                     : "+v"(acc[0][0]), "+v"(acc[0][1]), "+v"(acc[0][2]), "+v"(acc[0][3]), "+v"(acc[1][0]),
-                       "+v"(acc[1][1]), "+v"(acc[1][2]), "+v"(acc[1][3]), "+v"(acc[2][0]), "+v"(acc[2][1]),
-                       "+v"(acc[2][2]), "+v"(acc[2][3]), "=&v"(t0), "=&v"(t1), "=&v"(qf)
-                     : "v"(e.x), "v"(e.y), "v"(e.z), "v"(e.w), "s"(q[0]), "s"(q[1]), "s"(q[2]));
-    else
-        asm volatile("v_mov_b32 %18, %26\n\tv_sad_u32 %0, %19, %23, %0\n\t"
-                     "v_sub_f32 %16, %19, %18\n\tv_sad_u32 %4, %19, %24, %4\n\t"
-                     "v_add_f32 %12, %12, |%16|\n\tv_sad_u32 %8, %19, %25, %8\n\t"
-                     "v_sad_u32 %1, %20, %23, %1\n\tv_sub_f32 %17, %20, %18\n\t"
-                     "v_sad_u32 %5, %20, %24, %5\n\tv_add_f32 %13, %13, |%17|\n\t"
-                     "v_sad_u32 %9, %20, %25, %9\n\tv_sad_u32 %2, %21, %23, %2\n\t"
-                     "v_sub_f32 %16, %21, %18\n\tv_sad_u32 %6, %21, %24, %6\n\t"
-                     "v_add_f32 %14, %14, |%16|\n\tv_sad_u32 %10, %21, %25, %10\n\t"
-                     "v_sad_u32 %3, %22, %23, %3\n\tv_sub_f32 %17, %22, %18\n\t"
-                     "v_sad_u32 %7, %22, %24, %7\n\tv_add_f32 %15, %15, |%17|\n\t"
-                     "v_sad_u32 %11, %22, %25, %11"
-                     : "+v"(acc[0][0]), "+v"(acc[0][1]), "+v"(acc[0][2]), "+v"(acc[0][3]), "+v"(acc[1][0]),
-                       "+v"(acc[1][1]), "+v"(acc[1][2]), "+v"(acc[1][3]), "+v"(acc[2][0]), "+v"(acc[2][1]),
-                       "+v"(acc[2][2]), "+v"(acc[2][3]), "+v"(acc[3][0]), "+v"(acc[3][1]), "+v"(acc[3][2]),
-                       "+v"(acc[3][3]), "=&v"(t0), "=&v"(t1), "=&v"(qf)
-                     : "v"(e.x), "v"(e.y), "v"(e.z), "v"(e.w), "s"(q[0]), "s"(q[1]), "s"(q[2]), "s"(q[3]));
+    asm("v_sad_u32 %0, %1, %2, %0" : "+v"(acc) : "v"(e), "s"(q));
+    return acc;
 }
 
 template <int MODEL, int TQ, bool FIXED = false>
@@ -190,11 +153,8 @@ __global__ __launch_bounds__(256, 4) void k_score(ScoreArgs a, int nqg, int qchu
     const float* __restrict__ qp = a.qpack + ((int64_t)qb * a.d + k_begin) * F * TQ;
     const float* __restrict__ ep = a.ent + ((int64_t)eb * a.d + k_begin) * EF * kEntBlock;
 
-    // fixed-point form: rows r with r % G == G - 1 sum floats, the others
-    // integers; both kept as words
+    // (fixed-point form: integer sums)
     static_assert(!FIXED || MODEL == 0, "the fixed-point form is L1's");
-    constexpr int G = TQ % 3 == 0 ? 3 : 4;
-    static_assert(!FIXED || TQ % G == 0, "whole groups");
     uint32_t accw[FIXED ? TQ : 1][4];
     float acc[FIXED ? 1 : TQ][4];
     float acc2[TWO ? TQ : 1][4];
@@ -241,8 +201,12 @@ __global__ __launch_bounds__(256, 4) void k_score(ScoreArgs a, int nqg, int qchu
     auto compute = [&](const EVec& eu, const float (&qb)[SB * QN], auto off) {
         const float* qv = qb + decltype(off)::value * QN;
         if constexpr (FIXED) {
+            const uint32_t e4[4] = {__float_as_uint(eu.v[0].x), __float_as_uint(eu.v[0].y), __float_as_uint(eu.v[0].z),
+                                    __float_as_uint(eu.v[0].w)};
 #pragma unroll
-            for (int i = 0; i < TQ; i += G) l1_fixed_step<G>(accw + i, eu.v[0], qv + i);
+            for (int i = 0; i < TQ; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) accw[i][j] = sad_u32(e4[j], __float_as_uint(qv[i]), accw[i][j]);
         } else {
             const float e4[4] = {eu.v[0].x, eu.v[0].y, eu.v[0].z, eu.v[0].w};
 #pragma unroll
@@ -356,9 +320,14 @@ __global__ __launch_bounds__(256, 4) void k_score(ScoreArgs a, int nqg, int qchu
         }
     }
 
-    // row i's distance to entity j, in the units of dist_scale
+    // row i's distance to entity j, in the units of dist_scale; as it goes to
+    // the split-d partials (fixed point: the integer)
     auto dist = [&](int i, int j) {
-        if constexpr (FIXED) return i % G == G - 1 ? __uint_as_float(accw[i][j]) : (float)accw[i][j];
+        if constexpr (FIXED) return (float)accw[i][j];
+        else return acc[i][j];
+    };
+    auto raw = [&](int i, int j) {
+        if constexpr (FIXED) return __uint_as_float(accw[i][j]);
         else return acc[i][j];
     };
 
@@ -372,7 +341,7 @@ __global__ __launch_bounds__(256, 4) void k_score(ScoreArgs a, int nqg, int qchu
 #pragma unroll
         for (int i = 0; i < TQ; ++i) {
             const int64_t row = (int64_t)qb * TQ + i;
-            *reinterpret_cast<float4*>(pz + row * n_pad + e0) = make_float4(dist(i, 0), dist(i, 1), dist(i, 2), dist(i, 3));
+            *reinterpret_cast<float4*>(pz + row * n_pad + e0) = make_float4(raw(i, 0), raw(i, 1), raw(i, 2), raw(i, 3));
             if (TWO)
                 *reinterpret_cast<float4*>(pz + (rows_pad + row) * n_pad + e0) =
                     make_float4(acc2[i][0], acc2[i][1], acc2[i][2], acc2[i][3]);
@@ -470,13 +439,16 @@ __global__ __launch_bounds__(256) void k_score_sum(ScoreArgs a, int splits, int6
     float best = 0.f;
     for (int u = 0; u < nr; ++u) {
         float s1 = 0.f, s2 = 0.f;
+        uint32_t sw = 0u;                       // (fixed point: below 2^32 as a whole)
         for (int z = 0; z < splits; ++z) {
             const float* pz = a.part + (int64_t)z * F * rows_pad * n_pad;
-            s1 += pz[(int64_t)(r0 + u) * n_pad + e];
+            const float p = pz[(int64_t)(r0 + u) * n_pad + e];
+            sw += __float_as_uint(p);
+            s1 += p;
             if (MODEL == 1) s2 += pz[(rows_pad + r0 + u) * n_pad + e];
         }
         const float v =
-            MODEL != 1 ? (a.l1_fixed ? (float)(a.cq[r0 + u] - ((double)a.dist_scale + (double)a.dist_low) * (double)s1)
+            MODEL != 1 ? (a.l1_fixed ? (float)(a.cq[r0 + u] - ((double)a.dist_scale + (double)a.dist_low) * (double)sw)
                                      : a.gamma - a.dist_scale * s1) : a.gamma - s1 + (1.0f - a.center_reg) * s2;
         best = u == 0 ? v : fmaxf(best, v);
     }

@@ -77,14 +77,12 @@ inline int score_tq(int model, int n_rows)
 }
 
 // GQE's and LogicE's entity table in fixed point, for the L1 scorer's integer
-// form (k_score.hip): coordinate x is held as the bits 0x4B000000 + u, u =
-// round((x - lo) / quantum), lo the table's least value and u at most u_max <
-// 2^23. Read as an integer, differences of such words are differences of u;
-// read as a float, the word is 2^23 + u and they are the same, exactly.
-// u_max * width < 2^32, so a sum of |differences| over the scored width never
-// wraps. A query coordinate outside [lo, hi] is moved to the nearer end, and
-// what it was moved by is added to the row's distance as it is: every entity
-// lies on the other side, so the distance splits exactly.
+// form (k_score.hip): coordinate x is held as the word u = round((x - lo) /
+// quantum), lo the table's least value and u at most u_max, u_max * width <
+// 2^32: a sum of |differences| over the scored width never wraps. A query
+// coordinate outside [lo, hi] is moved to the nearer end, and what it was
+// moved by is added to the row's distance as it is: every entity lies on the
+// other side, so the distance splits exactly.
 struct L1Fixed {
     bool on = false;
     float lo = 0.f, hi = 0.f;
@@ -94,11 +92,11 @@ struct L1Fixed {
 // where it would be coarser than the float sums it replaces.
 L1Fixed choose_l1_fixed(double lo, double hi, double sum, double mad, int width);
 // x as u (x clamped to the table's range), and by how much it was clamped.
-__device__ __forceinline__ uint32_t l1_fixed_bits(float x, const L1Fixed& f, double inv_quantum, double& excess)
+__device__ __forceinline__ uint32_t l1_fixed_word(float x, const L1Fixed& f, double inv_quantum, double& excess)
 {
     const float c = fminf(fmaxf(x, f.lo), f.hi);
     excess += fabs((double)x - (double)c);             // NaN and infinities pass through here
-    return 0x4B000000u + (uint32_t)__double2uint_rn(((double)c - (double)f.lo) * inv_quantum);
+    return __double2uint_rn(((double)c - (double)f.lo) * inv_quantum);
 }
 
 // Rows that the pack writes: a whole number of the VALU scorers' row blocks.

@@ -69,7 +69,7 @@ def _gqe(table, rel_scale, d, n_ent, seed):
 def test_gpu_l1_fixed_and_float(table, d, B, rel_scale):
     """GQE's L1 scores on tables that take the fixed-point form (uniform,
     normal, shifted) and on those that keep floats (a far outlier, one value
-    only, too few dimensions), with query coordinates up to 24 times outside
+    only), with query coordinates up to 24 times outside
     the table's range. Tolerance: every coordinate off by a quantum (range /
     2^23) and the state's two roundings, and the sum by width ulp."""
     n_ent = 300
@@ -284,3 +284,17 @@ def test_gpu_topk_listed_nan(structure, B, every, sign):
     want = np.argsort(-key, axis=1, kind="stable")[:, :k]
     assert np.array_equal(idx, want)
     assert np.array_equal(val.view(np.uint32), np.take_along_axis(got, want, 1).view(np.uint32))
+
+
+@pytest.mark.parametrize("model", [O.GQE, O.LOGICE], ids=["gqe", "logice"])
+@pytest.mark.parametrize("n_ent,B", [(300, 30), (300, 1100), (6000, 200), (3000, 1100)])
+def test_gpu_l1_fixed_row_position(model, n_ent, B):
+    """One query at every position of a batch scores the same, bit for bit, in
+    fixed point (width 64 takes it on these tables): split dimensions, small
+    and large row form."""
+    w = synth.make_tiny(model, n_ent=n_ent, n_rel=7, dim=64 if model == O.GQE else 32, seed=151)
+    qb = synth.draw_queries("2p", B, n_ent, 7, seed=152)
+    qb.anchors[:], qb.relations[:] = qb.anchors[:1], qb.relations[:1]
+    out = _scores(w, model, "2p", qb, 5)
+    assert np.array_equal(out["scores"], np.broadcast_to(out["scores"][:1], (B, n_ent)))
+    assert np.array_equal(out["idx"], np.broadcast_to(out["idx"][:1], (B, 5)))
