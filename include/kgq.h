@@ -168,8 +168,12 @@ kgq_status kgq_create(const kgq_config* cfg, kgq_handle** out);
  * by columns for LogicE's concatenated input; the layer is linear in its
  * input, Eq. 4), rebuilt when the entity table, "relation", "proj.w1" or
  * "proj.b1" is loaded and all four are present; GQE's and LogicE's entity
- * coordinates as fixed-point words where their range and spread allow it
- * (chosen by the table's values); and every dense weight, and BetaE's
+ * coordinates, for scoring, as 32-bit fixed-point words of (the table's range)
+ * x width / 2^32 where the error that leaves in a score, at any distance, is
+ * at most a quarter of the float32 rounding of a score near gamma (width: the
+ * scored coordinates; chosen by the table's least and largest value and by
+ * gamma; entities closer than that to each other may then score equal, as they
+ * mostly do by the score's rounding); and every dense weight, and BetaE's
  * entity-side scoring rows, in the parts that the matrix-core paths read
  * (kgq_set_dense_path).
  * Errors: INVALID_ARG (unknown name, wrong nbytes or dtype, null src), OOM, DEVICE. */

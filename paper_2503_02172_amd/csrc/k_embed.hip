@@ -113,51 +113,43 @@ __global__ __launch_bounds__(256) void k_table_range(const float4* __restrict__ 
     }
     sum = block_sum(sum);
     if (threadIdx.x == 0) {
-        double* o = part + 4 * blockIdx.x;
+        double* o = part + 3 * blockIdx.x;
         o[0] = fminf(fminf(sh_lo[0], sh_lo[1]), fminf(sh_lo[2], sh_lo[3]));
         o[1] = fmaxf(fmaxf(sh_hi[0], sh_hi[1]), fmaxf(sh_hi[2], sh_hi[3]));
         o[2] = sum;
     }
 }
 
-__global__ __launch_bounds__(256) void k_table_deviation(const float4* __restrict__ x, int64_t n4,
-                                                         double* __restrict__ part)
-{
-    double mean = 0.0;
-    for (int b = threadIdx.x; b < kStatBlocks; b += 256) mean += part[4 * b + 2];
-    mean = block_sum(mean) / (4.0 * (double)n4);
-    double dev = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)kStatBlocks * 256) {
-        const float4 v = x[i];
-        dev += (fabs((double)v.x - mean) + fabs((double)v.y - mean)) + (fabs((double)v.z - mean) + fabs((double)v.w - mean));
-    }
-    dev = block_sum(dev);
-    if (threadIdx.x == 0) part[4 * blockIdx.x + 3] = dev;
-}
-
 void launch_table_stats(const float* x, int64_t n, double* part, hipStream_t s)
 {
     const float4* x4 = reinterpret_cast<const float4*>(x);
     hipLaunchKernelGGL(k_table_range, dim3(kStatBlocks), dim3(256), 0, s, x4, n / 4, part);
-    hipLaunchKernelGGL(k_table_deviation, dim3(kStatBlocks), dim3(256), 0, s, x4, n / 4, part);
 }
 
-// The quantisation error of a distance, each of its 2 x width values off by
-// at most half a quantum and 0.29 of one at the root mean square, is 0.41
-// sqrt(width) quanta; that of a float sum of width terms of mean size t grows
-// to 0.25 sqrt(width) 2^-24 (width t). The table takes the fixed-point form
-// while the first is at most a quarter of the second with t = mad, the mean
-// absolute deviation. Measured error against 64 bits on uniform tables: 5.2e-7
-// in floats, 1.2e-7 here (63,361 x 400); 1.9e-7 and 3.1e-8 (LogicE, 14,505 x
-// 800).
-L1Fixed choose_l1_fixed(double lo, double hi, double sum, double mad, int width)
+// A score is gamma - scale * distance in float32. The quantisation error of a
+// distance, each of its 2 x width values off by at most half a quantum and 0.29
+// of one at the root mean square, is 0.41 sqrt(width) quanta at every distance.
+// A score near gamma, of an entity that all but coincides with the query, is
+// rounded by 0.29 ulp, at least 0.29 x 2^-24 gamma, and further away the float
+// sum's own error, 0.25 sqrt(width) 2^-24 of the distance, soon exceeds that.
+// So the table takes the fixed-point form where the quantisation error is at
+// most a quarter of the rounding at gamma: however near the entities are to
+// each other or to the query, the score's error then grows by 3% at most, and
+// from a distance of about gamma / 50 on it is below the float form's.
+// Uniform tables of half width gamma / width take it up to a width of 500
+// (GQE; LogicE at gamma = 1 up to 2,000); a wider range, or one stretched by
+// outliers or by columns of different centres, doesn't. Measured error against
+// 64 bits on uniform tables: 5.2e-7 in floats, 1.2e-7 here (63,361 x 400);
+// 1.9e-7 and 3.1e-8 (LogicE, 14,505 x 800).
+L1Fixed choose_l1_fixed(double lo, double hi, double sum, int width, double gamma, double scale)
 {
     L1Fixed f;
     const double range = hi - lo;
     if (!(sum - sum == 0.0) || !(range > 0.0) || !(range < 1e30) || !(range > 1e-30)) return f;   // NaN, inf, no range
     const double u_max = std::floor(4294967295.0 / width);
     const float q = std::nextafter((float)(range / u_max), 1e38f);     // range / q <= u_max
-    if (0.41 * (double)q > 0.25 * 0.25 * 0x1p-24 * width * mad) return f;
+    const double error = 0.41 * std::sqrt((double)width) * (double)q * scale;
+    if (!(error <= 0.25 * 0.29 * 0x1p-24 * std::fabs(gamma))) return f;
     f.on = true;
     f.lo = (float)lo;
     f.hi = (float)hi;

@@ -1340,22 +1340,20 @@ static kgq_status build_proj1(kgq_handle* h)
 
 // GQE / LogicE: choose the scoring table's form from its values, and bring
 // it into fixed point where that is the one. `part`: device scratch of
-// kStatBlocks x 4 doubles.
+// kStatBlocks x 3 doubles.
 static hipError_t fix_points(kgq_handle* h, int width, void* part)
 {
-    const int64_t n = h->cfg.n_entities * width;
-    double p[4 * kStatBlocks];
-    launch_table_stats(h->ent_rm, n, static_cast<double*>(part), nullptr);
+    double p[3 * kStatBlocks];
+    launch_table_stats(h->ent_rm, h->cfg.n_entities * width, static_cast<double*>(part), nullptr);
     const hipError_t e = hipMemcpy(p, part, sizeof(p), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return e;
-    double lo = p[0], hi = p[1], sum = 0.0, dev = 0.0;
+    double lo = p[0], hi = p[1], sum = 0.0;
     for (int b = 0; b < kStatBlocks; ++b) {
-        lo = std::min(lo, p[4 * b]);
-        hi = std::max(hi, p[4 * b + 1]);
-        sum += p[4 * b + 2];
-        dev += p[4 * b + 3];
+        lo = std::min(lo, p[3 * b]);
+        hi = std::max(hi, p[3 * b + 1]);
+        sum += p[3 * b + 2];
     }
-    h->l1 = choose_l1_fixed(lo, hi, sum, dev / (double)n, width);
+    h->l1 = choose_l1_fixed(lo, hi, sum, width, h->cfg.gamma, h->cfg.model == KGQ_LOGICE ? 1.0 / width : 1.0);
     if (h->l1.on) launch_l1_quantise(h->ent_blk, h->n_blocks * kEntBlock * width, h->l1, nullptr);
     return hipSuccess;
 }
@@ -1435,7 +1433,7 @@ kgq_status kgq_load_params(kgq_handle* h, const char* name, const void* src, siz
     }
     // entity table: stage, then build the derived layouts
     void* stage = nullptr;
-    hipError_t e = hipMalloc(&stage, std::max(nbytes, (size_t)kStatBlocks * 4 * sizeof(double)));
+    hipError_t e = hipMalloc(&stage, std::max(nbytes, (size_t)kStatBlocks * 3 * sizeof(double)));
     if (e != hipSuccess) return fail(h, KGQ_E_OOM, "staging buffer for the entity table");
     e = hipMemcpy(stage, src, nbytes, kind);
     if (e == hipSuccess) {

@@ -88,9 +88,10 @@ struct L1Fixed {
     float lo = 0.f, hi = 0.f;
     float quantum = 0.f;
 };
-// The fixed-point form of a table of n coordinates (rows of `width`), or off
-// where it would be coarser than the float sums it replaces.
-L1Fixed choose_l1_fixed(double lo, double hi, double sum, double mad, int width);
+// The fixed-point form of a table with values in [lo, hi] (their sum tells a
+// NaN), scored over `width` coordinates as gamma - scale * distance; off where
+// its words would be too coarse beside the score's own rounding.
+L1Fixed choose_l1_fixed(double lo, double hi, double sum, int width, double gamma, double scale);
 // x as u (x clamped to the table's range), and by how much it was clamped.
 __device__ __forceinline__ uint32_t l1_fixed_word(float x, const L1Fixed& f, double inv_quantum, double& excess)
 {
@@ -208,8 +209,8 @@ __device__ __forceinline__ float apply_epilogue(int epi, int split, int n, float
 void launch_relayout_points(const void* src, int src_bf16, int64_t N, int d, int64_t n_blocks,
                             float* rowmajor, float* blocked, hipStream_t s);
 
-// Least and largest value, sum, and sum of |x - mean| of x[0 .. n), n a
-// multiple of 4: [kStatBlocks x 4] doubles, one part per workgroup.
+// Least and largest value and sum of x[0 .. n), n a multiple of 4:
+// [kStatBlocks x 3] doubles, one part per workgroup.
 constexpr int kStatBlocks = 512;
 void launch_table_stats(const float* x, int64_t n, double* part, hipStream_t s);
 // Blocked scoring table to fixed-point words, in place (n a multiple of 256).
