@@ -266,15 +266,15 @@ kgq_status kgq_set_checked(kgq_handle* h, int32_t on);
  * MLPs of Eq. 4 and of the intersection operators, and kgq_dense) and
  * BetaE's scoring contraction (the regrouped KL of Eq. 3's embeddings). Both
  * paths compute in FP32 precision class:
- *   KGQ_DENSE_AUTO (the default): BetaE's, ConE's and LogicE's layers (from 16
- *     embedding dimensions on) run on the f16 matrix cores at every size: each
+ *   KGQ_DENSE_AUTO (the default): BetaE's, ConE's and LogicE's layers (from 32
+ *     embedding dimensions on; below, on the FP32 matrix cores) run on the f16 matrix cores at every size: each
  *     FP32 row, of the weights and of the layer's input, is scaled by a power
  *     of two and split into two f16 parts, and three of the four part products
  *     are kept (error 2^-22 of each product, in the class of the FP32 sum;
  *     values more than 2^27 below a bound of their row's largest lose
- *     precision against it). BetaE scores the same way when the call has more
- *     than 256 tiles of 64 scored rows x 64 entities; smaller calls score on
- *     the FP32 matrix cores.
+ *     precision against it). BetaE scores the same way (from 16 dimensions on)
+ *     when the call has more than 256 tiles of 64 scored rows x 64 entities;
+ *     smaller calls score on the FP32 matrix cores.
  *     GQE's and Query2Box's layers and kgq_dense, with K >= 32 (K is a multiple
  *     of 4 on every path) and at least 384 output tiles of 64 x 64, or 1,024
  *     rows and 192 such tiles, run on the bf16 matrix cores, each FP32 operand

@@ -346,8 +346,8 @@ int64_t qpack_row_floats(int model, int d)
 
 // Floats of a row of `width` values that may be in split form (whole stages),
 // and of the widest dense-layer row.
-int64_t split_row_floats(int width) { return width >= kSplitDim ? plane_ld(width) : width; }
-int64_t mlp_row_floats(int d) { return d >= kSplitDim ? plane_ld(4 * d) : 4 * d; }
+int64_t split_row_floats(int width) { return width >= kSplitLayerDim ? plane_ld(width) : width; }
+int64_t mlp_row_floats(int d) { return d >= kSplitLayerDim ? plane_ld(4 * d) : 4 * d; }
 
 // The dense-layer buffers that live in h2's rows: a layer's input x is dead
 // once its first layer has run, before h2 is written; an intersection writes no
@@ -398,7 +398,7 @@ kgq_status allocate_all(kgq_handle* h)
     }
     // one piece of memory for a weight's split form: rows, scales, bound
     auto split_weight = [&](const float* of, int64_t rows, int64_t cols) -> kgq_status {
-        if (d < kSplitDim) return KGQ_OK;
+        if (d < kSplitLayerDim) return KGQ_OK;
         kgq_handle::SplitWeight w;
         ALLOC(w.rows, rows * plane_ld(cols) + rows + 2);
         w.scale = w.rows + rows * plane_ld(cols);
@@ -660,7 +660,7 @@ kgq_status run_plan(kgq_handle* h, Lane& L, const Plan& p, const int32_t* P, con
     };
 
     // the f16 form of a layer: rows x in split form, weights named by `w`
-    const bool split_mlp = mlp_model(c.model) && d >= kSplitDim && h->dense_path != KGQ_DENSE_FP32;
+    const bool split_mlp = mlp_model(c.model) && d >= kSplitLayerDim && h->dense_path != KGQ_DENSE_FP32;
     auto split_gemm = [&](const float* x, int64_t ldx, const float* xs, const float* w, const float* bias, float* y,
                           int64_t ldy, const int32_t* rowmap, SplitRows out, int M, int Nn, int K, int epi) {
         const kgq_handle::SplitWeight& sw = h->wsplit.at(w);

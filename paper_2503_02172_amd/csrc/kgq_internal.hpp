@@ -189,9 +189,16 @@ struct SplitRows {
     float* scale = nullptr;
 };
 
-// Embedding dimensions from which the split forms are used: below, rows padded
-// to whole stages hold more padding than values.
+// Embedding dimensions from which BetaE's scorer takes the split form: below,
+// rows padded to whole stages hold more padding than values. (Its contraction
+// of 2d positive terms is nearer to 64 bits than the FP32 one from there on.)
 constexpr int kSplitDim = 16;
+// And the dense layers: a product's dropped part, 2^-22 of it, costs more than
+// the fewer roundings of the sum give back while sums are short. BetaE's three
+// projection layers, relative error in FP32 | split form: d = 16 1.3e-7 |
+// 1.5e-7, 24 1.4e-7 | 1.6e-7, 32 1.7e-7 | 1.6e-7, 64 2.3e-7 | 1.6e-7, 400
+// 5.5e-7 | 2.4e-7.
+constexpr int kSplitLayerDim = 32;
 
 // Epilogue value of output column n.
 __device__ __forceinline__ float apply_epilogue(int epi, int split, int n, float v)

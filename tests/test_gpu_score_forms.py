@@ -233,7 +233,7 @@ def test_gpu_betae_split_scorer(structure, n_ent, d, B, wide):
 
 
 @pytest.mark.parametrize("model", [O.BETAE, O.CONE, O.LOGICE], ids=["betae", "cone", "logice"])
-@pytest.mark.parametrize("structure,d,B", [("2p", 16, 1), ("pni", 20, 16), ("2p", 36, 17), ("pni", 52, 32),
+@pytest.mark.parametrize("structure,d,B", [("2p", 32, 1), ("pni", 44, 16), ("2p", 36, 17), ("pni", 52, 32),
                                            ("pni", 36, 33), ("2p", 268, 32), ("2p", 52, 129), ("2p", 400, 512),
                                            ("2p", 400, 1990), ("2p", 128, 4100), ("2p", 128, 12289)])
 def test_gpu_split_layers(model, structure, d, B):

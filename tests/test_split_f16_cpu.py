@@ -7,7 +7,9 @@ brings the largest into [2^14, 2^15): with h = f16(x) and l = f16((x - h)
 2^-28 of the row's largest value, and to 2^-50 of the largest below; the
 three kept part products miss a product by less than 2^-21 of it; and the
 contraction of rows of positive values, summed in float32 over stages of 32,
-is no further from 64 bits than the six-product bf16 form's."""
+is no further from 64 bits than the six-product bf16 form's; nor is a chain of
+dense layers further than float32's, from the dimensions on where the layers
+take the form."""
 
 import numpy as np
 import pytest
@@ -88,3 +90,67 @@ def test_positive_contraction_no_further_off_than_bf16x3(K):
     old = staged([(xh, yh, 0), (xh, ym, 0), (xm, yh, 0), (xm, ym, 0), (xh, yl, 0), (xl, yh, 0)])[0]
     rms = lambda x: np.sqrt(np.mean(((x.astype(np.float64) - ref) / ref) ** 2))
     assert rms(new) <= rms(old), (rms(new), rms(old))
+
+
+def split_rows(x):
+    s = np.array([scale_of(r) for r in np.abs(x).max(1)])
+    parts = [split2(r, q) for r, q in zip(x, s)]
+    return np.stack([p[1] for p in parts]).astype(np.float64), np.stack([p[3] for p in parts]).astype(np.float64), s
+
+
+def layer(x, w, b, bounded, relu):
+    """One layer on split rows x = (h, l, scale) as the kernel does it, its
+    output in float32, or split again under the scale of its bound."""
+    (xh, xl, xs), (wh, wl, ws) = x, split_rows(w)
+    hi = np.zeros((len(xh), len(w)), np.float32)
+    lo = hi.copy()
+    for k in range(0, xh.shape[1], 32):
+        s = slice(k, k + 32)
+        hi = (hi + xh[:, s] @ wh[:, s].T).astype(np.float32)
+        lo = (lo + xh[:, s] @ wl[:, s].T).astype(np.float32)
+        lo = (lo + xl[:, s] @ wh[:, s].T).astype(np.float32)
+    y = ((hi + lo * np.float32(1 / 2048)) * (xs[:, None] * ws[None]) + b).astype(np.float32)
+    y = np.maximum(y, 0) if relu else y
+    if not bounded:
+        return y
+    bound = xs * np.float32(32768) * np.abs(w).sum(1).max() + np.float32(max(b.max(), 0))
+    s = np.array([scale_of(v) for v in bound])
+    parts = [split2(r, q) for r, q in zip(y, s)]
+    return np.stack([p[1] for p in parts]).astype(np.float64), np.stack([p[3] for p in parts]).astype(np.float64), s
+
+
+def layer32(x, w, b, relu):
+    acc = np.zeros((len(x), len(w)), np.float32)
+    for k in range(0, x.shape[1], 4):                # v_mfma_f32_16x16x4_f32
+        acc = (acc + x[:, k:k + 4].astype(np.float64) @ w[:, k:k + 4].T.astype(np.float64)).astype(np.float32)
+    y = (acc + b).astype(np.float32)
+    return np.maximum(y, 0) if relu else y
+
+
+def projection(g, d, factors=(1.0, 1.0)):
+    """Errors of BetaE's three projection layers, (split, float32), with one
+    unit of each hidden layer scaled by a factor and switched off."""
+    def make(o, i):
+        lim = np.sqrt(6.0 / (o + i))
+        return g.uniform(-lim, lim, (o, i)).astype(np.float32), (g.uniform(-1, 1, o) / np.sqrt(i)).astype(np.float32)
+    x = (np.maximum(g.uniform(0, 2, (48, 2 * d)), 0.05) + g.uniform(-0.5, 0.5, (48, 2 * d))).astype(np.float32)
+    ws = [make(4 * d, 2 * d), make(4 * d, 4 * d), make(2 * d, 4 * d)]
+    for (w, b), f in zip(ws, factors):
+        if f > 1:
+            w[3] *= np.float32(f)
+            b[3] = -np.float32(f) * 1000
+    ref, y32, y = x.astype(np.float64), x, split_rows(x)
+    for i, (w, b) in enumerate(ws):
+        ref = ref @ w.T.astype(np.float64) + b
+        ref = np.maximum(ref, 0) if i < 2 else ref
+        y32 = layer32(y32, w, b, i < 2)
+        y = layer(y, w, b, i < 2, i < 2)
+    n = np.linalg.norm
+    return n(y - ref) / n(ref), n(y32 - ref) / n(ref)
+
+
+@pytest.mark.parametrize("d", [32, 64, 200])
+def test_layers_no_further_off_than_float32(d):
+    g = np.random.default_rng(d)
+    split, flt = np.mean([projection(g, d) for _ in range(6)], 0)
+    assert split <= flt, (split, flt)
