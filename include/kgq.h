@@ -267,14 +267,20 @@ kgq_status kgq_set_checked(kgq_handle* h, int32_t on);
  * BetaE's scoring contraction (the regrouped KL of Eq. 3's embeddings). Both
  * paths compute in FP32 precision class:
  *   KGQ_DENSE_AUTO (the default): BetaE's, ConE's and LogicE's layers (from 32
- *     embedding dimensions on; below, on the FP32 matrix cores) run on the f16 matrix cores at every size: each
- *     FP32 row, of the weights and of the layer's input, is scaled by a power
- *     of two and split into two f16 parts, and three of the four part products
- *     are kept (error 2^-22 of each product, in the class of the FP32 sum;
- *     values more than 2^27 below a bound of their row's largest lose
- *     precision against it). BetaE scores the same way (from 16 dimensions on)
- *     when the call has more than 256 tiles of 64 scored rows x 64 entities;
- *     smaller calls score on the FP32 matrix cores.
+ *     embedding dimensions on; below, on the FP32 matrix cores) run on the f16
+ *     matrix cores at every size: each FP32 row, of the weights and of the
+ *     layer's input, is scaled by a power of two and split into two f16 parts,
+ *     each value held to 2^-23 of itself down to 2^-28 of a bound of its row's
+ *     largest and to 2^-50 of that bound below, and three of the four part
+ *     products are kept (error 2^-21 of each product, in the class of the FP32
+ *     sum). The bound of a layer's output comes from the weights' largest row
+ *     sum and bias, so weights are looked at when they are loaded: where a
+ *     hidden unit stands more than 4,096 times above the median one (the
+ *     product over proj.1 and proj.2), or a value is not finite or huge (a row
+ *     sum above 2^20, a bias above 2^40), the handle's layers run on the FP32
+ *     matrix cores. BetaE scores the same way (from 16 dimensions on) when the
+ *     call has more than 256 tiles of 64 scored rows x 64 entities; smaller
+ *     calls score on the FP32 matrix cores.
  *     GQE's and Query2Box's layers and kgq_dense, with K >= 32 (K is a multiple
  *     of 4 on every path) and at least 384 output tiles of 64 x 64, or 1,024
  *     rows and 192 such tiles, run on the bf16 matrix cores, each FP32 operand
@@ -286,9 +292,10 @@ kgq_status kgq_set_checked(kgq_handle* h, int32_t on);
  *     the bounds) on the FP32 matrix cores. Inputs must be finite and below
  *     3.39e38 in magnitude on the bf16 path.
  *   KGQ_DENSE_FP32: every layer and the BetaE scorer on the FP32 matrix cores.
- *   KGQ_DENSE_BF16X3: every layer with K >= 32 on the bf16 path (the f16 path
- *     for the models that take it), and the BetaE scorer on the f16 matrix
- *     cores, whatever the size (for tests).
+ *   KGQ_DENSE_BF16X3: GQE's and Query2Box's layers and kgq_dense with K >= 32
+ *     on the bf16 path, and BetaE's scorer (from 16 dimensions on) on the f16
+ *     matrix cores, whatever the size (for tests); BetaE's, ConE's and
+ *     LogicE's layers as by default.
  * The parts of the weights and of BetaE's entity-side scoring rows are made
  * when they are loaded, whatever the path. Takes effect for calls
  * enqueued after it. Errors: INVALID_ARG. */

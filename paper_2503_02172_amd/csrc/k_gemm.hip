@@ -21,7 +21,9 @@
 // times the work of v_mfma_f32_16x16x4_f32 per cycle, and six of its products
 // per k range reproduce one FP32 product.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
+#include <vector>
 
 #include "kgq_internal.hpp"
 #include "mfma_tile.hpp"
@@ -169,7 +171,7 @@ void launch_split_planes(const float* w, uint16_t* p, int64_t rows, int64_t cols
 
 __global__ __launch_bounds__(256) void k_split_rows(const float* __restrict__ w, int64_t rows, int cols, int64_t ld,
                                                     float* __restrict__ dst, float* __restrict__ scale,
-                                                    float* __restrict__ norm)
+                                                    float* __restrict__ sums)
 {
     const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= rows) return;
@@ -182,38 +184,40 @@ __global__ __launch_bounds__(256) void k_split_rows(const float* __restrict__ w,
             for (int t = 0; t < 8; ++t) x[t] = c * 8 + t < cols ? src[c * 8 + t] : 0.f;
         },
         n8, dst + row * (int64_t)n8 * 8, scale + row, lane);
-    if (norm) {
+    if (sums) {
         float m = 0.f;
         for (int k = lane; k < cols; k += 64) m += fabsf(src[k]);
         for (int off = 32; off > 0; off >>= 1) m += __shfl_xor(m, off, 64);
-        if (lane == 0) atomicMax(reinterpret_cast<unsigned int*>(norm), __float_as_uint(m));   // (bits order as values)
+        if (lane == 0) sums[row] = m;
     }
 }
 
-__global__ void k_zero_word(float* p) { *p = 0.f; }
-
-void launch_split_rows(const float* w, int64_t rows, int64_t cols, int64_t ld, float* dst, float* scale, float* norm,
+void launch_split_rows(const float* w, int64_t rows, int64_t cols, int64_t ld, float* dst, float* scale, float* sums,
                        hipStream_t s)
 {
     if (rows <= 0) return;
-    if (norm) hipLaunchKernelGGL(k_zero_word, dim3(1), dim3(1), 0, s, norm);
     hipLaunchKernelGGL(k_split_rows, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, w, rows, (int)cols, ld, dst,
-                       scale, norm);
+                       scale, sums);
 }
 
-// The largest bias, or 0: what a bias adds to a rectified layer's bound (a
+// What a bias adds to a rectified layer's bound is its largest value, or 0 (a
 // unit switched off by a huge negative bias doesn't widen it).
-__global__ __launch_bounds__(64) void k_bias_max(const float* b, int64_t n, float* out)
+SplitBound split_bound(const float* sums, const float* bias, int64_t n)
 {
-    float m = 0.f;
-    for (int64_t i = threadIdx.x; i < n; i += 64) m = fmaxf(m, b[i]);
-    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    if (threadIdx.x == 0) *out = m;
-}
-
-void launch_bias_max(const float* b, int64_t n, float* out, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_bias_max, dim3(1), dim3(64), 0, s, b, n, out);
+    SplitBound b;
+    std::vector<float> unit((size_t)n);
+    for (int64_t i = 0; i < n; ++i) {
+        const float add = bias ? bias[i] : 0.f;
+        b.fits = b.fits && sums[i] <= kSplitSumMax && std::fabs(add) <= kSplitBiasMax;    // (false for NaN)
+        b.norm = std::max(b.norm, sums[i]);
+        b.bias = std::max(b.bias, add);
+        unit[(size_t)i] = sums[i] + std::max(add, 0.f);
+    }
+    if (!b.fits || n == 0) return b;
+    std::nth_element(unit.begin(), unit.begin() + n / 2, unit.end());
+    const float median = unit[(size_t)(n / 2)], most = *std::max_element(unit.begin(), unit.end());
+    if (most > 0.f) b.spread = most / median;               // (median 0: infinite)
+    return b;
 }
 
 template <int BM, int BN, bool PRIO>

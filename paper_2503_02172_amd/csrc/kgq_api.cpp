@@ -126,9 +126,13 @@ struct kgq_handle {
     struct SplitWeight {
         float* rows = nullptr;
         float* scale = nullptr;
-        float* bound = nullptr;   // {largest row sum of magnitudes, largest bias or 0}
+        float* bound = nullptr;   // SplitBound's {norm, bias}
+        float* sums = nullptr;    // each row's sum of magnitudes
+        std::vector<float> host_sums, host_bias;
+        SplitBound host;
     };
     std::map<const float*, SplitWeight> wsplit;
+    bool split_ok = false;        // the weights suit the split form (split_weights_ok)
     int dense_path = KGQ_DENSE_AUTO;
 
     // structure id -> compiled program: the built-ins for this model, then
@@ -396,13 +400,14 @@ kgq_status allocate_all(kgq_handle* h)
         ALLOC(h->ent_blk, n_pad * d + kEntPad);
         if (c.model == KGQ_Q2B) ALLOC(h->rel_o_sp, (int64_t)c.n_relations * d);
     }
-    // one piece of memory for a weight's split form: rows, scales, bound
+    // one piece of memory for a weight's split form: rows, scales, sums, bound
     auto split_weight = [&](const float* of, int64_t rows, int64_t cols) -> kgq_status {
         if (d < kSplitLayerDim) return KGQ_OK;
         kgq_handle::SplitWeight w;
-        ALLOC(w.rows, rows * plane_ld(cols) + rows + 2);
+        ALLOC(w.rows, rows * plane_ld(cols) + 2 * rows + 2);
         w.scale = w.rows + rows * plane_ld(cols);
-        w.bound = w.scale + rows;
+        w.sums = w.scale + rows;
+        w.bound = w.sums + rows;
         h->wsplit[of] = w;
         return KGQ_OK;
     };
@@ -660,7 +665,7 @@ kgq_status run_plan(kgq_handle* h, Lane& L, const Plan& p, const int32_t* P, con
     };
 
     // the f16 form of a layer: rows x in split form, weights named by `w`
-    const bool split_mlp = mlp_model(c.model) && d >= kSplitLayerDim && h->dense_path != KGQ_DENSE_FP32;
+    const bool split_mlp = mlp_model(c.model) && d >= kSplitLayerDim && h->split_ok && h->dense_path != KGQ_DENSE_FP32;
     auto split_gemm = [&](const float* x, int64_t ldx, const float* xs, const float* w, const float* bias, float* y,
                           int64_t ldy, const int32_t* rowmap, SplitRows out, int M, int Nn, int K, int epi) {
         const kgq_handle::SplitWeight& sw = h->wsplit.at(w);
@@ -1338,6 +1343,18 @@ static kgq_status build_proj1(kgq_handle* h)
     return KGQ_OK;
 }
 
+// Whether the loaded weights suit the split form: each fits, and the spreads of
+// the layers that write split rows, one after the other, stay in its range.
+static bool split_weights_ok(const kgq_handle* h)
+{
+    for (auto& kv : h->wsplit)
+        if (!kv.second.host.fits) return false;
+    auto spread = [&](const float* w) { return h->wsplit.count(w) ? h->wsplit.at(w).host.spread : 1.f; };
+    auto named = [&](const char* n) { return h->dparam.count(n) ? spread(h->dparam.at(n)) : 1.f; };
+    return named("proj.w1") * named("proj.w2") <= kSplitSpreadMax && named("inter.w1") <= kSplitSpreadMax &&
+           spread(h->int_cat_w) <= kSplitSpreadMax;
+}
+
 // GQE / LogicE: choose the scoring table's form from its values, and bring
 // it into fixed point where that is the one. `part`: device scratch of
 // kStatBlocks x 3 doubles.
@@ -1391,23 +1408,39 @@ kgq_status kgq_load_params(kgq_handle* h, const char* name, const void* src, siz
             HIP_TRY(h, hipGetLastError());
             HIP_TRY(h, hipStreamSynchronize(nullptr));
         }
-        auto split = [&](const float* w, int64_t rows, int64_t cols) {
+        // a weight: its form for the matrix cores; with its bias, the bound of
+        // the layer's outputs
+        auto bound = [&](kgq_handle::SplitWeight& w) -> hipError_t {
+            w.host = split_bound(w.host_sums.data(), w.host_bias.empty() ? nullptr : w.host_bias.data(),
+                                 (int64_t)w.host_sums.size());
+            h->split_ok = split_weights_ok(h);
+            const float b[2] = {w.host.norm, w.host.bias};
+            return hipMemcpy(w.bound, b, sizeof(b), hipMemcpyHostToDevice);
+        };
+        auto split = [&](const float* w, int64_t rows, int64_t cols) -> hipError_t {
             auto pl = h->wplanes.find(w);
             auto sw = h->wsplit.find(w);
             if (pl != h->wplanes.end()) launch_split_planes(w, pl->second, rows, cols, nullptr);
-            if (sw != h->wsplit.end())
-                launch_split_rows(w, rows, cols, cols, sw->second.rows, sw->second.scale, sw->second.bound, nullptr);
+            if (sw == h->wsplit.end()) return hipSuccess;
+            kgq_handle::SplitWeight& s = sw->second;
+            launch_split_rows(w, rows, cols, cols, s.rows, s.scale, s.sums, nullptr);
+            s.host_sums.resize((size_t)rows);
+            const hipError_t e = hipMemcpy(s.host_sums.data(), s.sums, (size_t)rows * 4, hipMemcpyDeviceToHost);
+            return e == hipSuccess ? bound(s) : e;
         };
-        split(dst, ps.rows, ps.cols);
-        // a bias: its largest value, for its weight's bound (".b1" -> ".w1")
-        std::string wname = name;
+        auto split_bias = [&](const float* w, const float* b, int64_t n) -> hipError_t {
+            auto sw = h->wsplit.find(w);
+            if (sw == h->wsplit.end()) return hipSuccess;
+            kgq_handle::SplitWeight& s = sw->second;
+            s.host_bias.resize((size_t)n);
+            const hipError_t e = hipMemcpy(s.host_bias.data(), b, (size_t)n * 4, hipMemcpyDeviceToHost);
+            return e == hipSuccess && !s.host_sums.empty() ? bound(s) : e;
+        };
+        HIP_TRY(h, split(dst, ps.rows, ps.cols));
+        std::string wname = name;      // (".b1" -> ".w1")
         const size_t dot = wname.rfind(".b");
         if (dot != std::string::npos) wname[dot + 1] = 'w';
-        auto bound_of_bias = [&](const float* w, const float* b, int64_t n) {
-            auto sw = h->wsplit.find(w);
-            if (sw != h->wsplit.end()) launch_bias_max(b, n, sw->second.bound + 1, nullptr);
-        };
-        if (dot != std::string::npos && h->dparam.count(wname)) bound_of_bias(h->dparam.at(wname), dst, ps.cols);
+        if (dot != std::string::npos && h->dparam.count(wname)) HIP_TRY(h, split_bias(h->dparam.at(wname), dst, ps.cols));
         if (c.model == KGQ_CONE) {
             // the two set functions' first layers, stacked for one GEMM
             const size_t half_w = (size_t)2 * c.dim * c.dim, half_b = (size_t)c.dim;
@@ -1415,12 +1448,12 @@ kgq_status kgq_load_params(kgq_handle* h, const char* name, const void* src, siz
             if (!std::strcmp(name, "inter.arg.w1"))
                 HIP_TRY(h, hipMemcpy(h->int_cat_w + half_w, dst, nbytes, hipMemcpyDeviceToDevice));
             if (!std::strcmp(name, "inter.axis.w1") || !std::strcmp(name, "inter.arg.w1"))
-                split(h->int_cat_w, 2 * (int64_t)c.dim, 2 * (int64_t)c.dim);
+                HIP_TRY(h, split(h->int_cat_w, 2 * (int64_t)c.dim, 2 * (int64_t)c.dim));
             if (!std::strcmp(name, "inter.axis.b1")) HIP_TRY(h, hipMemcpy(h->int_cat_b, dst, nbytes, hipMemcpyDeviceToDevice));
             if (!std::strcmp(name, "inter.arg.b1"))
                 HIP_TRY(h, hipMemcpy(h->int_cat_b + half_b, dst, nbytes, hipMemcpyDeviceToDevice));
             if (!std::strcmp(name, "inter.axis.b1") || !std::strcmp(name, "inter.arg.b1"))
-                bound_of_bias(h->int_cat_w, h->int_cat_b, 2 * (int64_t)c.dim);
+                HIP_TRY(h, split_bias(h->int_cat_w, h->int_cat_b, 2 * (int64_t)c.dim));
             if (!std::strcmp(name, "modulus")) HIP_TRY(h, hipMemcpy(&h->cone_modulus, dst, sizeof(float), hipMemcpyDeviceToHost));
         }
         HIP_TRY(h, hipGetLastError());

@@ -160,12 +160,30 @@ void launch_split_planes(const float* w, uint16_t* p, int64_t rows, int64_t cols
 
 // Rows of w [rows x cols] (row stride ld) in the split form of the f16
 // matrix-core tile (mfma_tile.hpp): dst row stride plane_ld(cols) words, zeros
-// past cols, and each row's scale. norm (or nullptr): the largest row sum of
+// past cols, and each row's scale. sums (or nullptr): each row's sum of
 // magnitudes.
-void launch_split_rows(const float* w, int64_t rows, int64_t cols, int64_t ld, float* dst, float* scale, float* norm,
+void launch_split_rows(const float* w, int64_t rows, int64_t cols, int64_t ld, float* dst, float* scale, float* sums,
                        hipStream_t s);
-// The largest of b[0 .. n) and 0.
-void launch_bias_max(const float* b, int64_t n, float* out, hipStream_t s);
+
+// What bounds an output row of a layer on split rows, from its weights' row
+// sums of magnitudes and its biases (host arrays; bias or nullptr): the largest
+// of each (bias at least 0), and how far the largest unit (row sum + positive
+// bias) stands above the median one. fits: every value finite, and none so
+// large that the bounds of a chain of layers could overflow.
+constexpr float kSplitSumMax = 0x1p20f, kSplitBiasMax = 0x1p40f;
+struct SplitBound {
+    float norm = 0.f, bias = 0.f;
+    float spread = 1.f;
+    bool fits = true;
+};
+SplitBound split_bound(const float* sums, const float* bias, int64_t n);
+// A layer's outputs are scaled by their bound, so a unit far above the others
+// pushes these down the range that the form holds, also where it is switched
+// off; and the bound of the next layer starts from this one's. The chain's
+// error is that of ordinary weights until the spreads of its layers multiply to
+// 2^16 (at 2^20 six times the FP32 layers'); weights above 2^12, or that don't
+// fit, run on the FP32 matrix cores.
+constexpr float kSplitSpreadMax = 4096.f;
 
 // A dense layer on rows in split form: y[m] = epi(W x[m] + b), float32 rows
 // through the row map, or (y_split) rows in split form again for the next
@@ -178,7 +196,7 @@ struct SplitGemm {
     const float* w; const float* w_scale;                     // [N], stride plane_ld(K)
     const float* bias;
     float* y; int64_t ldy; const int32_t* y_rowmap;           // float32 output, or
-    float* y_split; float* y_scale; const float* bound;       // split output (stride plane_ld(N)); {norm of w, max(b, 0)}
+    float* y_split; float* y_scale; const float* bound;       // split output (stride plane_ld(N)); SplitBound's {norm, bias}
     int M, N, K, epi, epi_split;
 };
 void launch_gemm_split(const SplitGemm& g, hipStream_t s);

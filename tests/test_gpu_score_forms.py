@@ -251,6 +251,53 @@ def test_gpu_split_layers(model, structure, d, B):
     check_topk(out["idx"], out["score"], ref, 5, w.rtol, w.gamma, structure)
 
 
+def _auto_and_fp32(w, structure, qb):
+    """Scores by the default paths and by the FP32 matrix cores."""
+    import torch
+    from paper_2503_02172_amd import kgq
+    outs = []
+    with kgq.engine_for(w, max_batch=qb.batch) as eng:
+        for path in (kgq.DENSE_AUTO, kgq.DENSE_FP32):
+            eng.set_dense_path(path)
+            out = eng.execute(S[structure], qb.anchors, qb.relations, k=5, scores=True)
+            torch.cuda.synchronize()
+            outs.append(out["scores"].cpu().numpy())
+    return outs
+
+
+@pytest.mark.parametrize("model", [O.BETAE, O.CONE, O.LOGICE], ids=["betae", "cone", "logice"])
+@pytest.mark.parametrize("layer,factor", [("proj.1", 2.0 ** 10), ("proj.1", 2.0 ** 28), ("proj.2", 2.0 ** 28)])
+@pytest.mark.parametrize("B", [9, 200])
+def test_gpu_split_layers_dominating_unit(model, layer, factor, B):
+    """A hidden unit whose weights dwarf the others', switched off by its bias,
+    leaves the scores' error against 64 bits where the FP32 matrix cores have
+    it (half as much again for the sums' other order)."""
+    w = synth.make_tiny(model, n_ent=70, n_rel=7, dim=64, seed=171)
+    i = layer.rindex(".") + 1
+    w.params[layer[:i] + "w" + layer[i:]][3] *= np.float32(factor)
+    w.params[layer[:i] + "b" + layer[i:]].reshape(-1)[3] = -np.float32(factor) * 1000
+    qb = synth.draw_queries("2p", B, 70, 7, seed=172)
+    auto, fp32 = _auto_and_fp32(w, "2p", qb)
+    kw = {"center_reg": w.center_reg} if model == O.CONE else {}
+    ref = O.Model(model, w.params, w.gamma, **kw).scores(S["2p"], qb.anchors, qb.relations)
+    rms = lambda x: np.sqrt(np.mean(np.square(x - ref)))
+    assert rms(auto) <= 1.5 * rms(fp32), (rms(auto), rms(fp32))
+
+
+@pytest.mark.parametrize("d", [36, 64])
+@pytest.mark.parametrize("name", ["inter.arg.w1", "inter.axis.w1", "inter.arg.b2"])
+def test_gpu_cone_infinite_weight(name, d):
+    """An infinite weight reaches what it feeds, as on the FP32 matrix cores:
+    one of the aperture's does not touch the axis."""
+    w = synth.make_tiny(O.CONE, n_ent=70, n_rel=7, dim=d, seed=173)
+    w.params[name].reshape(-1)[5] = np.inf
+    qb = synth.draw_queries("2i", 40, 70, 7, seed=174)
+    auto, fp32 = _auto_and_fp32(w, "2i", qb)
+    assert np.array_equal(auto, fp32, equal_nan=True)
+    if name != "inter.axis.w1":
+        assert np.isfinite(auto).all()
+
+
 @pytest.mark.parametrize("n_ent,B,k", [(9001, 3, 1), (9001, 33, 70), (9001, 33, 71), (9001, 130, 64), (20011, 5, 156),
                                        (20011, 40, 157), (65600, 3, 256)])
 @pytest.mark.parametrize("structure", ["1p", "2u"])

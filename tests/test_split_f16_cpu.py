@@ -11,8 +11,12 @@ is no further from 64 bits than the six-product bf16 form's; nor is a chain of
 dense layers further than float32's, from the dimensions on where the layers
 take the form."""
 
+import ctypes
+
 import numpy as np
 import pytest
+
+from paper_2503_02172_amd import kgq
 
 from tests.test_split_bf16_cpu import split3
 
@@ -154,3 +158,48 @@ def test_layers_no_further_off_than_float32(d):
     g = np.random.default_rng(d)
     split, flt = np.mean([projection(g, d) for _ in range(6)], 0)
     assert split <= flt, (split, flt)
+
+
+LIMIT = 4096.0                                       # kSplitSpreadMax
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("factors", [(LIMIT, 1.0), (1.0, LIMIT), (64.0, 64.0)])
+def test_layers_with_a_unit_far_above_the_others(d, factors):
+    """At the largest spread that the form takes, with the unit that makes it
+    switched off, the layers are no further off than float32 ones (10% for the
+    draw); at 2^24 they would be, by far."""
+    g = np.random.default_rng(d)
+    split, flt = np.mean([projection(g, d, factors) for _ in range(4)], 0)
+    assert split <= 1.1 * flt, (split, flt)
+    split, flt = projection(g, d, (2.0 ** 24, 1.0))
+    assert split > 5 * flt
+
+
+class SplitBound(ctypes.Structure):
+    _fields_ = [("norm", ctypes.c_float), ("bias", ctypes.c_float), ("spread", ctypes.c_float), ("fits", ctypes.c_bool)]
+
+
+def bound(sums, bias):
+    """kgq::split_bound(sums, bias, n)."""
+    f = kgq.lib()._ZN3kgq11split_boundEPKfS1_l
+    f.restype = SplitBound
+    f.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_long]
+    sums = np.asarray(sums, np.float32)
+    bias = None if bias is None else np.asarray(bias, np.float32)
+    return f(sums.ctypes.data, None if bias is None else bias.ctypes.data, sums.size)
+
+
+def test_split_bound():
+    b = bound([3.0, 5.0, 4.0], [0.5, -100.0, -1.0])
+    assert (b.norm, b.bias, b.fits) == (5.0, 0.5, True) and b.spread == np.float32(5.0 / 4.0)
+    assert bound([3.0, 5.0, 4.0], None).bias == 0.0
+    assert bound([3.0, 4096.0 * 4, 4.0], None).spread == 4096.0
+    assert bound([3.0, 4.0, 4.0], [0.0, 1e6, 0.0]).spread > 1e5          # a huge positive bias counts,
+    assert bound([3.0, 4.0, 4.0], [0.0, -1e6, 0.0]).spread == 1.0        # a negative one switches the unit off
+    assert bound([0.0, 0.0, 4.0], None).spread == np.inf
+    assert bound([0.0, 0.0], None).spread == 1.0
+    for bad in (np.nan, np.inf, 2.0 ** 21):
+        assert not bound([3.0, bad, 4.0], None).fits
+    for bad in (np.nan, np.inf, -np.inf, 2.0 ** 41):
+        assert not bound([3.0, 4.0], [0.0, bad]).fits
