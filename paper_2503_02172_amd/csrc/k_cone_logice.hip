@@ -302,9 +302,6 @@ void launch_cone_int_prep(const GroupArgs& g, const float* states, int d, float*
         hipLaunchKernelGGL(k_cone_int_prep, dim3(g.n_groups), dim3(256), 0, s, g, states, d, x_int);
 }
 
-// ConE axis: attention-weighted mean of the branch axes' unit vectors; and
-// the mean over branches of the aperture set function's hidden features
-// (columns d .. 2d-1 of the stacked first layer's output).
 // Value k of a row in split form.
 __device__ __forceinline__ float split_value(const float* row, float scale, int k)
 {
@@ -312,6 +309,9 @@ __device__ __forceinline__ float split_value(const float* row, float scale, int 
     return fmaf((float)p[8], kSplitLow, (float)p[0]) * scale;
 }
 
+// ConE axis: attention-weighted mean of the branch axes' unit vectors; and
+// the mean over branches of the aperture set function's hidden features
+// (columns d .. 2d-1 of the stacked first layer's output).
 template <bool SPLIT>
 __global__ __launch_bounds__(1024) void k_cone_combine_axis(GroupArgs g, const float* states, const float* logits,
                                                            const float* hid, const float* hid_scale, int d, float* zmean,

@@ -139,8 +139,8 @@ void launch_table_stats(const float* x, int64_t n, double* part, hipStream_t s)
 // Uniform tables of half width gamma / width take it up to a width of 500
 // (GQE; LogicE at gamma = 1 up to 2,000); a wider range, or one stretched by
 // outliers or by columns of different centres, doesn't. Measured error against
-// 64 bits on uniform tables: 5.2e-7 in floats, 1.2e-7 here (63,361 x 400);
-// 1.9e-7 and 3.1e-8 (LogicE, 14,505 x 800).
+// 64 bits on uniform tables: 1.1e-6 in floats, 1.2e-7 here (63,361 x 400);
+// 1.9e-7 and 3.0e-8 (LogicE, 14,505 x 800).
 L1Fixed choose_l1_fixed(double lo, double hi, double sum, int width, double gamma, double scale)
 {
     L1Fixed f;

@@ -231,7 +231,7 @@ __device__ __forceinline__ void gemm_bf16x3_tile(const GemmArgs& g, int tm, int 
     const int m0 = mt * BM, n0 = nt * BN;
     v4f acc[Tile::TM][Tile::TN];
     const int64_t ldp = plane_ld(g.K);
-    Tile::run(g.A, g.lda, g.M, g.M, g.Wp, (int64_t)g.N * ldp, ldp, g.N, g.K, m0, n0, sm, acc);
+    Tile::run(g.A, g.lda, g.M, g.Wp, (int64_t)g.N * ldp, ldp, g.N, g.K, m0, n0, sm, acc);
 
     store_tile<Tile>(g, m0, n0, acc);
 }
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16x3_part(GemmArgs g, int kc)
     const int kn = min(kc, g.K - k0);
     v4f acc[Tile::TM][Tile::TN];
     const int64_t ldp = plane_ld(g.K);
-    Tile::run(g.A + k0, g.lda, g.M, g.M, g.Wp + k0, (int64_t)g.N * ldp, ldp, g.N, kn, m0, n0, sm, acc);
+    Tile::run(g.A + k0, g.lda, g.M, g.Wp + k0, (int64_t)g.N * ldp, ldp, g.N, kn, m0, n0, sm, acc);
     float* part = g.ws + (int64_t)blockIdx.z * g.M * g.N;
 #pragma unroll
     for (int j = 0; j < Tile::TN; ++j) {

@@ -40,10 +40,6 @@
 
 namespace kgq {
 
-// Workgroup tiles: 64 x 64 on the direct-to-LDS loop; on the register-staged
-// loop 128 x 128, or 64 x 64 for small batches, where the larger tile leaves
-// the chip underfilled and each workgroup's K loop is a latency chain. Query
-// rows are padded to 128 (kRowTileBetae), a multiple of every tile's rows.
 // x of the lane that the DPP control names (quad permutations).
 template <int CTRL>
 __device__ __forceinline__ float dpp_f32(float x)
@@ -51,6 +47,11 @@ __device__ __forceinline__ float dpp_f32(float x)
     return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xF, 0xF, false));
 }
 
+// Workgroup tiles of rows x entities: 64 x 64 on the direct-to-LDS loop, 32 x 64
+// as long as every tile has a compute unit to itself (launch_lds); on the
+// register-staged loop 128 x 128, or 64 x 64 for small batches, where the
+// larger tile leaves the chip underfilled and each workgroup's K loop is a
+// latency chain. Query rows are not padded: rows past the last are read from it.
 template <class KlTile>
 __global__ __launch_bounds__(256, 2) void k_score_kl(ScoreArgs a, int n_mt, int n_nt, int qchunk, int total,
                                                      int per_xcd)

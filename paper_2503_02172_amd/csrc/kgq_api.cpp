@@ -103,7 +103,7 @@ struct kgq_handle {
     float* ent_blk = nullptr;     // scoring table: GQE/Q2B/LogicE blocked points; BetaE row-major U|V;
                                   // ConE blocked half-angle sin | cos
     double* ent_const = nullptr;  // BetaE E_e [n_pad]
-    float* ent_split = nullptr;   // BetaE [U | V] rows of ent_blk in split form, with their scales [n_pad]
+    float* ent_split = nullptr;   // BetaE from d = kSplitDim: [U | V] rows of ent_blk in split form, with their scales [n_pad]
     float* ent_scale = nullptr;
     float* rel_o_sp = nullptr;    // Q2B softplus(offset_raw) [R x d]
     L1Fixed l1;                   // GQE / LogicE: fixed-point form of ent_blk (off: floats)
@@ -385,7 +385,7 @@ kgq_status allocate_all(kgq_handle* h)
         ALLOC(h->ent_rm, N * 2 * d);
         ALLOC(h->ent_blk, n_pad * 2 * d + kEntPad);
         if (c.model == KGQ_BETAE) ALLOC(h->ent_const, n_pad);
-        if (c.model == KGQ_BETAE) {
+        if (c.model == KGQ_BETAE && d >= kSplitDim) {
             ALLOC(h->ent_split, n_pad * plane_ld(2 * d));
             ALLOC(h->ent_scale, n_pad);
         }
@@ -459,7 +459,7 @@ kgq_status allocate_all(kgq_handle* h)
         if (!mlp_model(c.model)) ALLOC(L.logits, m_max * d);
         ALLOC(L.qpack, h->cap_score_rows * qpack_row_floats(c.model, (int)d) + kQpackPad);
         ALLOC(L.cq, h->cap_score_rows);
-        ALLOC(L.q_scale, h->cap_score_rows);
+        if (h->ent_split) ALLOC(L.q_scale, h->cap_score_rows);
         ALLOC(L.scores, Bm * N);
         // split-K runs only while a layer has fewer than 128 output tiles of
         // 64 x 64, so 16 slices of it stay below 16 x 128 x 4096 floats
@@ -1011,7 +1011,7 @@ int64_t carve_scratch(const kgq_handle* h, const Plan& p, int32_t k, bool need_s
     }
     if (!mlp_model(c.model)) V.logits = reinterpret_cast<float*>(take(m * d * 4));
     V.cq = reinterpret_cast<double*>(take(srows * 8));
-    if (c.model == KGQ_BETAE) V.q_scale = reinterpret_cast<float*>(take(srows * 4));
+    if (h->ent_split) V.q_scale = reinterpret_cast<float*>(take(srows * 4));
     V.scores = need_scores ? reinterpret_cast<float*>(take(B * N * 4)) : nullptr;
     const int64_t ncand = need_topk ? topk_scratch_elems(B, N, k) : 0;
     for (int i = 0; i < 2; ++i) {
@@ -1474,8 +1474,9 @@ kgq_status kgq_load_params(kgq_handle* h, const char* name, const void* src, siz
         if (c.model == KGQ_BETAE) {
             launch_betae_entity_prep(stage, bf16, c.n_entities, c.dim, h->n_blocks, h->ent_rm, h->ent_blk,
                                      h->ent_const, nullptr);
-            launch_split_rows(h->ent_blk, h->n_blocks * kEntBlock, 2 * (int64_t)c.dim, 2 * (int64_t)c.dim, h->ent_split,
-                              h->ent_scale, nullptr, nullptr);
+            if (h->ent_split)
+                launch_split_rows(h->ent_blk, h->n_blocks * kEntBlock, 2 * (int64_t)c.dim, 2 * (int64_t)c.dim, h->ent_split,
+                                  h->ent_scale, nullptr, nullptr);
         }
         else if (c.model == KGQ_CONE)
             launch_cone_entity_prep(static_cast<const float*>(stage), c.n_entities, c.dim, h->n_blocks, h->ent_rm,

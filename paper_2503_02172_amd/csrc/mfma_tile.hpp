@@ -47,8 +47,7 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 
 template <int BM, int BN>
 struct MfmaTileReg {
-    static constexpr int kBM = BM, kBN = BN, kThreads = 256;
-    static constexpr bool kSplit = false;
+    static constexpr int kBM = BM, kBN = BN;
     static constexpr int BK = 32;
     static constexpr int LD = BK + 4;                  // padded LDS row (floats)
     static constexpr int TM = BM / 32, TN = BN / 32;   // MFMA tiles per wavefront
@@ -158,8 +157,7 @@ typedef __attribute__((address_space(3))) void lds_void;
 
 template <int BM, int BN, int S, bool HALF = false>
 struct MfmaTileLds {
-    static constexpr int kBM = BM, kBN = BN, kThreads = 256;
-    static constexpr bool kSplit = false;
+    static constexpr int kBM = BM, kBN = BN;
     static constexpr int BK = 32;
     static constexpr int CH = BK / 4;                  // 16-byte chunks per row per stage
     static constexpr int RPI = 64 / CH;                // rows written by one wave instruction
@@ -406,10 +404,9 @@ struct MfmaTileBf16x3 {
     // acc = A[m0 : m0 + BM, :K] . B[n0 : n0 + BN, :K]^T; B's planes are
     // Bp, Bp + plane, Bp + 2 plane (row stride ldb elements, zero-padded
     // past K as above). A's rows are read up to M - 1; a wavefront whose rows
-    // all lie at or past live_rows (output rows the caller drops) takes its
-    // share of the loads and the barriers but no products, and its acc stays
-    // zero.
-    __device__ static void run(const float* __restrict__ A, int64_t lda, int M, int live_rows,
+    // all lie at or past M (output rows the caller drops) takes its share of
+    // the loads and the barriers but no products, and its acc stays zero.
+    __device__ static void run(const float* __restrict__ A, int64_t lda, int M,
                                const uint16_t* __restrict__ Bp, int64_t plane, int64_t ldb, int N, int K, int m0,
                                int n0, float* sm_f, v4f (&acc)[TM][TN])
     {
@@ -526,7 +523,7 @@ struct MfmaTileBf16x3 {
         // loads only: the caller has no vector-memory load outstanding on
         // entry, and at the wait stage kt's are the only ones in flight.
         issue(0, 0);
-        if (m0 + wm * (BM / WM) < live_rows) {
+        if (m0 + wm * (BM / WM) < M) {
             for (int kt = 0; kt < nk; ++kt) {
                 wait_vm_barrier<0>();
                 if (kt + 1 < nk) issue(kt + 1, (kt + 1) & 1);
@@ -649,7 +646,6 @@ __device__ __forceinline__ void split_row_wave(F f, int n8, float* dst, float* s
 template <int BM, int BN, int WM, int WN, int S = 2>
 struct MfmaTileF16x2 {
     static constexpr int kBM = BM, kBN = BN, kThreads = 64 * WM * WN;
-    static constexpr bool kSplit = true;
     static constexpr int BK = 32, ROW = 128;
     static constexpr int ABYTES = BM * ROW, STAGE = (BM + BN) * ROW;
     static constexpr int TM = BM / WM / 16, TN = BN / WN / 16;
