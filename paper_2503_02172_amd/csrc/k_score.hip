@@ -178,7 +178,8 @@ __global__ __launch_bounds__(256, 4) void k_score(ScoreArgs a, int nqg, int qchu
     // each wait on them covers every one outstanding: one issued later would
     // have less time to arrive in). d is a multiple of 4. Against one step
     // and half a step ahead: 1,229 rows x 63,361 GQE entities 0.89 -> 0.85 ms
-    // a call, 5,632 x 14,505 Query2Box 2.19 -> 2.15 ms.
+    // a call (with every third row in floats), 5,632 x 14,505 Query2Box 2.19 ->
+    // 2.15 ms.
     constexpr int QN = F * TQ;
     // steps per batch of query scalars (two batches in SGPRs): two where a
     // step is short, 4 rows or 8 (64 Query2Box queries over 14,505 entities:

@@ -37,8 +37,8 @@ constexpr int kTqCone = 8;
 constexpr int kRowGrainBetae = 128;
 
 // The VALU scorers read up to two dimension steps past the last block of the
-// entity table and one past the last block of packed rows: floats allocated
-// behind each.
+// entity table, and past the last block of packed rows a batch of scalars (one
+// step of up to 40 floats, or two of up to 8): floats allocated behind each.
 constexpr int kEntPad = 2 * 2 * kEntBlock;
 constexpr int kQpackPad = 64;
 
