@@ -274,13 +274,15 @@ kgq_status kgq_set_checked(kgq_handle* h, int32_t on);
  *     largest and to 2^-50 of that bound below, and three of the four part
  *     products are kept (error 2^-21 of each product, in the class of the FP32
  *     sum). The bound of a layer's output comes from the weights' largest row
- *     sum and bias, so weights are looked at when they are loaded: where a
- *     hidden unit stands more than 4,096 times above the median one (the
- *     product over proj.1 and proj.2), or a value is not finite or huge (a row
- *     sum above 2^20, a bias above 2^40), the handle's layers run on the FP32
- *     matrix cores. BetaE scores the same way (from 16 dimensions on) when the
- *     call has more than 256 tiles of 64 scored rows x 64 entities; smaller
- *     calls score on the FP32 matrix cores.
+ *     sum and bias, so weights and tables are looked at when they are loaded:
+ *     the handle's layers run on the FP32 matrix cores where the largest
+ *     relation or entity value over the geometric mean, times how far a hidden
+ *     unit stands above the median one (over proj.1 and proj.2, or the
+ *     intersection's first layer), exceeds 16,384, or where a value is not
+ *     finite or huge (a row sum above 2^20, a bias above 2^40). BetaE scores
+ *     the same way (from 16 dimensions on) when the call has more than 256
+ *     tiles of 64 scored rows x 64 entities; smaller calls score on the FP32
+ *     matrix cores.
  *     GQE's and Query2Box's layers and kgq_dense, with K >= 32 (K is a multiple
  *     of 4 on every path) and at least 384 output tiles of 64 x 64, or 1,024
  *     rows and 192 such tiles, run on the bf16 matrix cores, each FP32 operand

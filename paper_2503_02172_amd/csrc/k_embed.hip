@@ -120,6 +120,52 @@ __global__ __launch_bounds__(256) void k_table_range(const float4* __restrict__ 
     }
 }
 
+__global__ __launch_bounds__(256) void k_table_spread(const float4* __restrict__ x, int64_t n4, double* __restrict__ part)
+{
+    float most = 0.f;
+    double logs = 0.0, count = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)kStatBlocks * 256) {
+        const float4 q = x[i];
+        const float v[4] = {fabsf(q.x), fabsf(q.y), fabsf(q.z), fabsf(q.w)};
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            most = fmaxf(most, v[t]);
+            if (v[t] != 0.f) {
+                logs += (double)log2f(v[t]);       // (NaN and infinities pass through)
+                count += 1.0;
+            }
+        }
+    }
+    for (int off = 32; off > 0; off >>= 1) most = fmaxf(most, __shfl_xor(most, off, 64));
+    __shared__ float sh_most[4];
+    if ((threadIdx.x & 63) == 0) sh_most[threadIdx.x >> 6] = most;
+    logs = block_sum(logs);
+    count = block_sum(count);
+    if (threadIdx.x == 0) {
+        double* o = part + 3 * blockIdx.x;
+        o[0] = fmaxf(fmaxf(sh_most[0], sh_most[1]), fmaxf(sh_most[2], sh_most[3]));
+        o[1] = logs;
+        o[2] = count;
+    }
+}
+
+void launch_table_spread(const float* x, int64_t n, double* part, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_table_spread, dim3(kStatBlocks), dim3(256), 0, s, reinterpret_cast<const float4*>(x), n / 4, part);
+}
+
+float table_spread(const double* part)
+{
+    double most = 0.0, logs = 0.0, count = 0.0;
+    for (int b = 0; b < kStatBlocks; ++b) {
+        most = std::max(most, part[3 * b]);
+        logs += part[3 * b + 1];
+        count += part[3 * b + 2];
+    }
+    if (!(logs - logs == 0.0) || !(most < HUGE_VAL)) return HUGE_VALF;
+    return count > 0.0 ? (float)(most / std::exp2(logs / count)) : 1.f;
+}
+
 void launch_table_stats(const float* x, int64_t n, double* part, hipStream_t s)
 {
     const float4* x4 = reinterpret_cast<const float4*>(x);

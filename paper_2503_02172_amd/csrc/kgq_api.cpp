@@ -122,17 +122,23 @@ struct kgq_handle {
     // weight is loaded
     std::map<const float*, uint16_t*> wplanes;
     // BetaE, ConE, LogicE: the dense weights' rows in split form instead (the
-    // f16 matrix-core layers), with the bound of an output row's values
+    // f16 matrix-core layers)
     struct SplitWeight {
         float* rows = nullptr;
         float* scale = nullptr;
         float* bound = nullptr;   // SplitBound's {norm, bias}
-        float* sums = nullptr;    // each row's sum of magnitudes
-        std::vector<float> host_sums, host_bias;
-        SplitBound host;
+        float* sums = nullptr;    // each row's sum of magnitudes, then the biases [2 x n]
+        int64_t n = 0;            // rows
+        float spread = 1.f;       // SplitBound's
     };
     std::map<const float*, SplitWeight> wsplit;
-    bool split_ok = false;        // the weights suit the split form (split_weights_ok)
+    // What refresh_split reads back, in one piece: table statistics of the
+    // relation and the entity table [2 x 3 kStatBlocks], then every split
+    // weight's sums and biases; and the weights' bounds, in the map's order
+    double* stats = nullptr;
+    int64_t stats_elems = 0;
+    float* bounds = nullptr;
+    bool split_ok = false;        // weights and tables suit the split form (refresh_split)
     int dense_path = KGQ_DENSE_AUTO;
 
     // structure id -> compiled program: the built-ins for this model, then
@@ -400,14 +406,13 @@ kgq_status allocate_all(kgq_handle* h)
         ALLOC(h->ent_blk, n_pad * d + kEntPad);
         if (c.model == KGQ_Q2B) ALLOC(h->rel_o_sp, (int64_t)c.n_relations * d);
     }
-    // one piece of memory for a weight's split form: rows, scales, sums, bound
+    // one piece of memory for a weight's split form: rows, scales
     auto split_weight = [&](const float* of, int64_t rows, int64_t cols) -> kgq_status {
         if (d < kSplitLayerDim) return KGQ_OK;
         kgq_handle::SplitWeight w;
-        ALLOC(w.rows, rows * plane_ld(cols) + 2 * rows + 2);
+        ALLOC(w.rows, rows * plane_ld(cols) + rows);
         w.scale = w.rows + rows * plane_ld(cols);
-        w.sums = w.scale + rows;
-        w.bound = w.sums + rows;
+        w.n = rows;
         h->wsplit[of] = w;
         return KGQ_OK;
     };
@@ -430,6 +435,19 @@ kgq_status allocate_all(kgq_handle* h)
         h->wplanes[h->dparam.at(n)] = planes;
     }
     if (h->int_cat_w && (s = split_weight(h->int_cat_w, 2 * d, 2 * d)) != KGQ_OK) return s;
+    int64_t floats = 0;
+    for (auto& kv : h->wsplit) floats += 2 * kv.second.n;
+    h->stats_elems = 6 * kStatBlocks + (floats + 1) / 2;
+    ALLOC(h->stats, h->stats_elems);
+    ALLOC(h->bounds, std::max<size_t>(1, 2 * h->wsplit.size()));
+    float* sums = reinterpret_cast<float*>(h->stats + 6 * kStatBlocks);
+    float* bound = h->bounds;
+    for (auto& kv : h->wsplit) {
+        kv.second.sums = sums;
+        kv.second.bound = bound;
+        sums += 2 * kv.second.n;
+        bound += 2;
+    }
     h->bytes_params = h->bytes_total;   // everything after this is execute scratch
     const int n_lanes = c.concurrency > 0 ? c.concurrency : 1;
     for (int li = 0; li < n_lanes; ++li) {
@@ -781,7 +799,9 @@ kgq_status run_plan(kgq_handle* h, Lane& L, const Plan& p, const int32_t* P, con
                 }
                 {
                     // (reads the first d columns; what follows them up to the
-                    // stage's end meets the weights' zero padding)
+                    // stage's end, the aperture's, meets the weights' zero
+                    // padding, and is finite: weights that are not, or huge,
+                    // don't come here)
                     StageTimer t(h, 1, s);
                     if (split_mlp)
                         split_gemm(L.h1, ld2, L.row_scale[1], param("inter.axis.w2"), param("inter.axis.b2"), L.logits, d,
@@ -1343,25 +1363,44 @@ static kgq_status build_proj1(kgq_handle* h)
     return KGQ_OK;
 }
 
-// Whether the loaded weights suit the split form: each fits, and the spreads of
-// the layers that write split rows, one after the other, stay in its range.
-static bool split_weights_ok(const kgq_handle* h)
+// Once every parameter is there: the bounds of the split layers' outputs, and
+// whether weights and tables suit the form: each weight fits, and the spreads of
+// the input and of the layers that write split rows, one after the other, stay
+// in its range. (The loads leave the row sums, biases and table statistics on
+// the device; they come back in one copy.)
+static hipError_t refresh_split(kgq_handle* h)
 {
-    for (auto& kv : h->wsplit)
-        if (!kv.second.host.fits) return false;
-    auto spread = [&](const float* w) { return h->wsplit.count(w) ? h->wsplit.at(w).host.spread : 1.f; };
+    std::string missing;
+    if (h->wsplit.empty() || !all_loaded(h, missing)) return hipSuccess;
+    std::vector<double> host((size_t)h->stats_elems);
+    hipError_t e = hipMemcpy(host.data(), h->stats, host.size() * sizeof(double), hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return e;
+    const float* sums = reinterpret_cast<const float*>(host.data() + 6 * kStatBlocks);
+    std::vector<float> bounds;
+    bool fits = true;
+    for (auto& kv : h->wsplit) {
+        const SplitBound b = split_bound(sums, sums + kv.second.n, kv.second.n);
+        kv.second.spread = b.spread;
+        fits = fits && b.fits;
+        bounds.push_back(b.norm);
+        bounds.push_back(b.bias);
+        sums += 2 * kv.second.n;
+    }
+    const float in = std::max(table_spread(host.data()), table_spread(host.data() + 3 * kStatBlocks));
+    auto spread = [&](const float* w) { return h->wsplit.count(w) ? h->wsplit.at(w).spread : 1.f; };
     auto named = [&](const char* n) { return h->dparam.count(n) ? spread(h->dparam.at(n)) : 1.f; };
-    return named("proj.w1") * named("proj.w2") <= kSplitSpreadMax && named("inter.w1") <= kSplitSpreadMax &&
-           spread(h->int_cat_w) <= kSplitSpreadMax;
+    h->split_ok = fits && in * named("proj.w1") * named("proj.w2") <= kSplitSpreadMax &&
+                  in * named("inter.w1") <= kSplitSpreadMax && in * spread(h->int_cat_w) <= kSplitSpreadMax;
+    return hipMemcpy(h->bounds, bounds.data(), bounds.size() * sizeof(float), hipMemcpyHostToDevice);
 }
 
 // GQE / LogicE: choose the scoring table's form from its values, and bring
-// it into fixed point where that is the one. `part`: device scratch of
-// kStatBlocks x 3 doubles.
-static hipError_t fix_points(kgq_handle* h, int width, void* part)
+// it into fixed point where that is the one.
+static hipError_t fix_points(kgq_handle* h, int width)
 {
     double p[3 * kStatBlocks];
-    launch_table_stats(h->ent_rm, h->cfg.n_entities * width, static_cast<double*>(part), nullptr);
+    double* part = h->stats + 3 * kStatBlocks;      // (the entity table's; its spread comes after)
+    launch_table_stats(h->ent_rm, h->cfg.n_entities * width, part, nullptr);
     const hipError_t e = hipMemcpy(p, part, sizeof(p), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return e;
     double lo = p[0], hi = p[1], sum = 0.0;
@@ -1408,39 +1447,27 @@ kgq_status kgq_load_params(kgq_handle* h, const char* name, const void* src, siz
             HIP_TRY(h, hipGetLastError());
             HIP_TRY(h, hipStreamSynchronize(nullptr));
         }
-        // a weight: its form for the matrix cores; with its bias, the bound of
-        // the layer's outputs
-        auto bound = [&](kgq_handle::SplitWeight& w) -> hipError_t {
-            w.host = split_bound(w.host_sums.data(), w.host_bias.empty() ? nullptr : w.host_bias.data(),
-                                 (int64_t)w.host_sums.size());
-            h->split_ok = split_weights_ok(h);
-            const float b[2] = {w.host.norm, w.host.bias};
-            return hipMemcpy(w.bound, b, sizeof(b), hipMemcpyHostToDevice);
-        };
-        auto split = [&](const float* w, int64_t rows, int64_t cols) -> hipError_t {
+        auto split = [&](const float* w, int64_t rows, int64_t cols) {
             auto pl = h->wplanes.find(w);
             auto sw = h->wsplit.find(w);
             if (pl != h->wplanes.end()) launch_split_planes(w, pl->second, rows, cols, nullptr);
-            if (sw == h->wsplit.end()) return hipSuccess;
-            kgq_handle::SplitWeight& s = sw->second;
-            launch_split_rows(w, rows, cols, cols, s.rows, s.scale, s.sums, nullptr);
-            s.host_sums.resize((size_t)rows);
-            const hipError_t e = hipMemcpy(s.host_sums.data(), s.sums, (size_t)rows * 4, hipMemcpyDeviceToHost);
-            return e == hipSuccess ? bound(s) : e;
+            if (sw != h->wsplit.end())
+                launch_split_rows(w, rows, cols, cols, sw->second.rows, sw->second.scale, sw->second.sums, nullptr);
         };
-        auto split_bias = [&](const float* w, const float* b, int64_t n) -> hipError_t {
+        // a bias beside its weight's row sums (".b1" -> ".w1")
+        auto keep_bias = [&](const float* w, const float* b) {
             auto sw = h->wsplit.find(w);
-            if (sw == h->wsplit.end()) return hipSuccess;
-            kgq_handle::SplitWeight& s = sw->second;
-            s.host_bias.resize((size_t)n);
-            const hipError_t e = hipMemcpy(s.host_bias.data(), b, (size_t)n * 4, hipMemcpyDeviceToHost);
-            return e == hipSuccess && !s.host_sums.empty() ? bound(s) : e;
+            return sw == h->wsplit.end() ? hipSuccess
+                                         : hipMemcpyAsync(sw->second.sums + sw->second.n, b, (size_t)sw->second.n * 4,
+                                                          hipMemcpyDeviceToDevice, nullptr);
         };
-        HIP_TRY(h, split(dst, ps.rows, ps.cols));
-        std::string wname = name;      // (".b1" -> ".w1")
+        split(dst, ps.rows, ps.cols);
+        std::string wname = name;
         const size_t dot = wname.rfind(".b");
         if (dot != std::string::npos) wname[dot + 1] = 'w';
-        if (dot != std::string::npos && h->dparam.count(wname)) HIP_TRY(h, split_bias(h->dparam.at(wname), dst, ps.cols));
+        if (dot != std::string::npos && h->dparam.count(wname)) HIP_TRY(h, keep_bias(h->dparam.at(wname), dst));
+        if (!std::strcmp(name, "relation") && !h->wsplit.empty())
+            launch_table_spread(dst, ps.rows * ps.cols, h->stats, nullptr);
         if (c.model == KGQ_CONE) {
             // the two set functions' first layers, stacked for one GEMM
             const size_t half_w = (size_t)2 * c.dim * c.dim, half_b = (size_t)c.dim;
@@ -1448,17 +1475,18 @@ kgq_status kgq_load_params(kgq_handle* h, const char* name, const void* src, siz
             if (!std::strcmp(name, "inter.arg.w1"))
                 HIP_TRY(h, hipMemcpy(h->int_cat_w + half_w, dst, nbytes, hipMemcpyDeviceToDevice));
             if (!std::strcmp(name, "inter.axis.w1") || !std::strcmp(name, "inter.arg.w1"))
-                HIP_TRY(h, split(h->int_cat_w, 2 * (int64_t)c.dim, 2 * (int64_t)c.dim));
+                split(h->int_cat_w, 2 * (int64_t)c.dim, 2 * (int64_t)c.dim);
             if (!std::strcmp(name, "inter.axis.b1")) HIP_TRY(h, hipMemcpy(h->int_cat_b, dst, nbytes, hipMemcpyDeviceToDevice));
             if (!std::strcmp(name, "inter.arg.b1"))
                 HIP_TRY(h, hipMemcpy(h->int_cat_b + half_b, dst, nbytes, hipMemcpyDeviceToDevice));
             if (!std::strcmp(name, "inter.axis.b1") || !std::strcmp(name, "inter.arg.b1"))
-                HIP_TRY(h, split_bias(h->int_cat_w, h->int_cat_b, 2 * (int64_t)c.dim));
+                HIP_TRY(h, keep_bias(h->int_cat_w, h->int_cat_b));
             if (!std::strcmp(name, "modulus")) HIP_TRY(h, hipMemcpy(&h->cone_modulus, dst, sizeof(float), hipMemcpyDeviceToHost));
         }
         HIP_TRY(h, hipGetLastError());
         HIP_TRY(h, hipStreamSynchronize(nullptr));
         h->loaded[name] = true;
+        HIP_TRY(h, refresh_split(h));
         if (mlp_model(c.model) && (!std::strcmp(name, "relation") || !std::strcmp(name, "proj.w1") ||
                                    !std::strcmp(name, "proj.b1")))
             return build_proj1(h);
@@ -1466,7 +1494,7 @@ kgq_status kgq_load_params(kgq_handle* h, const char* name, const void* src, siz
     }
     // entity table: stage, then build the derived layouts
     void* stage = nullptr;
-    hipError_t e = hipMalloc(&stage, std::max(nbytes, (size_t)kStatBlocks * 3 * sizeof(double)));
+    hipError_t e = hipMalloc(&stage, nbytes);
     if (e != hipSuccess) return fail(h, KGQ_E_OOM, "staging buffer for the entity table");
     e = hipMemcpy(stage, src, nbytes, kind);
     if (e == hipSuccess) {
@@ -1484,14 +1512,17 @@ kgq_status kgq_load_params(kgq_handle* h, const char* name, const void* src, siz
         else {
             const int width = c.model == KGQ_LOGICE ? 2 * c.dim : c.dim;
             launch_relayout_points(stage, bf16, c.n_entities, width, h->n_blocks, h->ent_rm, h->ent_blk, nullptr);
-            if (c.model != KGQ_Q2B) e = fix_points(h, width, stage);
+            if (c.model != KGQ_Q2B) e = fix_points(h, width);
         }
+        if (e == hipSuccess && !h->wsplit.empty())
+            launch_table_spread(h->ent_rm, c.n_entities * 2 * (int64_t)c.dim, h->stats + 3 * kStatBlocks, nullptr);
         if (e == hipSuccess) e = hipGetLastError();
         if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     }
     (void)hipFree(stage);
     if (e != hipSuccess) return fail(h, KGQ_E_DEVICE, std::string("entity table load: ") + hipGetErrorString(e));
     h->loaded[name] = true;
+    HIP_TRY(h, refresh_split(h));
     if (mlp_model(c.model)) return build_proj1(h);
     return KGQ_OK;
 }

@@ -177,13 +177,15 @@ struct SplitBound {
     bool fits = true;
 };
 SplitBound split_bound(const float* sums, const float* bias, int64_t n);
-// A layer's outputs are scaled by their bound, so a unit far above the others
-// pushes these down the range that the form holds, also where it is switched
-// off; and the bound of the next layer starts from this one's. The chain's
-// error is that of ordinary weights until the spreads of its layers multiply to
-// 2^16 (at 2^20 six times the FP32 layers'); weights above 2^12, or that don't
-// fit, run on the FP32 matrix cores.
-constexpr float kSplitSpreadMax = 4096.f;
+// A layer's outputs are scaled by their bound, so a unit far above the others,
+// or an input value far above the others whose weights make up for it, pushes
+// them down the range that the form holds, also where the unit is switched off;
+// and the bound of the next layer starts from this one's. The chain's error is
+// that of ordinary weights until the spreads of the input tables (largest value
+// over the geometric mean) and of the layers multiply to 2^16 (at 2^20 up to
+// three times the FP32 layers', at 2^24 forty). Handles above 2^14, or whose
+// values don't fit, run their layers on the FP32 matrix cores.
+constexpr float kSplitSpreadMax = 16384.f;
 
 // A dense layer on rows in split form: y[m] = epi(W x[m] + b), float32 rows
 // through the row map, or (y_split) rows in split form again for the next
@@ -238,6 +240,11 @@ void launch_relayout_points(const void* src, int src_bf16, int64_t N, int d, int
 // [kStatBlocks x 3] doubles, one part per workgroup.
 constexpr int kStatBlocks = 512;
 void launch_table_stats(const float* x, int64_t n, double* part, hipStream_t s);
+// Largest magnitude, sum of log2 of the magnitudes other than 0, and their
+// number, laid out alike; and from these how far the largest stands above the
+// geometric mean (infinite where a value is not finite).
+void launch_table_spread(const float* x, int64_t n, double* part, hipStream_t s);
+float table_spread(const double* part);
 // Blocked scoring table to fixed-point words, in place (n a multiple of 256).
 void launch_l1_quantise(float* blk, int64_t n, const L1Fixed& f, hipStream_t s);
 

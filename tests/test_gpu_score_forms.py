@@ -305,11 +305,14 @@ def test_gpu_split_layers(model, structure, d, B):
         assert np.median(per_query(seen, ref[few])) > 10.0 * np.median(base), name
 
 
-def _auto_and_fp32(w, structure, qb):
-    """Scores by the default paths and by the FP32 matrix cores."""
+def _auto_and_fp32(w, structure, qb, reverse=False):
+    """Scores by the default paths and by the FP32 matrix cores; reverse: the
+    parameters loaded last to first."""
     import torch
     from paper_2503_02172_amd import kgq
     outs = []
+    if reverse:
+        w.params = dict(reversed(w.params.items()))
     with kgq.engine_for(w, max_batch=qb.batch) as eng:
         for path in (kgq.DENSE_AUTO, kgq.DENSE_FP32):
             eng.set_dense_path(path)
@@ -334,6 +337,25 @@ def test_gpu_split_layers_dominating_unit(model, layer, factor, B):
     auto, fp32 = _auto_and_fp32(w, "2p", qb)
     kw = {"center_reg": w.center_reg} if model == O.CONE else {}
     ref = O.Model(model, w.params, w.gamma, **kw).scores(S["2p"], qb.anchors, qb.relations)
+    rms = lambda x: np.sqrt(np.mean(np.square(x - ref)))
+    assert rms(auto) <= 1.5 * rms(fp32), (rms(auto), rms(fp32))
+
+
+@pytest.mark.parametrize("model", [O.BETAE, O.LOGICE], ids=["betae", "logice"])
+@pytest.mark.parametrize("B,reverse", [(9, False), (200, True)])
+@pytest.mark.parametrize("big", [2.0 ** 11, 2.0 ** 31])
+def test_gpu_split_layers_wide_input_rows(model, B, reverse, big):
+    """Layer inputs with one value far above the others (2^31: more than the
+    2^28 that the form holds in full), and that value's weights as small: the
+    scores' error against 64 bits stays where the FP32 matrix cores have it."""
+    d = 64
+    w = synth.make_tiny(model, n_ent=70, n_rel=7, dim=d, seed=181)
+    col = 2 * d + 5 if model == O.LOGICE else 5
+    w.params["relation"][:, 5] = np.linspace(0.5, 1.0, 7) * big
+    w.params["proj.w1"][:, col] /= np.float32(big)
+    qb = synth.draw_queries("2p", B, 70, 7, seed=182)
+    auto, fp32 = _auto_and_fp32(w, "2p", qb, reverse)
+    ref = O.Model(model, w.params, w.gamma).scores(S["2p"], qb.anchors, qb.relations)
     rms = lambda x: np.sqrt(np.mean(np.square(x - ref)))
     assert rms(auto) <= 1.5 * rms(fp32), (rms(auto), rms(fp32))
 

@@ -131,14 +131,17 @@ def layer32(x, w, b, relu):
     return np.maximum(y, 0) if relu else y
 
 
-def projection(g, d, factors=(1.0, 1.0)):
+def projection(g, d, factors=(1.0, 1.0), big=1.0):
     """Errors of BetaE's three projection layers, (split, float32), with one
-    unit of each hidden layer scaled by a factor and switched off."""
+    unit of each hidden layer scaled by a factor and switched off, and one input
+    value `big` times the others and its weights as small."""
     def make(o, i):
         lim = np.sqrt(6.0 / (o + i))
         return g.uniform(-lim, lim, (o, i)).astype(np.float32), (g.uniform(-1, 1, o) / np.sqrt(i)).astype(np.float32)
     x = (np.maximum(g.uniform(0, 2, (48, 2 * d)), 0.05) + g.uniform(-0.5, 0.5, (48, 2 * d))).astype(np.float32)
     ws = [make(4 * d, 2 * d), make(4 * d, 4 * d), make(2 * d, 4 * d)]
+    x[:, 5] *= np.float32(big)
+    ws[0][0][:, 5] /= np.float32(big)
     for (w, b), f in zip(ws, factors):
         if f > 1:
             w[3] *= np.float32(f)
@@ -160,19 +163,22 @@ def test_layers_no_further_off_than_float32(d):
     assert split <= flt, (split, flt)
 
 
-LIMIT = 4096.0                                       # kSplitSpreadMax
+LIMIT = 16384.0                                      # kSplitSpreadMax
 
 
 @pytest.mark.parametrize("d", [32, 64, 128])
-@pytest.mark.parametrize("factors", [(LIMIT, 1.0), (1.0, LIMIT), (64.0, 64.0)])
-def test_layers_with_a_unit_far_above_the_others(d, factors):
+@pytest.mark.parametrize("factors,big", [((LIMIT, 1.0), 1.0), ((1.0, LIMIT), 1.0), ((128.0, 128.0), 1.0),
+                                         ((1.0, 1.0), LIMIT), ((16.0, 16.0), 64.0)])
+def test_layers_with_a_value_far_above_the_others(d, factors, big):
     """At the largest spread that the form takes, with the unit that makes it
-    switched off, the layers are no further off than float32 ones (10% for the
-    draw); at 2^24 they would be, by far."""
+    switched off or the input value's weights as small, the layers are no
+    further off than float32 ones (10% for the draw); at 2^24 they would be."""
     g = np.random.default_rng(d)
-    split, flt = np.mean([projection(g, d, factors) for _ in range(4)], 0)
+    split, flt = np.mean([projection(g, d, factors, big) for _ in range(4)], 0)
     assert split <= 1.1 * flt, (split, flt)
-    split, flt = projection(g, d, (2.0 ** 24, 1.0))
+    more = 2.0 ** 24 / LIMIT
+    f = [v * more if v == max(*factors, big) else v for v in (*factors, big)]
+    split, flt = projection(g, d, tuple(f[:2]), f[2])
     assert split > 5 * flt
 
 
@@ -203,3 +209,20 @@ def test_split_bound():
         assert not bound([3.0, bad, 4.0], None).fits
     for bad in (np.nan, np.inf, -np.inf, 2.0 ** 41):
         assert not bound([3.0, 4.0], [0.0, bad]).fits
+
+
+def test_table_spread():
+    f = kgq.lib()._ZN3kgq12table_spreadEPKd
+    f.restype = ctypes.c_float
+    f.argtypes = [ctypes.c_void_p]
+
+    def spread(rows):
+        """rows: (largest magnitude, sum of log2, count) of a few workgroups."""
+        p = np.zeros((512, 3))
+        p[:len(rows)] = np.reshape(rows, (-1, 3))
+        return f(p.ctypes.data)
+    assert spread([]) == 1.0                                             # all zeros
+    assert spread([(2.0, 0.0, 4), (8.0, 4.0, 4)]) == np.float32(8.0 / 2.0 ** 0.5)
+    for bad in (np.nan, np.inf, -np.inf):
+        assert spread([(2.0, bad, 4)]) == np.inf
+    assert spread([(np.inf, 3.0, 4)]) == np.inf
