@@ -175,7 +175,9 @@ kgq_status kgq_create(const kgq_config* cfg, kgq_handle** out);
  * gamma; entities closer than that to each other may then score equal, as they
  * mostly do by the score's rounding); and every dense weight, and BetaE's
  * entity-side scoring rows, in the parts that the matrix-core paths read
- * (kgq_set_dense_path).
+ * (kgq_set_dense_path). Which forms the scorer and the layers take is settled
+ * here, by the values: an execute that was enqueued before a load, or captured
+ * before it, keeps the forms of before and has to be issued, or captured, again.
  * Errors: INVALID_ARG (unknown name, wrong nbytes or dtype, null src), OOM, DEVICE. */
 kgq_status kgq_load_params(kgq_handle* h, const char* name, const void* src, size_t nbytes,
                            int32_t dtype, int32_t src_is_device);
